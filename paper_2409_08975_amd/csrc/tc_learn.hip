@@ -69,8 +69,8 @@ __device__ __forceinline__ uint16_t bf16_bits(float f) {
 }
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-// two values that cannot be NaN (outputs of a ReLU), rounded to nearest even
-// in one instruction: a in the low half, b in the high half
+// two values rounded to nearest even in one instruction (a NaN stays a NaN):
+// a in the low half, b in the high half
 __device__ __forceinline__ uint32_t bf16x2_bits(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
@@ -231,13 +231,33 @@ struct MlpOps {
   bf16x8 w2[2][4];  // layer 2, output block ob, K-chunk kc: W2[32 ob + i][krow(kc, s, h)]
 };
 
+// four consecutive parameters (no alignment beyond a float's is assumed)
+struct F4 {
+  float v[4];
+};
+__device__ __forceinline__ F4 load4(const float* __restrict__ p) {
+  F4 r;
+  __builtin_memcpy(&r, p, sizeof(r));
+  return r;
+}
+
 __device__ void load_ops(const float* __restrict__ P, int lane, MlpOps* o) {
   const int i = lane & 31, h = lane >> 5;
+  F4 q1[2], q2[2][4][2];  // every load issued before the first conversion
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) q1[rb] = load4(P + kOffW1 + (32 * rb + i) * kIn + 4 * h);
+#pragma unroll
+  for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+      for (int g = 0; g < 2; ++g)  // krow is consecutive over s = 4 g .. 4 g + 3
+        q2[ob][kc][g] = load4(P + kOffW2 + (32 * ob + i) * kHid + krow(kc, 4 * g, h));
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
     s16x4 v;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) v[s] = (short)bf16_bits(P[kOffW1 + (32 * rb + i) * kIn + 4 * h + s]);
+    for (int s = 0; s < 4; ++s) v[s] = (short)bf16_bits(q1[rb].v[s]);
     o->w1[rb] = v;
   }
 #pragma unroll
@@ -246,7 +266,7 @@ __device__ void load_ops(const float* __restrict__ P, int lane, MlpOps* o) {
     for (int kc = 0; kc < 4; ++kc) {
       uint16_t e[8];
 #pragma unroll
-      for (int s = 0; s < 8; ++s) e[s] = bf16_bits(P[kOffW2 + (32 * ob + i) * kHid + krow(kc, s, h)]);
+      for (int s = 0; s < 8; ++s) e[s] = bf16_bits(q2[ob][kc][s >> 2].v[s & 3]);
       o->w2[ob][kc] = pack8(e);
     }
 }
@@ -268,6 +288,7 @@ __device__ void load_vecs(const float* __restrict__ P, MlpVecs* s) {
 struct Fwd {
   f32x16 z1[2], z2[2];
   bf16x8 h1[4];  // layer-2 B operand chunks (relu(z1) in bfloat16)
+  uint32_t h2[2][8];  // relu(z2) in bfloat16, two per word
   float z3;
 };
 
@@ -306,6 +327,7 @@ __device__ __forceinline__ void mlp_fwd(const MlpOps& o, const MlpVecs& sv, s16x
 #pragma unroll
     for (int v = 0; v < 16; v += 2) {
       const uint32_t pr = bf16x2_bits(fmaxf(c[v], 0.0f), fmaxf(c[v + 1], 0.0f));
+      r->h2[ob][v >> 1] = pr;
       part += sv.w3[32 * ob + drow(v, h) + z] * __uint_as_float(pr << 16);
       part += sv.w3[32 * ob + drow(v + 1, h) + z] * __uint_as_float(pr & 0xFFFF0000u);
     }
@@ -315,10 +337,6 @@ __device__ __forceinline__ void mlp_fwd(const MlpOps& o, const MlpVecs& sv, s16x
 }
 
 __device__ __forceinline__ float sigmoidf(float z) { return 1.0f / (1.0f + expf(-z)); }
-__device__ __forceinline__ float softplusf(float x) {
-  return fmaxf(x, 0.0f) + log1pf(expf(-fabsf(x)));
-}
-
 __device__ __forceinline__ s16x4 load_feat4(const uint16_t* __restrict__ feat, int64_t row, int h) {
   const uint2 q = *reinterpret_cast<const uint2*>(feat + row * kIn + 4 * h);
   s16x4 v;
@@ -365,30 +383,112 @@ constexpr int kTS = 40;  // LDS row stride (bfloat16 entries) of a 64 x 32 tile
 
 struct GradLds {
   MlpVecs sv;
-  uint16_t w2b[kHid * kHid];  // W2 in bfloat16, row-major
+  // W2 in bfloat16 as MFMA A operands, eight entries of a lane together at
+  // ((block 4 + kc) 2 + h) 32 + i: W2[32 ob + i][krow(kc, 0..7, h)] for the
+  // forward layer and W2[krow(kc, 0..7, h)][32 kb + i] for dH1 = W2^T dZ2
+  bf16x8 w2f[2 * 4 * 2 * 32], w2t[2 * 4 * 2 * 32];
   alignas(16) uint16_t dz2[kGradWaves][kHid * kTS];
   alignas(16) uint16_t h1[kGradWaves][kHid * kTS];
   alignas(16) uint16_t dz1[kGradWaves][kHid * kTS];
   alignas(16) uint16_t f[kGradWaves][32 * 8];
-  float red[kGradWaves][kNParams + 1];
+  alignas(16) float red[kGradWaves][kNParams + 1];
 };
 
 // Label row of item i of the current batch: index = (mul * (start + i) + add)
 // mod n of the label arrays (a bijection of [0, n) when gcd(mul, n) = 1).
 struct BatchMap {
-  uint64_t mul, add, n, start;
+  uint64_t mul, base, n;  // base = (mul * start + add) mod n
+  double inv_n;
   uint32_t count;
   uint64_t n_feat;  // feature rows; labels whose row is outside are ignored
   float label_cap;  // 0: y = [X > 0]; else y = min(1, X / label_cap)
 };
 
-// mul < n and start + i < n with n < 2^31, so the product fits 64 bits
+static BatchMap batch_map(uint64_t mul, uint64_t add, uint64_t n, uint64_t start, uint32_t count,
+                          uint64_t n_feat, float label_cap) {
+  return BatchMap{mul, (mul * start + add) % n, n, 1.0 / (double)n, count, n_feat, label_cap};
+}
+
+// x = base + mul i stays below 2^53 (mul < n < 2^31 and i < 2^20 in training;
+// mul = 1 otherwise), so its binary64 quotient by n is off by at most one.
 __device__ __forceinline__ uint64_t batch_index(const BatchMap& bm, uint64_t i) {
-  return (bm.mul * (bm.start + i) + bm.add) % bm.n;
+  const uint64_t x = bm.base + bm.mul * i;
+  int64_t r = (int64_t)(x - (uint64_t)((double)x * bm.inv_n) * bm.n);
+  if (r < 0) r += (int64_t)bm.n;
+  if (r >= (int64_t)bm.n) r -= (int64_t)bm.n;
+  return (uint64_t)r;
+}
+
+// The label of lane i of a tile: its feature half-row and target.
+struct Label {
+  s16x4 fb;
+  float y;
+  bool valid;
+};
+
+__device__ __forceinline__ Label load_label(const BatchMap& bm, const uint16_t* __restrict__ feat,
+                                            const uint32_t* __restrict__ rows,
+                                            const uint64_t* __restrict__ X, uint32_t tile,
+                                            uint32_t tiles, int i, int h) {
+  const uint32_t item = tile * 32 + i;
+  Label l{s16x4{0, 0, 0, 0}, 0.0f, false};
+  if (tile < tiles && item < bm.count) {
+    const uint64_t idx = batch_index(bm, item);
+    const int64_t row = rows ? (int64_t)rows[idx] : (int64_t)idx;
+    const uint64_t xv = X[idx];
+    l.valid = (uint64_t)row < bm.n_feat;
+    if (l.valid) l.fb = load_feat4(feat, row, h);
+    l.y = bm.label_cap > 0.0f ? fminf(1.0f, __fdiv_rn((float)xv, bm.label_cap))
+                              : (xv != 0 ? 1.0f : 0.0f);
+  }
+  return l;
+}
+
+// Sum over the 32 lanes of each half of 64 values per lane, spread out: at
+// step OFF a lane keeps half of its values and adds the copies of them that
+// lane i ^ OFF holds, so the 64 sums cost 62 additions instead of 320, each
+// formed by the same tree as a butterfly over the lanes.  Lane i is left
+// with the sums of values 2 i and 2 i + 1 in val[0] and val[1].  Inside a row
+// of 16 lanes the other lane's value is a DPP operand (rotations by 8, by
+// 12 or 4, quad permutations); rows are exchanged by a bpermute.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(
+      0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, true));
+}
+// CLO brings lane i + OFF of the row to a lane with (i & OFF) = 0, CHI lane
+// i - OFF to the others
+template <int OFF, int CLO, int CHI>
+__device__ __forceinline__ void half_sum_step(float (&val)[64], int i) {
+  const bool up = (i & OFF) != 0;
+#pragma unroll
+  for (int k = 0; k < 2 * OFF; ++k) {
+    const float lo = val[k] + dpp_f32<CLO>(val[k]);
+    const float hi = val[k + 2 * OFF] + dpp_f32<CHI>(val[k + 2 * OFF]);
+    val[k] = up ? hi : lo;
+  }
+}
+__device__ __forceinline__ void half_sums64(float (&val)[64], int i) {
+#pragma unroll
+  for (int k = 0; k < 32; ++k) {
+    const bool up = (i & 16) != 0;
+    const float send = up ? val[k] : val[k + 32];
+    const float keep = up ? val[k + 32] : val[k];
+    val[k] = keep + __shfl_xor(send, 16, kWave);
+  }
+  half_sum_step<8, 0x128, 0x128>(val, i);
+  half_sum_step<4, 0x12C, 0x124>(val, i);
+  half_sum_step<2, 0x4E, 0x4E>(val, i);
+  half_sum_step<1, 0xB1, 0xB1>(val, i);
 }
 
 // Partial loss and gradient of one block over its tiles of the batch; the
-// tile-to-block assignment depends only on the launch shape.
+// tile-to-block assignment depends only on the launch shape.  A batch of
+// 8,192 labels is one tile per wavefront on 64 blocks, so the launch is as
+// long as one wavefront's chain of label gathers, layers and sums: the first
+// tile's labels are fetched before the parameters, the sums over a tile's 32
+// edges are spread over the lanes, and every operand is read as 16-byte
+// words.  At 8,192 labels 37.3 -> 13.2 us.
 __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict__ P,
                                                          const uint16_t* __restrict__ feat,
                                                          const uint32_t* __restrict__ rows,
@@ -397,12 +497,53 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict
                                                          float* __restrict__ partial) {
   extern __shared__ char s_raw[];
   GradLds& L = *reinterpret_cast<GradLds*>(s_raw);
+  const int lane = threadIdx.x & 63, h = lane >> 5, i = lane & 31;
+  const int wave = (int)uni(threadIdx.x >> 6);
+  const uint32_t tiles = (bm.count + 31) / 32;
+  const uint32_t first = blockIdx.x * kGradWaves + wave;
+  Label lab = load_label(bm, feat, rows, X, first, tiles, i, h);
   load_vecs(P, &L.sv);
-  const int lane = threadIdx.x & 63, h = lane >> 5, i = lane & 31, wave = threadIdx.x >> 6;
+  // every operand is read from memory once per block
+  constexpr int kSlots = 2 * 4 * 2 * 32 / kGradBlock;
+  F4 qf[kSlots][2];
+  float qt[kSlots][8];
+  F4 q1[2];
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) {
+    const int sl = q * kGradBlock + threadIdx.x;
+    const int si = sl & 31, sh = (sl >> 5) & 1, kc = (sl >> 6) & 3, b = sl >> 8;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)  // krow is consecutive over s = 4 g .. 4 g + 3
+      qf[q][g] = load4(P + kOffW2 + (32 * b + si) * kHid + krow(kc, 4 * g, sh));
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qt[q][s] = P[kOffW2 + krow(kc, s, sh) * kHid + 32 * b + si];
+  }
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) q1[rb] = load4(P + kOffW1 + (32 * rb + i) * kIn + 4 * h);
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) {
+    uint16_t ef[8], et[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      ef[s] = bf16_bits(qf[q][s >> 2].v[s & 3]);
+      et[s] = bf16_bits(qt[q][s]);
+    }
+    L.w2f[q * kGradBlock + threadIdx.x] = pack8(ef);
+    L.w2t[q * kGradBlock + threadIdx.x] = pack8(et);
+  }
   MlpOps o;
-  load_ops(P, lane, &o);
-  for (int j = threadIdx.x; j < kHid * kHid; j += blockDim.x) L.w2b[j] = bf16_bits(P[kOffW2 + j]);
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {
+    s16x4 v;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v[s] = (short)bf16_bits(q1[rb].v[s]);
+    o.w1[rb] = v;
+  }
   __syncthreads();
+#pragma unroll
+  for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc) o.w2[ob][kc] = L.w2f[((ob * 4 + kc) * 2 + h) * 32 + i];
   const float inv_n = 1.0f / (float)bm.count;
   f32x16 gW2[2][2], gW1[2];
 #pragma unroll
@@ -412,91 +553,79 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict
     for (int b2 = 0; b2 < 2; ++b2) gW2[a2][b2] = f32x16{};
   }
   float gb3 = 0.0f, loss = 0.0f;
-  // this wave's partial gradient; w3 and b2 are accumulated here tile by tile
-  float* red = L.red[wave];
-  for (int j = lane; j <= kNParams; j += kWave) red[j] = 0.0f;
+  float g32[2] = {0.0f, 0.0f};  // this lane's two of the w3 and b2 gradients (half_sums64)
   uint16_t* tdz2 = L.dz2[wave];
   uint16_t* th1 = L.h1[wave];
   uint16_t* tdz1 = L.dz1[wave];
   uint16_t* tf = L.f[wave];
-  const uint32_t tiles = (bm.count + 31) / 32;
-  // uniform trip count over the block so the barriers below are uniform
-  const uint32_t per_round = gridDim.x * kGradWaves;
-  for (uint32_t base = blockIdx.x * kGradWaves; base < tiles; base += per_round) {
-    const uint32_t tile = base + wave;
-    const uint32_t item = tile * 32 + i;
-    const bool in_batch = tile < tiles && item < bm.count;
-    int64_t row = 0;
-    float y = 0.0f;
-    bool valid = in_batch;
-    if (in_batch) {
-      const uint64_t idx = batch_index(bm, item);
-      row = rows ? (int64_t)rows[idx] : (int64_t)idx;
-      const uint64_t xv = X[idx];
-      y = bm.label_cap > 0.0f ? fminf(1.0f, __fdiv_rn((float)xv, bm.label_cap))
-                              : (xv != 0 ? 1.0f : 0.0f);
-      valid = (uint64_t)row < bm.n_feat;
-    }
-    const s16x4 fb = valid ? load_feat4(feat, row, h) : s16x4{0, 0, 0, 0};
+  const uint32_t stride = gridDim.x * kGradWaves;
+  for (uint32_t tile = first; tile < tiles; tile += stride) {  // uniform over the wavefront
+    const s16x4 fb = lab.fb;
+    const bool valid = lab.valid;
+    const float y = lab.y;
+    if (tile + stride < tiles) lab = load_label(bm, feat, rows, X, tile + stride, tiles, i, h);
     Fwd r;
     mlp_fwd(o, L.sv, fb, h, &r);
     const float gz = sigmoidf(r.z3);
     const float dz3 = valid ? (gz - y) * inv_n : 0.0f;
     if (h == 0 && valid) {
-      loss += y * softplusf(-r.z3) + (1.0f - y) * softplusf(r.z3);
+      // the two softplus terms share log1p(exp(-|z|))
+      const float tail = log1pf(expf(-fabsf(r.z3)));
+      loss += y * (fmaxf(-r.z3, 0.0f) + tail) + (1.0f - y) * (fmaxf(r.z3, 0.0f) + tail);
       gb3 += dz3;
     }
     // layer 3 and dZ2 (registers, rows drow(v, h) of block ob, edge i); the
     // w3 and b2 gradients are summed over the tile's 32 edges right away
-    uint16_t dz2b[2][16];
+    bf16x8 dzc[4];  // dZ2 in bfloat16: the B operand of dH1
+    float val[64];  // w3 terms, then b2 terms, 16 ob + v each
 #pragma unroll
-    for (int ob = 0; ob < 2; ++ob)
+    for (int ob = 0; ob < 2; ++ob) {
+      uint32_t pk[8];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int rr = 32 * ob + drow(v, h);
-        const float z2 = r.z2[ob][v];
-        float s3 = dz3 * bf16_round(fmaxf(z2, 0.0f));
-        const float d = z2 > 0.0f ? L.sv.w3[rr] * dz3 : 0.0f;
-        float s2 = d;
-        dz2b[ob][v] = bf16_bits(d);
+      for (int v = 0; v < 16; v += 2) {
+        float d[2];
 #pragma unroll
-        for (int off = 16; off > 0; off >>= 1) {
-          s3 += __shfl_xor(s3, off, kWave);
-          s2 += __shfl_xor(s2, off, kWave);
+        for (int e = 0; e < 2; ++e) {
+          d[e] = r.z2[ob][v + e] > 0.0f ? L.sv.w3[32 * ob + drow(v + e, h)] * dz3 : 0.0f;
+          val[32 + 16 * ob + v + e] = d[e];
         }
-        if (i == 0) {
-          red[kOffW3 + rr] += s3;
-          red[kOffB2 + rr] += s2;
-        }
+        const uint32_t pr = r.h2[ob][v >> 1];
+        val[16 * ob + v] = dz3 * __uint_as_float(pr << 16);
+        val[16 * ob + v + 1] = dz3 * __uint_as_float(pr & 0xFFFF0000u);
+        pk[v >> 1] = bf16x2_bits(d[0], d[1]);
       }
-    // dH1 = W2^T dZ2, then dZ1 = dH1 * [z1 > 0]
-    bf16x8 dzc[4];
 #pragma unroll
-    for (int kc = 0; kc < 4; ++kc) {
-      uint16_t e[8];
-#pragma unroll
-      for (int s = 0; s < 8; ++s) e[s] = dz2b[kc >> 1][8 * (kc & 1) + s];
-      dzc[kc] = pack8(e);
+      for (int c = 0; c < 2; ++c)
+        dzc[2 * ob + c] = __builtin_bit_cast(
+            bf16x8, uint4{pk[4 * c], pk[4 * c + 1], pk[4 * c + 2], pk[4 * c + 3]});
     }
+    half_sums64(val, i);
+    g32[0] += val[0];
+    g32[1] += val[1];
+    // dH1 = W2^T dZ2, then dZ1 = dH1 * [z1 > 0]
     // stage dZ2, H1, dZ1 and F with edges along rows for the weight gradients
+    // (each wavefront its own tiles)
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
       f32x16 c = f32x16{};
 #pragma unroll
       for (int kc = 0; kc < 4; ++kc) {
-        // A operand of dH1 = W2^T dZ2: W2[krow(kc, s, h)][32 kb + i]
-        uint16_t e[8];
-#pragma unroll
-        for (int s = 0; s < 8; ++s) e[s] = L.w2b[krow(kc, s, h) * kHid + 32 * kb + i];
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pack8(e), dzc[kc], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L.w2t[((kb * 4 + kc) * 2 + h) * 32 + i],
+                                                    dzc[kc], c, 0, 0, 0);
       }
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int rr = 32 * kb + drow(v, h);
-        const float z1 = r.z1[kb][v];
-        tdz1[rr * kTS + i] = bf16_bits(z1 > 0.0f ? c[v] : 0.0f);
-        th1[rr * kTS + i] = bf16_bits(fmaxf(z1, 0.0f));
-        tdz2[rr * kTS + i] = dz2b[kb][v];
+      for (int v = 0; v < 16; v += 2) {
+        const int r0 = (32 * kb + drow(v, h)) * kTS + i, r1 = r0 + kTS;  // rows of v, v + 1
+        const uint32_t pd = bf16x2_bits(r.z1[kb][v] > 0.0f ? c[v] : 0.0f,
+                                        r.z1[kb][v + 1] > 0.0f ? c[v + 1] : 0.0f);
+        const s16x8 ph = __builtin_bit_cast(s16x8, r.h1[2 * kb + (v >> 3)]);
+        const s16x8 pz = __builtin_bit_cast(s16x8, dzc[2 * kb + (v >> 3)]);
+        tdz1[r0] = (uint16_t)pd;
+        tdz1[r1] = (uint16_t)(pd >> 16);
+        th1[r0] = (uint16_t)ph[v & 7];
+        th1[r1] = (uint16_t)ph[(v & 7) + 1];
+        tdz2[r0] = (uint16_t)pz[v & 7];
+        tdz2[r1] = (uint16_t)pz[(v & 7) + 1];
       }
     }
     {
@@ -504,7 +633,8 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict
                        (uint32_t)(uint16_t)fb[2] | ((uint32_t)(uint16_t)fb[3] << 16)};
       *reinterpret_cast<uint2*>(tf + i * 8 + 4 * h) = q;
     }
-    __syncthreads();
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
     // dW2[32 ob + .][32 kb + .] += dZ2 H1^T and [dW1 | db1] += dZ1 [F | 1]^T,
     // contracting over the 32 edges (two K-chunks of 16)
 #pragma unroll
@@ -533,9 +663,16 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict
         gW1[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, Bf, gW1[rb], 0, 0, 0);
       }
     }
-    __syncthreads();
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();  // the next tile rewrites the staged ones
   }
   // per-wave partials into LDS, then the block sum in wave order
+  float* red = L.red[wave];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int k = 2 * i + e, v = k & 15, ob = (k >> 4) & 1;
+    red[(k & 32 ? kOffB2 : kOffW3) + 32 * ob + drow(v, h)] = g32[e];
+  }
 #pragma unroll
   for (int ob = 0; ob < 2; ++ob)
 #pragma unroll
@@ -559,11 +696,17 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict
     }
   }
   __syncthreads();
-  for (int j = threadIdx.x; j <= kNParams; j += blockDim.x) {
-    float s = 0.0f;
+  // two parameters per thread and round (an even row length)
+  static_assert((kNParams + 1) % 2 == 0, "pairs of a partial row");
+  for (int j = threadIdx.x; j < (kNParams + 1) / 2; j += kGradBlock) {
+    float2 s{0.0f, 0.0f};
 #pragma unroll
-    for (int w = 0; w < kGradWaves; ++w) s += L.red[w][j];
-    partial[(size_t)blockIdx.x * (kNParams + 1) + j] = s;
+    for (int w = 0; w < kGradWaves; ++w) {
+      const float2 v = *reinterpret_cast<const float2*>(&L.red[w][2 * j]);
+      s.x += v.x;
+      s.y += v.y;
+    }
+    reinterpret_cast<float2*>(partial + (size_t)blockIdx.x * (kNParams + 1))[j] = s;
   }
 }
 
@@ -577,15 +720,32 @@ struct AdamArgs {
   float bc1, bc2;    // 1 - beta^step
 };
 
-__global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ partial, int nblocks,
-                                                    int mode, float* __restrict__ grad,
-                                                    float* __restrict__ loss, float loss_scale,
-                                                    float* __restrict__ params,
-                                                    float* __restrict__ opt, AdamArgs ad) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// One thread per parameter.  Its partials (1.2 MB over 64 blocks, mostly from
+// other XCDs' writes) are fetched 32 at a time and added in block order: the
+// launch takes two or three memory round trips instead of one per few
+// blocks (64 blocks' partials: 16.6 -> 5.1 us).
+constexpr int kReduceBlock = 64;
+constexpr int kReduceGrid = (kNParams + kReduceBlock) / kReduceBlock;
+__global__ __launch_bounds__(kReduceBlock) void k_mlp_reduce(
+    const float* __restrict__ partial, int nblocks, int mode, float* __restrict__ grad,
+    float* __restrict__ loss, float loss_scale, float* __restrict__ params,
+    float* __restrict__ opt, AdamArgs ad) {
+  const int j = blockIdx.x * kReduceBlock + threadIdx.x;
   if (j > kNParams || (j == kNParams && !loss)) return;
+  const bool adam = mode == 1 && j < kNParams;
+  const float o1 = adam ? opt[j] : 0.0f, o2 = adam ? opt[kNParams + j] : 0.0f;
+  const float p0 = adam ? params[j] : 0.0f;
   float s = 0.0f;
-  for (int b = 0; b < nblocks; ++b) s += partial[(size_t)b * (kNParams + 1) + j];
+  constexpr int kAtOnce = 32;
+  for (int b0 = 0; b0 < nblocks; b0 += kAtOnce) {
+    float v[kAtOnce];
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q)
+      v[q] = b0 + q < nblocks ? partial[(size_t)(b0 + q) * (kNParams + 1) + j] : 0.0f;
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q)
+      if (b0 + q < nblocks) s += v[q];
+  }
   if (j == kNParams) {
     // loss: sum over rows / batch size, scaled (e.g. 1 / batches per epoch)
     *loss += s * loss_scale;
@@ -595,14 +755,12 @@ __global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ pa
     grad[j] = s;
     return;
   }
-  float* m1 = opt;
-  float* m2 = opt + kNParams;
-  const float mj = ad.beta1 * m1[j] + ad.omb1 * s;
-  const float vj = ad.beta2 * m2[j] + ad.omb2 * (s * s);
-  m1[j] = mj;
-  m2[j] = vj;
+  const float mj = ad.beta1 * o1 + ad.omb1 * s;
+  const float vj = ad.beta2 * o2 + ad.omb2 * (s * s);
+  opt[j] = mj;
+  opt[kNParams + j] = vj;
   const float mh = mj / ad.bc1, vh = vj / ad.bc2;
-  params[j] -= ad.lr * mh / (sqrtf(vh) + ad.eps);
+  params[j] = p0 - ad.lr * mh / (sqrtf(vh) + ad.eps);
 }
 
 __global__ void k_zero_f32(float* p, int n) {
@@ -742,12 +900,12 @@ tc_status mlp_grad(const float* params, const uint16_t* feat, int64_t n_feat, co
                    const uint64_t* X, int64_t n, float label_cap, float* grad, float* loss,
                    void* ws, size_t ws_bytes, hipStream_t st) {
   if (ws_bytes < mlp_workspace_bytes(n)) return TC_E_WORKSPACE;
-  const BatchMap bm{1, 0, (uint64_t)n, 0, (uint32_t)n, (uint64_t)n_feat, label_cap};
+  const BatchMap bm = batch_map(1, 0, (uint64_t)n, 0, (uint32_t)n, (uint64_t)n_feat, label_cap);
   float* partial = (float*)ws;
   tc_status s = launch_grad(params, feat, rows, X, bm, partial, st);
   if (s != TC_OK) return s;
   hipLaunchKernelGGL(k_zero_f32, dim3(1), dim3(64), 0, st, loss, 1);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((kNParams + 256) / 256), dim3(256), 0, st,
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(kReduceGrid), dim3(kReduceBlock), 0, st,
                      (const float*)partial, mlp_grad_blocks(n), 0, grad, loss, 1.0f / (float)n,
                      (float*)nullptr, (float*)nullptr, AdamArgs{});
   return hipGetLastError() == hipSuccess ? TC_OK : TC_E_HIP;
@@ -769,7 +927,7 @@ static AdamArgs adam_args(int64_t step, float lr) {
 tc_status mlp_adam(float* params, float* opt, const float* grad, int64_t step, float lr,
                    hipStream_t st) {
   // the gradient is one "partial" of one block
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((kNParams + 256) / 256), dim3(256), 0, st, grad, 1, 1,
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(kReduceGrid), dim3(kReduceBlock), 0, st, grad, 1, 1,
                      (float*)nullptr, (float*)nullptr, 0.0f, params, opt, adam_args(step, lr));
   return hipGetLastError() == hipSuccess ? TC_OK : TC_E_HIP;
 }
@@ -804,11 +962,12 @@ tc_status mlp_train(float* params, float* opt, const uint16_t* feat, int64_t n_f
     for (int64_t bi = 0; bi < nbatches; ++bi) {
       const uint64_t start = (uint64_t)bi * (uint64_t)batch;
       const uint32_t count = (uint32_t)std::min<int64_t>(batch, n - (int64_t)start);
-      const BatchMap bm{mul, add, (uint64_t)n, start, count, (uint64_t)n_feat, label_cap};
+      const BatchMap bm =
+          batch_map(mul, add, (uint64_t)n, start, count, (uint64_t)n_feat, label_cap);
       tc_status s = launch_grad(params, feat, rows, X, bm, partial, st);
       if (s != TC_OK) return s;
       ++step;
-      hipLaunchKernelGGL(k_mlp_reduce, dim3((kNParams + 256) / 256), dim3(256), 0, st,
+      hipLaunchKernelGGL(k_mlp_reduce, dim3(kReduceGrid), dim3(kReduceBlock), 0, st,
                          (const float*)partial, mlp_grad_blocks(count), 1, (float*)nullptr,
                          loss_per_epoch ? loss_per_epoch + e : (float*)nullptr,
                          1.0f / ((float)count * (float)nbatches), params, opt,

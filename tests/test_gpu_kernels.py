@@ -1,0 +1,66 @@
+"""GPU tests of single kernel branches at the sizes where they change: tile
+remainders, the first size on either side of a dispatch rule, and inputs
+that only one branch sees."""
+import math
+
+import numpy as np
+import pytest
+
+import synthgraph as sg
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tcb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_08975_amd as tcb
+    tcb.lib()
+    return tcb
+
+
+@pytest.fixture(scope="module")
+def torch_mod():
+    import torch
+    return torch
+
+
+def _philox(seed, stream, i):
+    c, k = [i & 0xFFFFFFFF, i >> 32, 0, stream], [seed & 0xFFFFFFFF, seed >> 32]
+    for _ in range(10):
+        p0, p1 = 0xD2511F53 * c[0], 0xCD9E8D57 * c[2]
+        c = [(p1 >> 32) ^ c[1] ^ k[0], p1 & 0xFFFFFFFF, (p0 >> 32) ^ c[3] ^ k[1], p0 & 0xFFFFFFFF]
+        k = [(k[0] + 0x9E3779B9) & 0xFFFFFFFF, (k[1] + 0xBB67AE85) & 0xFFFFFFFF]
+    return c
+
+
+@pytest.mark.parametrize("n,batch", [(1, 32), (33, 32), (70001, 65536), (1500007, 1 << 20)])
+def test_train_equals_single_steps(tcb, torch_mod, n, batch):
+    """An epoch equals, bit for bit, one gradient and one Adam step per batch
+    over the labels in the epoch's Philox order formed here in Python
+    integers: one tile, a ragged tile, more tiles than wavefronts, and label
+    indices whose product with the multiplier passes 2^32."""
+    torch = torch_mod
+    seed, lr = 0x123456789, 1e-3
+    rng = np.random.default_rng(n)
+    F = torch.from_numpy(sg.random_bf16_bits(n, (5000, 8)).view(np.int16)).cuda()
+    P = sg.random_params(n)
+    rows = rng.integers(0, 5000, size=n).astype(np.int32)
+    X = sg.random_counts(n, n).view(np.int64)
+    p1, o1 = torch.from_numpy(P.copy()).cuda(), torch.zeros(2 * tcb.MLP_PARAMS, device="cuda")
+    p2, o2 = p1.clone(), o1.clone()
+    rd, Xd = torch.from_numpy(rows).cuda(), torch.from_numpy(X).cuda()
+    tcb.tc_mlp_train(p1, o1, F, rd, Xd, batch, 1, lr, seed)
+    x0, x1, x2, x3 = _philox(seed, 0x4D4C5000, 0)
+    mul = 1 + ((x1 << 32) | x0) % (n - 1) if n > 1 else 1
+    while math.gcd(mul, n) != 1:
+        mul = mul + 1 if mul + 1 < n else 1
+    add = ((x3 << 32) | x2) % n
+    order = (mul * torch.arange(n, device="cuda") + add) % n
+    for step, start in enumerate(range(0, n, batch), 1):
+        i = order[start:start + batch]
+        g, _ = tcb.tc_mlp_grad(p2, F, rd[i].contiguous(), Xd[i].contiguous())
+        tcb.tc_mlp_adam(p2, o2, g, step, lr)
+    assert torch.equal(p1, p2) and torch.equal(o1, o2)
