@@ -64,3 +64,36 @@ def test_train_equals_single_steps(tcb, torch_mod, n, batch):
         g, _ = tcb.tc_mlp_grad(p2, F, rd[i].contiguous(), Xd[i].contiguous())
         tcb.tc_mlp_adam(p2, o2, g, step, lr)
     assert torch.equal(p1, p2) and torch.equal(o1, o2)
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 2048 * 32 * 4 + 5])
+def test_mlp_forward_tiles_and_special_values(tcb, torch_mod, n):
+    """Network scores over one ragged tile up to more tiles than the launch
+    has wavefronts with all their prefetched tiles, with infinite and NaN
+    features among the rows: a ReLU takes NaN to 0, so the scores agree with
+    a float64 network that does the same, NaN for NaN."""
+    torch = torch_mod
+    bits = sg.random_bf16_bits(n, (n, 8))
+    special = [0x7F80, 0xFF80, 0x7FC0, 0x0000, 0x8000]
+    for k, b in enumerate(special):
+        if 3 * k < n:
+            bits[3 * k, k] = b
+    P = sg.random_params(7)
+    g = tcb.tc_mlp_forward(torch.from_numpy(P).cuda(),
+                           torch.from_numpy(bits.view(np.int16)).cuda()).cpu().numpy()
+
+    def bf(x):  # bfloat16 rounding of float64 values (via float32)
+        return torch.from_numpy(x).float().to(torch.bfloat16).double().numpy()
+
+    with np.errstate(all="ignore"):
+        f = (bits.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+        w1, b1, w2 = bf(P[:512].astype(np.float64)).reshape(64, 8), P[512:576], bf(P[576:4672].astype(np.float64))
+        b2, w3, b3 = P[4672:4736], bf(P[4736:4800].astype(np.float64)), P[4800]
+        relu = lambda z: bf(np.where(z > 0, z, 0.0))  # noqa: E731
+        h1 = relu((f[:, None, :] * w1).sum(2) + b1) if n < 100 else relu(f @ w1.T + b1)
+        h2 = relu(h1 @ w2.reshape(64, 64).T + b2)
+        want = 1.0 / (1.0 + np.exp(-(h2 @ w3 + b3)))
+    assert np.array_equal(np.isnan(g), np.isnan(want))
+    ok = ~np.isnan(want)
+    # a bfloat16 ulp of one hidden activation is 2^-8 of it
+    assert np.max(np.abs(g[ok] - want[ok])) <= 4e-3
