@@ -97,3 +97,16 @@ def test_mlp_forward_tiles_and_special_values(tcb, torch_mod, n):
     ok = ~np.isnan(want)
     # a bfloat16 ulp of one hidden activation is 2^-8 of it
     assert np.max(np.abs(g[ok] - want[ok])) <= 4e-3
+
+
+@pytest.mark.parametrize("m,delta", [(1, 5), (7, 0), (2048, 40), (2049, 3), (6000, 10**9)])
+def test_features_long_runs_and_tiles(tcb, torch_mod, m, delta):
+    """Edge features on five vertices (pair runs of hundreds of entries and
+    equal times, both directions of every pair) at the scan's tile edges:
+    float32 evaluation and one bfloat16 rounding, so within 2^-8."""
+    from test_gpu_parity import build_both
+    G, og = build_both(tcb, torch_mod, sg.gen_micro(m, n=5, m=m, t_span=200))
+    F = tcb.tc_edge_features(G, tcb.tc_path_weights(G, delta)).cpu().numpy().view(np.uint16)
+    got = (F.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    want = og.features(og.weights(delta))
+    assert np.all(np.abs(got - want) <= 2.0**-8 * np.abs(want) + 1e-6)
