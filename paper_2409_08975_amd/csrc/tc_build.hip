@@ -6,15 +6,18 @@
 // per-vertex lists; the tie order is this library's convention).
 //
 // Radix sort design (gfx950, wave64): every sort moves 16-byte edge
-// records, tiles of 1536 records per 256-thread block; the last pass of a
-// vertex sort writes the graph's columns instead of records.  A pass is (1)
-// per-tile digit histograms written tile-major (each tile's 256 or 512
-// counts are one contiguous row), (2) a column scan of that [tiles][bins]
-// matrix that turns every count into the tile's global offset for its digit,
-// (3) a scatter that ranks keys stably inside the tile with wavefront
-// ballots (one ballot per digit bit gives the lanes sharing a digit), stages
-// the tile in LDS in digit order and writes each digit run to its global
-// slot with coalesced stores.
+// records in tiles of 512 threads; the last pass of a vertex sort writes the
+// graph's columns instead of records.  A pass is (1) per-tile digit
+// histograms written tile-major (one contiguous row of counts per tile), (2)
+// a column scan of that matrix that turns every count into the keys of its
+// digit in the tiles before, (3) a scatter that ranks keys stably inside the
+// tile with wavefront ballots (one ballot per digit bit gives the lanes
+// sharing a digit), exchanges the tile through LDS into digit order and
+// writes each digit run to its global slot with coalesced stores.  Digits
+// have up to 11 bits: a pass costs about the same whatever its digit (the
+// memory rate bounds it), so fewer, wider digits win as long as a tile still
+// holds a few records per digit; the tile is as large as the LDS exchange
+// allows for that reason.
 //
 // The whole build is one stream-ordered launch sequence: it allocates
 // nothing, never waits on the device, and can be captured in a HIP graph.
@@ -27,12 +30,22 @@
 
 namespace tc {
 
-constexpr int kSortBlock = 256;
+constexpr int kSortBlock = 512;
+constexpr int kSortWaves = kSortBlock / kWave;
 constexpr uint32_t kXcds = 8;  // accelerator complex dies of an MI355X, each with its own L2
-constexpr int kRecItems = 6;  // record-carrying sorts: 1536-entry tiles (LDS holds 16 B/entry)
-constexpr int kRecTile = kSortBlock * kRecItems;
 constexpr int kColChunk = 32;  // tiles per chunk of the histogram column scan
-constexpr int kMaxBins = 512;  // digits of at most 9 bits
+constexpr int kMaxDigit = 11;
+constexpr int kMaxBins = 1 << kMaxDigit;
+constexpr int kMinBins = 64;  // histogram rows are at least one 256-byte line
+// Records per thread: tiles of 4,096 records, or of 2,048 where the larger
+// ones would be too few to fill the CUs.
+constexpr int kItemsLarge = 8, kItemsSmall = 4;
+constexpr int64_t kLargeFrom = 3000000;
+static bool large_tiles(int64_t m) { return m >= kLargeFrom; }
+static int64_t sort_tiles(int64_t m) {
+  const int64_t t = (int64_t)kSortBlock * (large_tiles(m) ? kItemsLarge : kItemsSmall);
+  return (m + t - 1) / t;
+}
 
 static unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
@@ -45,12 +58,13 @@ __global__ void k_init_build(uint32_t* status, uint64_t* tminmax) {
   }
 }
 
-// The validation, which also counts the low byte of every time per sort tile
-// (tile-major rows of 256, as the radix histograms): the first pass of the
-// time sort takes its digit counts from these rows once t_min is known
-// (k_fold_hist), so it needs no histogram read of its own.  Each block walks
-// tiles blockIdx.x, blockIdx.x + gridDim.x, ...
+// The validation, which also counts the low kMaxDigit bits of every time per
+// sort tile (tile-major rows of kMaxBins): the first pass of the time sort
+// takes its digit counts from these rows once t_min is known (k_fold_hist), so
+// it needs no histogram read of its own.  Each block walks tiles blockIdx.x,
+// blockIdx.x + gridDim.x, ...
 // t is mapped to an order-preserving unsigned key (flip the sign bit)
+template <int ITEMS>
 __global__ __launch_bounds__(kSortBlock) void k_validate(const int32_t* __restrict__ src,
                                                          const int32_t* __restrict__ dst,
                                                          const int64_t* __restrict__ t, int64_t m,
@@ -66,16 +80,18 @@ __global__ __launch_bounds__(kSortBlock) void k_validate(const int32_t* __restri
     mn = key < mn ? key : mn;
     mx = key > mx ? key : mx;
   };
-  __shared__ uint32_t s_h[256];
-  const int64_t ntiles = (m + kRecTile - 1) / kRecTile;
+  __shared__ uint32_t s_h[kMaxBins];
+  constexpr int kTile = kSortBlock * ITEMS;
+  const int64_t ntiles = (m + kTile - 1) / kTile;
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    s_h[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t start = tile * kRecTile;
-    int32_t sv[kRecItems], dv[kRecItems];
-    int64_t tv[kRecItems];
 #pragma unroll
-    for (int r = 0; r < kRecItems; ++r) {  // the tile's loads issued together
+    for (int q = 0; q < kMaxBins / kSortBlock; ++q) s_h[q * kSortBlock + threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t start = tile * kTile;
+    int32_t sv[ITEMS], dv[ITEMS];
+    int64_t tv[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {  // the tile's loads issued together
       const int64_t i = start + (int64_t)r * kSortBlock + threadIdx.x;
       const bool in = i < m;
       sv[r] = in ? src[i] : 0;
@@ -83,14 +99,16 @@ __global__ __launch_bounds__(kSortBlock) void k_validate(const int32_t* __restri
       tv[r] = in ? t[i] : 0;
     }
 #pragma unroll
-    for (int r = 0; r < kRecItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
       if (start + (int64_t)r * kSortBlock + threadIdx.x < m) {
         check(sv[r], dv[r], tv[r]);
-        atomicAdd(&s_h[(uint32_t)(uint64_t)tv[r] & 255u], 1u);
+        atomicAdd(&s_h[(uint32_t)(uint64_t)tv[r] & (kMaxBins - 1)], 1u);
       }
     }
     __syncthreads();
-    hist[tile * 256 + threadIdx.x] = s_h[threadIdx.x];
+#pragma unroll
+    for (int q = 0; q < kMaxBins / kSortBlock; ++q)
+      hist[tile * kMaxBins + q * kSortBlock + threadIdx.x] = s_h[q * kSortBlock + threadIdx.x];
     __syncthreads();  // the next tile clears s_h
   }
 #pragma unroll
@@ -102,8 +120,8 @@ __global__ __launch_bounds__(kSortBlock) void k_validate(const int32_t* __restri
     bad |= __shfl_xor(bad, off, kWave);
   }
   // one pair of atomics per block (not per wavefront): they all hit two words
-  __shared__ uint64_t s_mn[4], s_mx[4];
-  __shared__ uint32_t s_bad[4];
+  __shared__ uint64_t s_mn[kSortWaves], s_mx[kSortWaves];
+  __shared__ uint32_t s_bad[kSortWaves];
   const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
     s_mn[wave] = mn;
@@ -125,29 +143,38 @@ __global__ __launch_bounds__(kSortBlock) void k_validate(const int32_t* __restri
 
 // ------------------------------------------------------------ sort plan ---
 // Every sort of the build moves whole 16-byte edge records.  The time sort
-// sorts the records by t - t_min, which needs up to 63 bits: up to four
-// passes over the low 32 bits, then (only when the range is wider than 32
-// bits) up to four over the high 32 bits.  How many of those eight launched
-// passes do work, their digit widths and their ping-pong buffers are decided
-// on the device from the validated time range (k_plan), so the host
-// enqueues the same launches whatever the data and never waits for the
-// device: the build is one stream-ordered sequence that a HIP graph can
-// capture.  A pass with no work leaves at once.
-constexpr int kTimePasses = 8;  // launched passes of the time sort (4 low + 4 high)
+// sorts the records by t - t_min, which needs up to 63 bits: its low 32 bits
+// are a word of the record, and the bits above them sit in the unused top
+// bits of a vertex word where they fit there (PACKED: millisecond times of a
+// few years, with vertex ids of up to 26 bits), so that the digits run over
+// all of the value and no later step reads the input again.  A range too wide
+// for that takes passes over the low word, then over the high word, re-keyed
+// from the input by edge id (WIDE).  How many of the launched passes do work,
+// their digit widths and their ping-pong buffers are decided on the device
+// from the validated time range (k_plan), so the host enqueues the same
+// launches whatever the data and never waits for the device: the build is one
+// stream-ordered sequence that a HIP graph can capture.  A pass with no work
+// leaves at once.
+constexpr int kTimePasses = 6;  // 63 bits in digits of kMaxDigit, or two words of 32
 
 struct BuildPlan {
   int64_t tmin, tmax;  // time range (0, 0 for an empty or rejected input)
   uint32_t bad;        // the validation set TC_F_RANGE: nothing after it runs
-  int32_t wide;        // the range needs more than 32 bits (high-word passes)
-  int32_t npass;       // passes of the time sort that do work
-  int32_t active[kTimePasses], order[kTimePasses], shift[kTimePasses], dbits[kTimePasses];
+  int32_t wide;        // high-word passes, times read back from the input
+  int32_t npass;       // passes of the time sort that do work (the first npass ones)
+  int32_t high;        // first high-word pass of a wide range (else kTimePasses)
+  int32_t shift[kTimePasses], dbits[kTimePasses];
 };
 
 __device__ __forceinline__ int bitlen_dev(uint64_t x) { return x ? 64 - __clzll(x) : 0; }
 
-// ceil(bits / 8) passes with digit widths as equal as possible (narrow ones
-// first): fewer distinct digits per tile means longer runs in the scatter's
-// output, and fewer partly written cache lines
+__host__ __device__ constexpr int digit_passes(int bits) {
+  return (bits + kMaxDigit - 1) / kMaxDigit;
+}
+
+// digit widths as equal as possible (narrow ones first): fewer distinct
+// digits per tile means longer runs in the scatter's output, and fewer partly
+// written cache lines
 __host__ __device__ inline void digit_plan(int bits, int npass, int i, int* shift, int* dbits) {
   int sh = 0;
   for (int q = 0; q < i; ++q) sh += (bits - sh) / (npass - q);
@@ -155,54 +182,61 @@ __host__ __device__ inline void digit_plan(int bits, int npass, int i, int* shif
   *dbits = (bits - sh) / (npass - i);
 }
 
+// row length of a pass's histogram matrix
+__host__ __device__ constexpr int hist_bins(int dbits) {
+  return (1 << dbits) < kMinBins ? kMinBins : 1 << dbits;
+}
+
 __global__ void k_plan(const uint32_t* __restrict__ status, const uint64_t* __restrict__ tminmax,
-                       int64_t m, BuildPlan* __restrict__ P) {
+                       int64_t m, int vbits, BuildPlan* __restrict__ P,
+                       int64_t* __restrict__ t_range) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   BuildPlan B;
   B.bad = *status != 0 ? 1u : 0u;
   B.tmin = B.tmax = 0;
   B.wide = 0;
   B.npass = 0;
-  for (int p = 0; p < kTimePasses; ++p) B.active[p] = B.order[p] = B.shift[p] = B.dbits[p] = 0;
+  B.high = kTimePasses;
+  for (int p = 0; p < kTimePasses; ++p) B.shift[p] = B.dbits[p] = 0;
   if (!B.bad && m > 0) {
     B.tmin = (int64_t)(tminmax[0] ^ (1ull << 63));
     B.tmax = (int64_t)(tminmax[1] ^ (1ull << 63));
     const int tbits = bitlen_dev((uint64_t)(B.tmax - B.tmin));
-    const int lo = tbits < 32 ? tbits : 32, hi = tbits - lo;
-    const int nlo = (lo + 7) / 8, nhi = (hi + 7) / 8;
-    for (int i = 0; i < nlo; ++i) {
-      B.active[i] = 1;
-      B.order[i] = i;
-      digit_plan(lo, nlo, i, &B.shift[i], &B.dbits[i]);
-    }
-    for (int i = 0; i < nhi; ++i) {
-      B.active[4 + i] = 1;
-      B.order[4 + i] = nlo + i;
-      digit_plan(hi, nhi, i, &B.shift[4 + i], &B.dbits[4 + i]);
-    }
+    B.wide = tbits > 64 - vbits ? 1 : 0;
+    const int lo = B.wide ? 32 : tbits, hi = tbits - lo;
+    const int nlo = digit_passes(lo), nhi = digit_passes(hi);
+    for (int i = 0; i < nlo; ++i) digit_plan(lo, nlo, i, &B.shift[i], &B.dbits[i]);
+    for (int i = 0; i < nhi; ++i) digit_plan(hi, nhi, i, &B.shift[nlo + i], &B.dbits[nlo + i]);
     B.npass = nlo + nhi;
-    B.wide = hi > 0 ? 1 : 0;
+    if (B.wide) B.high = nlo;
   }
   *P = B;
+  t_range[0] = B.tmin;  // for tc_graph
+  t_range[1] = B.tmax;
 }
 
 // The digit counts of the time sort's first pass from the validation's
-// low-byte counts: its digit is the low w <= 8 bits of t - t_min (shift 0),
-// so digit d counts the bytes b with (b - t_min) mod 2^w = d.  In place, one
-// tile row at a time.
-__global__ __launch_bounds__(256) void k_fold_hist(uint32_t* __restrict__ hist, int64_t ntiles,
-                                                   const BuildPlan* __restrict__ plan) {
-  if (plan->bad || !plan->active[0]) return;
-  __shared__ uint32_t s_r[256];
+// counts of the low bits: its digit is the low w <= kMaxDigit bits of t - t_min
+// (shift 0), so digit d counts the low bits b with (b - t_min) mod 2^w = d.
+__global__ __launch_bounds__(kSortBlock) void k_fold_hist(const uint32_t* __restrict__ low,
+                                                          uint32_t* __restrict__ hist,
+                                                          int64_t ntiles,
+                                                          const BuildPlan* __restrict__ plan) {
+  if (plan->bad || plan->npass == 0) return;
+  __shared__ uint32_t s_r[kMaxBins];
   const uint32_t W = 1u << plan->dbits[0], tm = (uint32_t)(uint64_t)plan->tmin;
-  const uint32_t d = threadIdx.x;
+  const int bins = hist_bins(plan->dbits[0]);
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    s_r[d] = hist[tile * 256 + d];
+#pragma unroll
+    for (int q = 0; q < kMaxBins / kSortBlock; ++q)
+      s_r[q * kSortBlock + threadIdx.x] = low[tile * kMaxBins + q * kSortBlock + threadIdx.x];
     __syncthreads();
-    uint32_t v = 0;
-    if (d < W)
-      for (uint32_t b = (d + tm) & (W - 1); b < 256; b += W) v += s_r[b];
-    hist[tile * 256 + d] = v;
+    for (uint32_t d = threadIdx.x; d < (uint32_t)bins; d += kSortBlock) {
+      uint32_t v = 0;
+      if (d < W)
+        for (uint32_t b = (d + tm) & (W - 1); b < (uint32_t)kMaxBins; b += W) v += s_r[b];
+      hist[tile * bins + d] = v;
+    }
     __syncthreads();  // the next row overwrites s_r
   }
 }
@@ -223,16 +257,21 @@ __device__ __forceinline__ uint4 rec_xform(const uint4& r, int xf) {
 
 // The input edge columns (read by the first pass of the time sort, which
 // builds each record (t - t_min, eid, src, dst) as it loads it, and by the
-// first high-word pass, which re-keys each record with the high word of
-// t[eid] - t_min).
+// first high-word pass of a wide range, which re-keys each record with the
+// high word of t[eid] - t_min).
 struct EdgeCols {
   const int32_t* src;
   const int32_t* dst;
   const int64_t* t;
 };
 
-// Where a pass reads its records from.
-enum { SRC_BUF = 0, SRC_COLS = 1, SRC_HIGH = 2, SRC_INCOLS = 3 };
+// What a pass is and where it reads its records from (a template parameter:
+// the choice costs the scatter registers when it is made at run time):
+//   RP_COLS    first pass of the time sort, from the edge columns
+//   RP_TIME    a later pass of the time sort, from the buffer before it
+//   RP_VERTEX  a pass of a vertex sort, from a buffer
+//   RP_INCOLS  first pass of the pair sort, from the in-list columns
+enum { RP_COLS = 0, RP_TIME = 1, RP_VERTEX = 2, RP_INCOLS = 3 };
 
 // The in-list columns as the pair sort's input: the 16-byte in-CSR records
 // {src, eid, t} and the key column dst give the record (src, eid, dst,
@@ -241,8 +280,21 @@ enum { SRC_BUF = 0, SRC_COLS = 1, SRC_HIGH = 2, SRC_INCOLS = 3 };
 struct InCols {
   const uint4* rec;
   const int32_t* key;
-  const BuildPlan* plan;  // t_min
+  const int32_t* src;  // the new key, for the histogram
 };
+
+// The bits of t - t_min above its low 32 travel in the top bits of one vertex
+// word (zero when the range needs none or is wide): the word that holds dst
+// in the time sort, and whichever word that becomes after it.
+__host__ __device__ __forceinline__ uint32_t vertex_mask(int vbits) { return (1u << vbits) - 1u; }
+
+// The time of a record (key, eid, other, low word of t - t_min)
+__device__ __forceinline__ int64_t rec_time(const BuildPlan& P, const int64_t* __restrict__ t_in,
+                                            const uint4& r, int vbits) {
+  if (P.wide) return t_in[r.y];
+  const uint32_t hi = (r.x >> vbits) | (r.z >> vbits);
+  return P.tmin + (int64_t)(((uint64_t)hi << 32) | r.w);
+}
 
 // The graph columns that the last pass of a vertex sort writes in place of
 // its sorted records: for output position i with record (key, eid, other,
@@ -259,277 +311,346 @@ struct EmitCols {
   int64_t* skip;   // or null
 };
 
-// One launched radix pass.  With `plan` null the host planned it (the vertex
-// sorts: bit counts follow from n); otherwise it is pass `pass` of the time
-// sort and everything below `plan` is resolved on the device.
+// One launched radix pass.  A vertex sort's passes are planned by the host
+// (bit counts follow from n); with time >= 0 it is that pass of the time
+// sort and everything below `out` is resolved on the device.
 struct RecPass {
   const BuildPlan* plan;
-  int pass;
+  int time;         // pass of the time sort, or -1
+  int vbits;
   const uint4* in;  // host-planned input
   uint4* out;       // host-planned output
   uint4* buf[2];    // time sort: the ping-pong buffers (the sort ends in buf[0])
   int shift, dbits;
   int xfin;         // re-keying of the input as it is loaded (host-planned passes)
-  int xf1;          // re-keying of the output (last pass of a sort)
-  uint4* out2;      // second, re-keyed copy (last pass), or null
-  int xf2;
+  int xf1;          // re-keying of the time sort's last output
   EdgeCols ec;
   EmitCols E;       // k_radix_scatter<..., true>: the columns out of the last pass
   InCols ic;        // host-planned input from the in-list columns (ic.rec non-null)
 };
 
 struct PassCfg {
-  bool active;
-  int shift, dbits, src, xfin, xf1, xf2;
+  bool active, wide, high;  // high: the pass that re-keys a wide range's records
+  int shift, dbits, xfin, xf1, vbits;
   int64_t tmin;
   const uint4* in;
   uint4* out;
-  uint4* out2;
-  InCols ic;
 };
 
+template <int KIND>
 __device__ __forceinline__ PassCfg resolve(const RecPass& R) {
   PassCfg c;
-  c.tmin = 0;
-  if (!R.plan) {
-    c.active = true;
+  const BuildPlan& P = *R.plan;
+  c.vbits = R.vbits;
+  c.tmin = P.tmin;
+  c.wide = P.wide != 0;
+  c.high = false;
+  if (KIND == RP_VERTEX || KIND == RP_INCOLS) {
+    // a rejected input leaves the sorts' records undefined: nothing runs
+    c.active = P.bad == 0;
     c.shift = R.shift;
     c.dbits = R.dbits;
-    c.src = R.ic.rec ? SRC_INCOLS : SRC_BUF;
-    c.ic = R.ic;
-    if (R.ic.rec) c.tmin = R.ic.plan->tmin;
     c.xfin = R.xfin;
     c.in = R.in;
     c.out = R.out;
-    c.xf1 = R.xf1;
-    c.out2 = R.out2;
-    c.xf2 = R.xf2;
+    c.xf1 = RX_NONE;
     return c;
   }
-  const BuildPlan& P = *R.plan;
-  const int p = R.pass;
+  const int p = R.time, n = P.npass;
   c.xfin = RX_NONE;
-  c.ic = InCols{nullptr, nullptr, nullptr};
-  c.active = P.active[p] != 0 && P.bad == 0;
+  c.active = p < n && P.bad == 0;
   c.shift = P.shift[p];
   c.dbits = P.dbits[p];
-  c.tmin = P.tmin;
-  // active pass i of n writes buf[(n - 1 - i) & 1], so the last one writes
-  // buf[0]; pass 0 reads the edge columns, the others the previous output
-  const int i = P.order[p], n = P.npass;
-  c.out = R.buf[(n - 1 - i) & 1];
-  c.in = R.buf[(n - i) & 1];
-  c.src = i == 0 ? SRC_COLS : (p == 4 ? SRC_HIGH : SRC_BUF);
-  const bool last = i == n - 1;
-  c.xf1 = last ? R.xf1 : RX_NONE;
-  c.out2 = last ? R.out2 : nullptr;
-  c.xf2 = last ? R.xf2 : RX_NONE;
+  // pass p of n writes buf[(n - 1 - p) & 1], so the last one writes buf[0];
+  // pass 0 reads the edge columns, the others the previous output
+  c.out = R.buf[(n - 1 - p) & 1];
+  c.in = R.buf[(n - p) & 1];
+  c.high = p == P.high;
+  c.xf1 = p == n - 1 ? R.xf1 : RX_NONE;
   return c;
 }
 
-__device__ __forceinline__ uint4 load_rec(const PassCfg& c, const EdgeCols& ec, int64_t g) {
-  if (c.src == SRC_COLS)
-    return make_uint4((uint32_t)(uint64_t)(ec.t[g] - c.tmin), (uint32_t)g, (uint32_t)ec.src[g],
-                      (uint32_t)ec.dst[g]);
-  if (c.src == SRC_INCOLS) {
-    const uint4 q = c.ic.rec[g];
-    const int64_t te = (int64_t)(((uint64_t)q.w << 32) | q.z);
-    return make_uint4(q.x, q.y, (uint32_t)c.ic.key[g], (uint32_t)(uint64_t)(te - c.tmin));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 load_once(const uint4* p) {
+  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+template <int KIND>
+__device__ __forceinline__ uint4 load_rec(const RecPass& R, const PassCfg& c, int64_t g) {
+  if (KIND == RP_COLS) {
+    const uint64_t dt = (uint64_t)(R.ec.t[g] - c.tmin);
+    // a wide range's high word has no room here
+    const uint32_t hi = c.wide ? 0u : (uint32_t)(dt >> 32) << c.vbits;
+    return make_uint4((uint32_t)dt, (uint32_t)g, (uint32_t)R.ec.src[g],
+                      (uint32_t)R.ec.dst[g] | hi);
   }
-  uint4 r = c.in[g];
-  if (c.src == SRC_HIGH) r.x = (uint32_t)((uint64_t)(ec.t[r.y] - c.tmin) >> 32);
+  if (KIND == RP_INCOLS) {
+    const uint4 q = load_once(R.ic.rec + g);
+    const uint64_t dt = (((uint64_t)q.w << 32) | q.z) - (uint64_t)c.tmin;
+    const uint32_t hi = c.wide ? 0u : (uint32_t)(dt >> 32) << c.vbits;
+    return make_uint4(q.x, q.y, (uint32_t)R.ic.key[g] | hi, (uint32_t)dt);
+  }
+  uint4 r = load_once(c.in + g);
+  if (KIND == RP_TIME) {
+    if (c.high) r.x = (uint32_t)((uint64_t)(R.ec.t[r.y] - c.tmin) >> 32);
+    return r;
+  }
   return rec_xform(r, c.xfin);
+}
+
+// the digit of a record: of its key word, or in the time sort of the whole
+// t - t_min (low word, then the bits above dst)
+template <int KIND>
+__device__ __forceinline__ uint32_t digit_of(const PassCfg& c, uint32_t mask, uint32_t x,
+                                             uint32_t w) {
+  if (KIND == RP_VERTEX || KIND == RP_INCOLS) return (x >> c.shift) & mask;
+  return (uint32_t)((((uint64_t)(w >> c.vbits) << 32) | x) >> c.shift) & mask;
 }
 
 // With no active time pass (every time equal): the records built from the
 // edge columns, re-keyed like the last pass of the time sort would leave them.
 __global__ __launch_bounds__(256) void k_rec_init(EdgeCols ec, int64_t m,
                                                   const BuildPlan* __restrict__ plan,
-                                                  uint4* __restrict__ out, int xf1,
-                                                  uint4* __restrict__ out2, int xf2) {
+                                                  uint4* __restrict__ out, int xf1) {
   if (plan->npass != 0 || plan->bad) return;
   // grid-stride: the launch is small, since it is idle for all but inputs
   // whose times are all equal
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const uint4 r = make_uint4((uint32_t)(uint64_t)(ec.t[i] - plan->tmin), (uint32_t)i,
-                               (uint32_t)ec.src[i], (uint32_t)ec.dst[i]);
+    const uint4 r = make_uint4(0u, (uint32_t)i, (uint32_t)ec.src[i], (uint32_t)ec.dst[i]);
     out[i] = rec_xform(r, xf1);
-    if (out2) out2[i] = rec_xform(r, xf2);
   }
 }
 
 // the re-keying of a vertex sort with no pass (n = 1): a[i] from in[i]
 // (in == a allowed: every element is read and written by the same thread)
 __global__ __launch_bounds__(256) void k_rec_xform(const uint4* in, int xfin, uint4* a, int64_t m,
-                                                   int xf1, uint4* __restrict__ out2, int xf2) {
+                                                   uint4* __restrict__ out2, int xf2) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < m) {
     const uint4 r = rec_xform(in[i], xfin);
-    a[i] = rec_xform(r, xf1);
+    a[i] = r;
     if (out2) out2[i] = rec_xform(r, xf2);
   }
 }
 
-template <int ITEMS, int BINS>
+template <int ITEMS, int KIND>
 __global__ __launch_bounds__(kSortBlock) void k_radix_hist(RecPass R, int64_t m,
                                                            uint32_t* __restrict__ hist) {
-  constexpr int kDig = BINS / kSortBlock;  // digits per thread
-  __shared__ uint32_t s_h[BINS];
-  const PassCfg c = resolve(R);
+  __shared__ uint32_t s_h[kMaxBins];
+  const PassCfg c = resolve<KIND>(R);
   if (!c.active) return;
   const uint32_t mask = (1u << c.dbits) - 1u;
+  const int bins = hist_bins(c.dbits);
+  constexpr int kTile = kSortBlock * ITEMS;
   // one tile per block, or several when the grid is smaller than the tile
   // count (the passes that are usually idle)
-  const int64_t ntiles = (m + kSortBlock * ITEMS - 1) / (kSortBlock * ITEMS);
+  const int64_t ntiles = (m + kTile - 1) / kTile;
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-#pragma unroll
-    for (int q = 0; q < kDig; ++q) s_h[q * kSortBlock + threadIdx.x] = 0;
+    for (int d = threadIdx.x; d < bins; d += kSortBlock) s_h[d] = 0;
     __syncthreads();
-    const int64_t start = tile * (kSortBlock * ITEMS);
+    const int64_t start = tile * kTile;
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
-      int64_t i = start + (int64_t)r * kSortBlock + threadIdx.x;
+      const int64_t i = start + (int64_t)r * kSortBlock + threadIdx.x;
       if (i < m) {
-        const uint32_t key = c.src == SRC_COLS ? (uint32_t)(uint64_t)(R.ec.t[i] - c.tmin)
-                                               : load_rec(c, R.ec, i).x;
-        atomicAdd(&s_h[(key >> c.shift) & mask], 1u);
+        uint4 k;
+        if (KIND == RP_INCOLS)
+          k.x = (uint32_t)R.ic.src[i], k.w = 0;  // 4 bytes of it, not 16
+        else
+          k = load_rec<KIND>(R, c, i);
+        atomicAdd(&s_h[digit_of<KIND>(c, mask, k.x, k.w)], 1u);
       }
     }
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kDig; ++q)
-      hist[tile * BINS + q * kSortBlock + threadIdx.x] = s_h[q * kSortBlock + threadIdx.x];
+    for (int d = threadIdx.x; d < bins; d += kSortBlock) hist[tile * bins + d] = s_h[d];
     __syncthreads();  // the next tile clears s_h
   }
 }
 
-// Column scan of the tile-major histogram: hist[t][d] becomes the position
-// of tile t's first key of digit d in the pass output, i.e. the keys of all
-// smaller digits plus the keys of digit d in tiles before t.  Three kernels:
-// per-chunk column sums, an exclusive scan of each digit's chunk sums (which
-// also leaves the digit totals in row `nchunks`), and an in-place walk of
-// every chunk that adds the digit base.  Every access reads or writes whole
-// rows (BINS words) except the per-digit chunk scan, which touches
-// nchunks*BINS words.  `gate` (time sort passes) skips a pass the plan
-// leaves idle.
-struct PassGate {
-  const BuildPlan* plan;
-  int pass;
-};
-__device__ __forceinline__ bool idle(const PassGate& G) {
-  return G.plan && (G.plan->bad || !G.plan->active[G.pass]);
+// The histograms of the in-CSR and the out-CSR sorts' first passes from one
+// read of the time-ordered records (src, eid, dst, t) that both start from.
+template <int ITEMS>
+__global__ __launch_bounds__(kSortBlock) void k_radix_hist2(const uint4* __restrict__ in,
+                                                            const BuildPlan* __restrict__ plan,
+                                                            int dbits, int64_t m,
+                                                            uint32_t* __restrict__ by_dst,
+                                                            uint32_t* __restrict__ by_src) {
+  if (plan->bad) return;
+  __shared__ uint32_t s_h[2][kMaxBins];
+  const uint32_t mask = (1u << dbits) - 1u;
+  const int bins = hist_bins(dbits);
+  for (int d = threadIdx.x; d < bins; d += kSortBlock) s_h[0][d] = s_h[1][d] = 0;
+  __syncthreads();
+  const int64_t start = (int64_t)blockIdx.x * (kSortBlock * ITEMS);
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int64_t i = start + (int64_t)r * kSortBlock + threadIdx.x;
+    if (i < m) {
+      const uint4 k = load_once(in + i);
+      atomicAdd(&s_h[0][k.z & mask], 1u);
+      atomicAdd(&s_h[1][k.x & mask], 1u);
+    }
+  }
+  __syncthreads();
+  for (int d = threadIdx.x; d < bins; d += kSortBlock) {
+    by_dst[(int64_t)blockIdx.x * bins + d] = s_h[0][d];
+    by_src[(int64_t)blockIdx.x * bins + d] = s_h[1][d];
+  }
 }
 
-template <int BINS>
+// Column scan of the tile-major histogram: hist[t][d] becomes the number of
+// keys of digit d in the tiles before t, and tot[d] the digit's total; the
+// scatter adds the keys of smaller digits.  Up to kOneScanTiles tiles it is
+// one kernel (32 digits per block, the tiles spread over its threads): at that
+// size a launch costs more than its work.  Above, three kernels: per-chunk
+// column sums, an exclusive scan of each digit's chunk sums (which also
+// leaves the totals), and an in-place walk of every chunk.  Every access
+// reads or writes whole row pieces.  The row length follows the pass's digit;
+// a pass the plan leaves idle returns at once.
+constexpr int kOneScanTiles = 512;
+
+struct PassBins {
+  const BuildPlan* plan;
+  int time;  // pass of the time sort, or -1
+  int bins;  // row length of a vertex sort's pass
+};
+// row length of the pass, 0 if it is idle
+__device__ __forceinline__ int pass_bins(const PassBins& G) {
+  if (G.plan->bad) return 0;
+  if (G.time < 0) return G.bins;
+  return G.time < G.plan->npass ? hist_bins(G.plan->dbits[G.time]) : 0;
+}
+
+__global__ __launch_bounds__(1024) void k_col_one(uint32_t* __restrict__ hist, int ntiles,
+                                                  uint32_t* __restrict__ tot, PassBins G) {
+  const int bins = pass_bins(G);
+  constexpr int kDig = 32, kParts = 1024 / kDig;
+  constexpr int kRows = kOneScanTiles / kParts;
+  if ((int)blockIdx.x * kDig >= bins) return;
+  __shared__ uint32_t s_sum[kParts][kDig];
+  const int dl = threadIdx.x % kDig, part = threadIdx.x / kDig;
+  const int d = blockIdx.x * kDig + dl;
+  const int per = (ntiles + kParts - 1) / kParts;  // at most kRows
+  const int t0 = part * per;
+  uint32_t v[kRows];
+  uint32_t s = 0;
+#pragma unroll
+  for (int j = 0; j < kRows; ++j) {
+    v[j] = j < per && t0 + j < ntiles ? hist[(int64_t)(t0 + j) * bins + d] : 0u;
+    s += v[j];
+  }
+  s_sum[part][dl] = s;
+  __syncthreads();
+  uint32_t run = 0, all = 0;
+  for (int p = 0; p < kParts; ++p) {
+    const uint32_t x = s_sum[p][dl];
+    run += p < part ? x : 0u;
+    all += x;
+  }
+  if (part == 0) tot[d] = all;
+#pragma unroll
+  for (int j = 0; j < kRows; ++j) {
+    if (j < per && t0 + j < ntiles) hist[(int64_t)(t0 + j) * bins + d] = run;
+    run += v[j];
+  }
+}
+
 __global__ __launch_bounds__(256) void k_col_sum(const uint32_t* __restrict__ hist,
                                                  int64_t ntiles, uint32_t* __restrict__ csum,
-                                                 PassGate gate) {
-  if (idle(gate)) return;
+                                                 PassBins G) {
+  const int bins = pass_bins(G);
   const int64_t t0 = (int64_t)blockIdx.x * kColChunk;
-#pragma unroll
-  for (int q = 0; q < BINS / 256; ++q) {
-    const int d = q * 256 + threadIdx.x;
+  for (int d = threadIdx.x; d < bins; d += 256) {
     uint32_t s = 0;
 #pragma unroll
     for (int j = 0; j < kColChunk; ++j) {
       // clamped index: every load is issued unconditionally
       const int64_t t = t0 + j < ntiles ? t0 + j : ntiles - 1;
-      const uint32_t v = hist[t * BINS + d];
+      const uint32_t v = hist[t * bins + d];
       s += (t0 + j < ntiles) ? v : 0u;
     }
-    csum[(int64_t)blockIdx.x * BINS + d] = s;
+    csum[(int64_t)blockIdx.x * bins + d] = s;
   }
 }
 
 // one block per digit (blockIdx.x), chunks spread over the block's threads
-template <int BINS>
 __global__ __launch_bounds__(256) void k_col_scan(uint32_t* __restrict__ csum, int64_t nchunks,
-                                                  PassGate gate) {
-  if (idle(gate)) return;
+                                                  uint32_t* __restrict__ tot, PassBins G) {
+  const int bins = pass_bins(G);
+  if ((int)blockIdx.x >= bins) return;
   __shared__ uint32_t s_w[256 / kWave];
   const int d = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t carry = 0;
   for (int64_t base = 0; base < nchunks; base += 256) {
     const int64_t c = base + threadIdx.x;
-    const uint32_t v = c < nchunks ? csum[c * BINS + d] : 0u;
+    const uint32_t v = c < nchunks ? csum[c * bins + d] : 0u;
     const uint32_t inc = wave_inclusive_scan(v);
     if (lane == 63) s_w[wave] = inc;
     __syncthreads();
-    uint32_t off = 0, tot = 0;
+    uint32_t off = 0, all = 0;
 #pragma unroll
     for (int w = 0; w < 256 / kWave; ++w) {
       off += w < wave ? s_w[w] : 0u;
-      tot += s_w[w];
+      all += s_w[w];
     }
-    if (c < nchunks) csum[c * BINS + d] = carry + off + inc - v;
-    carry += tot;
+    if (c < nchunks) csum[c * bins + d] = carry + off + inc - v;
+    carry += all;
     __syncthreads();
   }
-  if (threadIdx.x == 0) csum[nchunks * BINS + d] = carry;
+  if (threadIdx.x == 0) tot[d] = carry;
 }
 
-// one block per chunk; thread tid walks the chunk's tiles for digits
-// tid, tid + 256, ...
-template <int BINS>
+// one block per chunk: its threads walk the chunk's tiles
 __global__ __launch_bounds__(256) void k_col_apply(uint32_t* __restrict__ hist, int64_t ntiles,
                                                    const uint32_t* __restrict__ csum,
-                                                   int64_t nchunks, PassGate gate) {
-  if (idle(gate)) return;
-  constexpr int kDig = BINS / 256;
-  __shared__ uint32_t s_w[kDig][256 / kWave];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                                   PassBins G) {
+  const int bins = pass_bins(G);
   const int64_t t0 = (int64_t)blockIdx.x * kColChunk;
-  uint32_t carry = 0;  // totals of the digits below this group of 256
-#pragma unroll
-  for (int q = 0; q < kDig; ++q) {
-    const int d = q * 256 + tid;
-    // digit base: exclusive scan of the digit totals over d
-    const uint32_t tot = csum[nchunks * BINS + d];
-    const uint32_t inc = wave_inclusive_scan(tot);
-    if (lane == 63) s_w[q][wave] = inc;
-    __syncthreads();
-    uint32_t run = carry + inc - tot, group = 0;
-#pragma unroll
-    for (int w = 0; w < 256 / kWave; ++w) {
-      run += w < wave ? s_w[q][w] : 0u;
-      group += s_w[q][w];
-    }
-    carry += group;
-    run += csum[(int64_t)blockIdx.x * BINS + d];
+  for (int d = threadIdx.x; d < bins; d += 256) {
+    uint32_t run = csum[(int64_t)blockIdx.x * bins + d];
     uint32_t v[kColChunk];
 #pragma unroll
     for (int j = 0; j < kColChunk; ++j) {
       const int64_t t = t0 + j < ntiles ? t0 + j : ntiles - 1;
-      v[j] = hist[t * BINS + d];
+      v[j] = hist[t * bins + d];
     }
 #pragma unroll
     for (int j = 0; j < kColChunk; ++j) {
-      if (t0 + j < ntiles) hist[(t0 + j) * BINS + d] = run;
+      if (t0 + j < ntiles) hist[(t0 + j) * bins + d] = run;
       run += v[j];
     }
   }
 }
 
-size_t col_scan_scratch_elems(int64_t ntiles, int bins) {
-  return (size_t)bins * ((ntiles + kColChunk - 1) / kColChunk + 1);
+// the totals row, then the chunk sums
+size_t col_scan_scratch_elems(int64_t ntiles) {
+  return (size_t)kMaxBins * ((ntiles + kColChunk - 1) / kColChunk + 1);
 }
 
-template <int BINS>
-void col_scan(uint32_t* hist, int64_t ntiles, uint32_t* csum, PassGate gate, hipStream_t st) {
+static void col_scan(uint32_t* hist, int64_t ntiles, uint32_t* part, const PassBins& G,
+                     hipStream_t st) {
+  const unsigned bins = G.time < 0 ? (unsigned)G.bins : (unsigned)kMaxBins;
+  if (ntiles <= kOneScanTiles) {
+    hipLaunchKernelGGL(k_col_one, dim3((bins + 31) / 32), dim3(1024), 0, st, hist, (int)ntiles,
+                       part, G);
+    return;
+  }
   const int64_t nchunks = (ntiles + kColChunk - 1) / kColChunk;
-  hipLaunchKernelGGL(k_col_sum<BINS>, dim3((unsigned)nchunks), dim3(256), 0, st,
-                     (const uint32_t*)hist, ntiles, csum, gate);
-  hipLaunchKernelGGL(k_col_scan<BINS>, dim3(BINS), dim3(256), 0, st, csum, nchunks, gate);
-  hipLaunchKernelGGL(k_col_apply<BINS>, dim3((unsigned)nchunks), dim3(256), 0, st, hist, ntiles,
-                     (const uint32_t*)csum, nchunks, gate);
+  uint32_t* csum = part + kMaxBins;
+  hipLaunchKernelGGL(k_col_sum, dim3((unsigned)nchunks), dim3(256), 0, st,
+                     (const uint32_t*)hist, ntiles, csum, G);
+  hipLaunchKernelGGL(k_col_scan, dim3(bins), dim3(256), 0, st, csum, nchunks, part, G);
+  hipLaunchKernelGGL(k_col_apply, dim3((unsigned)nchunks), dim3(256), 0, st, hist, ntiles,
+                     (const uint32_t*)csum, G);
 }
 
 // the columns of one sorted record at output position i (see EmitCols)
-__device__ __forceinline__ void emit_cols(const EmitCols& E, int64_t m, int64_t i,
-                                          const uint4& r) {
-  const BuildPlan& P = *E.plan;
-  const int64_t te = P.wide ? E.t_in[r.y] : P.tmin + (int64_t)r.w;
+__device__ __forceinline__ void emit_cols(const EmitCols& E, int vbits, int64_t m, int64_t i,
+                                          uint4 r) {
+  const int64_t te = rec_time(*E.plan, E.t_in, r, vbits);
+  r.x &= vertex_mask(vbits);
+  r.z &= vertex_mask(vbits);
   E.key[i] = (int32_t)r.x;
   E.other[i] = (int32_t)r.z;
   E.t[i] = te;
@@ -543,264 +664,318 @@ __device__ __forceinline__ void emit_cols(const EmitCols& E, int64_t m, int64_t 
   }
 }
 
-template <int ITEMS, int BINS, bool EMIT = false, bool LOOP = false>
-__global__ __launch_bounds__(kSortBlock) void k_radix_scatter(RecPass R, int64_t m,
-                                                              const uint32_t* __restrict__ hist) {
-  // Each wavefront owns a contiguous quarter of the tile and ranks its keys
+// The scatter moves 32 bytes per record and runs at the rate of a large
+// device copy (3*10^8 records by a 9-bit digit: 2.3 ms, 4.2 TB/s; 2*10^7 by a
+// 10-bit digit 0.17 ms), so the sort's time is its passes and its histogram
+// reads.  Against 8- and 9-bit digits in 1,536-record tiles (12 passes for
+// 2*10^7 edges of 20-bit vertices and 22-bit times, now 8) the build went from
+// 4.65 to 4.03 ms, 5*10^6 edges of millisecond times from 1.45 to 1.11 ms,
+// and 3*10^8 edges from 55.8 to 50 ms.  Records are read past the caches'
+// replacement order (non-temporal: 3% of the 2*10^7-edge build), which leaves
+// the half-written lines of the digit runs in L2 until they are full.
+// Tiles of 6,144 records exchanged half a record at a time needed 128
+// registers and spills (twice the time per pass); 2,048-record tiles give the
+// scatter 5-10% but pay more for four times the histogram rows.
+template <int ITEMS, int KIND, bool EMIT>
+__global__ __launch_bounds__(kSortBlock, ITEMS > 5 ? 4 : 6) void k_radix_scatter(
+    RecPass R, int64_t m,
+    const uint32_t* __restrict__ hist, const uint32_t* __restrict__ tot) {
+  // Each wavefront owns a contiguous eighth of the tile and ranks its keys
   // in order with ballots (no block barrier inside); one block-wide pass then
   // offsets every wavefront's digit counts by those of the wavefronts before
   // it, which keeps the pass stable.
-  static_assert(BINS == 256 || BINS == 512, "8- or 9-bit digits");
   constexpr int kTile = kSortBlock * ITEMS;
-  constexpr int kWaves = kSortBlock / kWave;
   constexpr int kSub = kWave * ITEMS;  // entries per wavefront
-  constexpr int kDig = BINS / kSortBlock;
-  constexpr int kBits = BINS == 512 ? 9 : 8;
+  constexpr int kOwn = 4;              // digits per thread of the block-wide pass
+  static_assert(kMaxBins <= kOwn * kSortBlock, "every digit has a thread");
   static_assert(2 * kTile < 65536, "16-bit tile positions");
-  const PassCfg c = resolve(R);
+  const PassCfg c = resolve<KIND>(R);
   if (!c.active) return;
-  const int shift = c.shift, dbits = c.dbits;
+  const int dbits = c.dbits;
   const uint32_t mask = (1u << dbits) - 1u;
+  const int bins = hist_bins(dbits);
   // s_base[d]: global position of digit d's run minus its start in the tile
   // s_pos[w][d]: wavefront w's running count of digit d, then the position
-  //              in the tile of w's first key of digit d (16 bits suffice)
-  __shared__ uint32_t s_base[BINS];
-  __shared__ uint16_t s_pos[kWaves][BINS];
-  __shared__ uint32_t s_wsum[kDig][kWaves];
-  __shared__ uint4 s_key[kTile];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // One tile per block (the grid is the tile count), or with LOOP several
-  // when the grid is smaller (a multiple of 8 blocks then, for the passes
-  // that are usually idle).  XCD-aware tile order: workgroups are dealt to the XCDs round
-  // robin (block b to XCD b mod 8), and each XCD has its own L2.
-  // Neighbouring tiles write neighbouring pieces of every digit run, so each
-  // XCD takes a contiguous range of tiles: partial cache lines then meet in
-  // one L2 instead of being written back piecewise from several.
-  const uint32_t nb = LOOP ? (uint32_t)((m + kTile - 1) / kTile) : gridDim.x;
+  //              in the tile of w's first key of digit d (16 bits suffice);
+  //              once every thread holds its records' positions, the same
+  //              LDS exchanges the records
+  constexpr int kPosBytes = kSortWaves * kMaxBins * 2, kXBytes = kTile * 16;
+  __shared__ __align__(16) char s_mem[kPosBytes > kXBytes ? kPosBytes : kXBytes];
+  __shared__ uint32_t s_base[kMaxBins];
+  __shared__ uint64_t s_wsum[kSortWaves];
+  uint16_t* const s_pos = reinterpret_cast<uint16_t*>(s_mem);
+  uint4* const s_rec = reinterpret_cast<uint4*>(s_mem);
+  const uint32_t nb = (uint32_t)((m + kTile - 1) / kTile);
+  // One tile per block, or several when the grid is smaller (a multiple of 8
+  // blocks then, for the passes that are usually idle).  XCD-aware tile
+  // order: workgroups are dealt to the XCDs round robin (block b to XCD b mod
+  // 8), and each XCD has its own L2.  Neighbouring tiles write neighbouring
+  // pieces of every digit run, so each XCD takes a contiguous range of tiles:
+  // partial cache lines then meet in one L2 instead of being written back
+  // piecewise from several.
   for (uint32_t vt = blockIdx.x; vt < nb; vt += gridDim.x) {
+    // a thread index the compiler cannot carry over from the last tile: it
+    // would keep every address formed from it in registers across the loop
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = (int)uni(threadIdx.x >> 6);
+    uint16_t* const my_pos = s_pos + wave * bins;
     const uint32_t xcd = vt % kXcds, slot = vt / kXcds;
     const uint32_t q = nb / kXcds, rem = nb % kXcds;
     const uint32_t tile = xcd * q + (xcd < rem ? xcd : rem) + slot;
     const int64_t start = (int64_t)tile * kTile;
     const int len = (int)((m - start) < kTile ? (m - start) : kTile);
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 
-    uint32_t gbase[kDig];  // loaded now, used after the ranking
-#pragma unroll
-    for (int j = 0; j < kDig; ++j) gbase[j] = hist[(int64_t)tile * BINS + j * kSortBlock + tid];
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w)
-#pragma unroll
-      for (int j = 0; j < kDig; ++j) s_pos[w][j * kSortBlock + tid] = 0;
-    __syncthreads();
-
+    // the last tile is filled up with records of the largest digit: they rank
+    // behind all of its own, so only the final writes need to leave them out
     uint4 key[ITEMS];
-    uint32_t rank[ITEMS];  // rank among the wavefront's keys of the same digit
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
       const int idx = wave * kSub + r * kWave + lane;
-      const bool valid = idx < len;
-      key[r] = valid ? load_rec(c, R.ec, start + idx) : uint4{};
-      const uint32_t d = (key[r].x >> shift) & mask;
-      uint64_t vb = __ballot(valid);
-      uint64_t peers = valid ? vb : ~vb;
+      key[r] = idx < len ? load_rec<KIND>(R, c, start + idx) : uint4{~0u, ~0u, ~0u, ~0u};
+    }
+    uint4 gb{0, 0, 0, 0}, tt{0, 0, 0, 0};  // digits kOwn tid ..: prefix over tiles, totals
+    if (kOwn * tid < bins) {
+      gb = *reinterpret_cast<const uint4*>(hist + (int64_t)tile * bins + kOwn * tid);
+      tt = *reinterpret_cast<const uint4*>(tot + kOwn * tid);
+    }
+    for (int i = tid; i < kSortWaves * bins / 8; i += kSortBlock)
+      reinterpret_cast<uint4*>(s_mem)[i] = uint4{0, 0, 0, 0};
+    __syncthreads();
+
+    // lanes whose record r has the digit of this lane's: one ballot per bit,
+    // the records of a thread side by side
+    uint32_t dig[ITEMS], rank[ITEMS];
+    uint64_t peers[ITEMS];
 #pragma unroll
-      for (int b = 0; b < kBits; ++b) {
-        if (b < dbits) {  // uniform: the digit has dbits bits
-          const bool bit = (d >> b) & 1u;
-          const uint64_t bb = __ballot(bit);
-          peers &= bit ? bb : ~bb;
-        }
+    for (int r = 0; r < ITEMS; ++r) {
+      dig[r] = digit_of<KIND>(c, mask, key[r].x, key[r].w);
+      peers[r] = ~0ull;
+    }
+    for (int b = 0; b < dbits; ++b) {  // uniform
+#pragma unroll
+      for (int r = 0; r < ITEMS; ++r) {
+        const bool bit = (dig[r] >> b) & 1u;
+        const uint64_t bb = __ballot(bit);
+        peers[r] &= bit ? bb : ~bb;
       }
-      const uint32_t below = (uint32_t)__popcll(peers & lt_mask);
+    }
+    // rank among the wavefront's records of the same digit
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+          (uint32_t)(peers[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers[r], 0u));
       // read the running count before the leader of each digit group adds to it
-      const uint32_t run = valid ? (uint32_t)s_pos[wave][d] : 0u;
+      const uint32_t run = my_pos[dig[r]];
       rank[r] = run + below;
       __builtin_amdgcn_wave_barrier();
-      if (valid && below == 0) s_pos[wave][d] = (uint16_t)(run + (uint32_t)__popcll(peers));
+      if (below == 0) my_pos[dig[r]] = (uint16_t)(run + (uint32_t)__popcll(peers[r]));
       __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    // thread tid owns digits tid, tid + 256, ...: the tile-local start of each
-    // wavefront's run of that digit, digits in increasing order
+    // thread tid owns digits kOwn tid ..: one scan over the block gives both
+    // the keys of smaller digits (totals, above bit 16) and the digit's start
+    // in the tile (counts, below)
     {
-      uint32_t carry = 0;  // keys of the digit groups below
+      // the counts of four digits as 16-bit halves (a tile's sums fit them)
+      uint2 c2{0, 0};
+      const bool own = kOwn * tid < bins;
+      if (own)
 #pragma unroll
-      for (int j = 0; j < kDig; ++j) {
-        const int d = j * kSortBlock + tid;
-        uint32_t cw[kWaves], tot = 0;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-          cw[w] = s_pos[w][d];
-          tot += cw[w];
+        for (int w = 0; w < kSortWaves; ++w) {
+          const uint2 v = *reinterpret_cast<const uint2*>(s_pos + w * bins + kOwn * tid);
+          c2.x += v.x;
+          c2.y += v.y;
         }
-        const uint32_t inc = wave_inclusive_scan(tot);
-        if (lane == 63) s_wsum[j][wave] = inc;
-        __syncthreads();
-        uint32_t off = carry + inc - tot, group = 0;
+      const uint32_t cnt[kOwn] = {c2.x & 0xFFFFu, c2.x >> 16, c2.y & 0xFFFFu, c2.y >> 16};
+      const uint32_t total[kOwn] = {tt.x, tt.y, tt.z, tt.w};
+      const uint32_t before[kOwn] = {gb.x, gb.y, gb.z, gb.w};
+      uint64_t s = 0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-          off += w < wave ? s_wsum[j][w] : 0u;
-          group += s_wsum[j][w];
+      for (int j = 0; j < kOwn; ++j) s += ((uint64_t)total[j] << 16) + cnt[j];
+      const uint64_t inc = wave_inclusive_scan(s);
+      if (lane == 63) s_wsum[wave] = inc;
+      __syncthreads();
+      uint64_t run = inc - s;
+#pragma unroll
+      for (int w = 0; w < kSortWaves; ++w) run += w < wave ? s_wsum[w] : 0ull;
+      if (own) {
+        uint32_t pos[kOwn];
+#pragma unroll
+        for (int j = 0; j < kOwn; ++j) {
+          const uint32_t off = (uint32_t)run & 0xFFFFu;
+          // modulo 2^32; the sum with the tile position is exact
+          s_base[kOwn * tid + j] = (uint32_t)(run >> 16) + before[j] - off;
+          pos[j] = off;
+          run += ((uint64_t)total[j] << 16) + cnt[j];
         }
-        carry += group;
-        s_base[d] = gbase[j] - off;  // modulo 2^32; the sum below is exact
-        uint32_t p = off;
+        uint2 at{pos[0] | pos[1] << 16, pos[2] | pos[3] << 16};
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-          s_pos[w][d] = (uint16_t)p;
-          p += cw[w];
+        for (int w = 0; w < kSortWaves; ++w) {
+          uint2* const sp = reinterpret_cast<uint2*>(s_pos + w * bins + kOwn * tid);
+          const uint2 v = *sp;
+          *sp = at;
+          at.x += v.x;
+          at.y += v.y;
         }
       }
     }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r)
+      rank[r] += my_pos[dig[r]];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) s_rec[rank[r]] = key[r];
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
-      const int idx = wave * kSub + r * kWave + lane;
-      if (idx < len) {
-        const uint32_t d = (key[r].x >> shift) & mask;
-        s_key[(uint32_t)s_pos[wave][d] + rank[r]] = key[r];
+      const int i = r * kSortBlock + tid;
+      if (i < len) {
+        const uint4 k = s_rec[i];
+        const int64_t gpos = (int64_t)(s_base[digit_of<KIND>(c, mask, k.x, k.w)] + (uint32_t)i);
+        // the time sort's last pass re-keys the records for the next sort; a
+        // vertex sort's last pass writes the graph's columns instead
+        if (EMIT)
+          emit_cols(R.E, c.vbits, m, gpos, k);
+        else
+          c.out[gpos] = rec_xform(k, c.xf1);
       }
     }
-    __syncthreads();
-    const bool cols = EMIT && R.E.plan->bad == 0;
-    for (int i = tid; i < len; i += kSortBlock) {
-      const uint4 k = s_key[i];
-      const uint32_t d = (k.x >> shift) & mask;
-      const int64_t gpos = (int64_t)(s_base[d] + (uint32_t)i);
-      // the last pass of a sort can re-key the records for the next sort, or
-      // write the graph's columns instead of the records
-      if (EMIT) {
-        if (cols) emit_cols(R.E, m, gpos, k);
-      } else {
-        c.out[gpos] = rec_xform(k, c.xf1);
-      }
-      if (c.out2) c.out2[gpos] = rec_xform(k, c.xf2);
-    }
-    if (!LOOP) break;
     __syncthreads();  // the next tile reuses the LDS
   }
 }
 
-// One host-planned pass with BINS-entry digit histograms.
-template <int ITEMS, int BINS>
-void radix_pass(const RecPass& R, bool emit, int64_t m, int64_t ntiles, uint32_t* hist,
-                uint32_t* part, hipStream_t st) {
-  hipLaunchKernelGGL((k_radix_hist<ITEMS, BINS>), dim3((unsigned)ntiles), dim3(kSortBlock), 0,
-                     st, R, m, hist);
-  col_scan<BINS>(hist, ntiles, part, PassGate{nullptr, 0}, st);
+// Histogram and scan scratch of the sorts.
+struct SortScratch {
+  uint32_t* hist;
+  uint32_t* part;
+  size_t part_elems;
+  int vbits;
+};
+
+// One launched pass: histogram (unless its counts are there already), column
+// scan, scatter.  `grid` blocks walk the tiles.
+template <int ITEMS, int KIND>
+void radix_pass(const RecPass& R, bool count, bool emit, int64_t m, unsigned grid,
+                const SortScratch& sc, hipStream_t st) {
+  const int64_t ntiles = (m + kSortBlock * ITEMS - 1) / (kSortBlock * ITEMS);
+  const dim3 g(grid), b(kSortBlock);
+  if constexpr (KIND != RP_COLS)
+    if (count)
+    hipLaunchKernelGGL((k_radix_hist<ITEMS, KIND>), g, b, 0, st, R, m, sc.hist);
+  col_scan(sc.hist, ntiles, sc.part,
+           PassBins{R.plan, R.time, R.time < 0 ? hist_bins(R.dbits) : 0}, st);
   TimedLaunch tl("k_radix_scatter", st);
-  if (emit)
-    hipLaunchKernelGGL((k_radix_scatter<ITEMS, BINS, true>), dim3((unsigned)ntiles),
-                       dim3(kSortBlock), 0, st, R, m, (const uint32_t*)hist);
+  constexpr bool kVertex = KIND == RP_VERTEX || KIND == RP_INCOLS;
+  if (kVertex && emit)
+    hipLaunchKernelGGL((k_radix_scatter<ITEMS, KIND, kVertex>), g, b, 0, st, R, m,
+                       (const uint32_t*)sc.hist, (const uint32_t*)sc.part);
   else
-    hipLaunchKernelGGL((k_radix_scatter<ITEMS, BINS>), dim3((unsigned)ntiles), dim3(kSortBlock),
-                       0, st, R, m, (const uint32_t*)hist);
+    hipLaunchKernelGGL((k_radix_scatter<ITEMS, KIND, false>), g, b, 0, st, R, m,
+                       (const uint32_t*)sc.hist, (const uint32_t*)sc.part);
+}
+
+template <int KIND>
+void radix_pass(const RecPass& R, bool count, bool emit, int64_t m, unsigned grid,
+                const SortScratch& sc, hipStream_t st) {
+  if (large_tiles(m))
+    radix_pass<kItemsLarge, KIND>(R, count, emit, m, grid, sc, st);
+  else
+    radix_pass<kItemsSmall, KIND>(R, count, emit, m, grid, sc, st);
+}
+
+// width of pass p of a vertex sort: wide digits first, a narrow one last, so
+// that the last pass, which writes four or five arrays, writes the longest
+// runs
+static int vertex_digit(int bits, int npass, int p) {
+  int sh, db;
+  digit_plan(bits, npass, npass - 1 - p, &sh, &db);
+  return db;
 }
 
 // Host-planned stable sort of m records by the low `bits` bits of their
-// first word (a vertex id), ping-ponging between k0 and k1; returns 0 if the
-// result is in k0, 1 if in k1, -1 if the scan scratch is too small (nothing
-// enqueued then).  The result is re-keyed by xf1, and if `extra` is given a
-// second copy re-keyed by xf2 goes there.  With `emit` the last pass writes
-// the columns *emit instead of the sorted records (returns 2 then; with no
-// pass at all the caller emits from k0).  With `in0` the first pass reads
-// the records from there, re-keyed by xf_in as it loads them, and in0 is
-// left as it was; with `ic` it reads them from the in-list columns (the
-// caller passes ic only when the sort has a pass).  Digits are at most 8 bits wide,
-// or at most 9 where that saves a pass (9, 17-18 and 25-27 bits: a 26-bit
-// vertex id takes 8 + 9 + 9 instead of 6 + 6 + 7 + 7); a 9-bit pass moves
-// twice the histogram rows, a few percent of the records' bytes.
-template <int ITEMS>
-int radix_sort(uint4* k0, uint4* k1, int64_t m, int bits, uint32_t* hist, uint32_t* part,
-               size_t part_elems, hipStream_t st, int xf1 = RX_NONE, uint4* extra = nullptr,
-               int xf2 = RX_NONE, const EmitCols* emit = nullptr, const uint4* in0 = nullptr,
-               int xf_in = RX_NONE, const InCols* ic = nullptr) {
-  if (m <= 0) return 0;
-  constexpr int kTile = kSortBlock * ITEMS;
-  const int64_t ntiles = (m + kTile - 1) / kTile;
-  const int n8 = (bits + 7) / 8, n9 = (bits + 8) / 9;
-  const bool nine = n9 < n8;
-  const int npass = nine ? n9 : n8;
-  if (part_elems < col_scan_scratch_elems(ntiles, nine ? 512 : 256)) return -1;
-  int cur = 0;
-  if (npass == 0 && (xf1 != RX_NONE || extra || in0))
-    hipLaunchKernelGGL(k_rec_xform, dim3(blocks_for(m, 256)), dim3(256), 0, st,
-                       in0 ? in0 : (const uint4*)k0, in0 ? xf_in : (int)RX_NONE, k0, m, xf1,
-                       extra, xf2);
-  int shift = 0;
+// first word (a vertex id), ping-ponging between k0 and k1; the last pass
+// writes the columns E instead of the sorted records (returns 1).  With no
+// pass (bits = 0) the records stay in k0, a second copy re-keyed by xf2 goes
+// to `extra` if given, and the caller emits from k0 (returns 0).  Returns -1
+// if the scan scratch is too small (nothing enqueued then).  With `in0` the
+// first pass reads the records from there, re-keyed by xf_in as it loads
+// them, and in0 is left as it was; with `ic` it reads them from the in-list
+// columns (the caller passes ic only when the sort has a pass).  With `first`
+// the first pass's histogram matrix is already there.
+static int radix_sort(uint4* k0, uint4* k1, int64_t m, int bits, const SortScratch& sc,
+                      hipStream_t st, uint4* extra, int xf2, const EmitCols& E, const uint4* in0,
+                      int xf_in, const InCols* ic, uint32_t* first) {
+  const int64_t ntiles = sort_tiles(m);
+  if (sc.part_elems < col_scan_scratch_elems(ntiles)) return -1;
+  const int npass = digit_passes(bits);
+  if (npass == 0) {
+    if (extra || in0)
+      hipLaunchKernelGGL(k_rec_xform, dim3(blocks_for(m, 256)), dim3(256), 0, st,
+                         in0 ? in0 : (const uint4*)k0, in0 ? xf_in : (int)RX_NONE, k0, m, extra,
+                         xf2);
+    return 0;
+  }
+  int cur = 0, shift = 0;
   for (int p = 0; p < npass; ++p) {
-    const bool last = p + 1 == npass;
     RecPass R{};
-    R.plan = nullptr;
+    R.plan = E.plan;
+    R.time = -1;
+    R.vbits = sc.vbits;
     R.in = p == 0 && in0 ? in0 : (cur ? k1 : k0);
     R.xfin = p == 0 && in0 ? xf_in : (int)RX_NONE;
     if (p == 0 && ic) R.ic = *ic;
     R.out = cur ? k0 : k1;
-    // with 9-bit digits the narrow one goes last: the last pass writes the
-    // longest runs, and an 8-bit pass takes 256-entry rows
-    int sh, db;
-    digit_plan(bits, npass, nine ? npass - 1 - p : p, &sh, &db);
     R.shift = shift;
-    R.dbits = db;
-    shift += db;
-    R.xf1 = last ? xf1 : (int)RX_NONE;
-    R.out2 = last ? extra : nullptr;
-    R.xf2 = last ? xf2 : (int)RX_NONE;
-    const bool em = last && emit;
-    if (em) R.E = *emit;
-    if (db > 8)
-      radix_pass<ITEMS, 512>(R, em, m, ntiles, hist, part, st);
+    R.dbits = vertex_digit(bits, npass, p);
+    shift += R.dbits;
+    const bool last = p + 1 == npass;
+    if (last) R.E = E;
+    SortScratch use = sc;
+    const bool counted = p == 0 && first;
+    if (counted) use.hist = first;
+    if (R.ic.rec)
+      radix_pass<RP_INCOLS>(R, !counted, last, m, (unsigned)ntiles, use, st);
     else
-      radix_pass<ITEMS, 256>(R, em, m, ntiles, hist, part, st);
+      radix_pass<RP_VERTEX>(R, !counted, last, m, (unsigned)ntiles, use, st);
     cur ^= 1;
   }
-  return npass > 0 && emit ? 2 : cur;
+  return 1;
 }
 
 // The time sort: kTimePasses launched passes planned on the device (see
 // BuildPlan).  It reads the edge columns and leaves the time-ordered records
-// re-keyed by xf1 in buf[0] and, if out2 is given, by xf2 in out2.  Its
-// first pass takes its digit counts from the validation (k_fold_hist).
-template <int ITEMS>
-bool time_sort(const BuildPlan* plan, const EdgeCols& ec, uint4* b0, uint4* b1, int64_t m,
-               uint32_t* hist, uint32_t* part, size_t part_elems, hipStream_t st, int xf1,
-               uint4* out2, int xf2) {
-  constexpr int kTile = kSortBlock * ITEMS;
-  const int64_t ntiles = (m + kTile - 1) / kTile;
-  if (part_elems < col_scan_scratch_elems(ntiles, 256)) return false;
+// re-keyed by xf1 in b0.  Its first pass takes its digit counts from the
+// validation (k_fold_hist).
+static bool time_sort(const BuildPlan* plan, const EdgeCols& ec, uint4* b0, uint4* b1, int64_t m,
+                      const uint32_t* low, const SortScratch& sc, hipStream_t st, int xf1) {
+  const int64_t ntiles = sort_tiles(m);
+  if (sc.part_elems < col_scan_scratch_elems(ntiles)) return false;
   hipLaunchKernelGGL(k_rec_init, dim3(blocks_for(m, 256) < 2048 ? blocks_for(m, 256) : 2048),
-                     dim3(256), 0, st, ec, m, plan, b0,
-                     xf1, out2, xf2);
+                     dim3(256), 0, st, ec, m, plan, b0, xf1);
   for (int p = 0; p < kTimePasses; ++p) {
     RecPass R{};
     R.plan = plan;
-    R.pass = p;
+    R.time = p;
+    R.vbits = sc.vbits;
     R.buf[0] = b0;
     R.buf[1] = b1;
     R.xf1 = xf1;
-    R.out2 = out2;
-    R.xf2 = xf2;
     R.ec = ec;
-    // the high-word passes work only for time ranges wider than 32 bits:
-    // their launches take up to eight tiles per block, so that idle ones
-    // cost a few microseconds
+    // the passes past 33 bits work only for ranges that wide: their launches
+    // take up to eight tiles per block, so that idle ones cost a few
+    // microseconds
     const int64_t hb = ((ntiles + 63) / 64) * 8;
-    const unsigned grid = (unsigned)(p >= 4 && hb < ntiles ? hb : ntiles);
+    const unsigned grid = (unsigned)(p >= 3 && hb < ntiles ? hb : ntiles);
     // pass 0 takes its counts from the validation's (k_fold_hist)
-    if (p == 0)
-      hipLaunchKernelGGL(k_fold_hist, dim3((unsigned)(ntiles < 2048 ? ntiles : 2048)), dim3(256),
-                         0, st, hist, ntiles, plan);
-    else
-      hipLaunchKernelGGL((k_radix_hist<ITEMS, 256>), dim3(grid), dim3(kSortBlock), 0, st, R, m,
-                         hist);
-    col_scan<256>(hist, ntiles, part, PassGate{plan, p}, st);
-    if (p >= 4)
-      hipLaunchKernelGGL((k_radix_scatter<ITEMS, 256, false, true>), dim3(grid), dim3(kSortBlock),
-                         0, st, R, m, (const uint32_t*)hist);
-    else
-      hipLaunchKernelGGL((k_radix_scatter<ITEMS, 256>), dim3(grid), dim3(kSortBlock), 0, st, R,
-                         m, (const uint32_t*)hist);
+    if (p == 0) {
+      hipLaunchKernelGGL(k_fold_hist, dim3((unsigned)(ntiles < 2048 ? ntiles : 2048)),
+                         dim3(kSortBlock), 0, st, low, sc.hist, ntiles, plan);
+      radix_pass<RP_COLS>(R, false, false, m, grid, sc, st);
+    } else {
+      radix_pass<RP_TIME>(R, true, false, m, grid, sc, st);
+    }
   }
   return true;
 }
@@ -892,15 +1067,17 @@ __global__ __launch_bounds__(256) void k_emit(const uint4* __restrict__ in, int6
                                               int32_t* __restrict__ other_col,
                                               int64_t* __restrict__ t_col,
                                               int32_t* __restrict__ eid_col,
-                                              uint4* __restrict__ rec, int32_t n,
+                                              uint4* __restrict__ rec, int32_t n, int vbits,
                                               uint32_t* __restrict__ off,
                                               int64_t* __restrict__ skip) {
   if (plan->bad) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < m) {
-    const uint4 r = in[i];
+    uint4 r = in[i];
+    const int64_t te = rec_time(*plan, t_in, r, vbits);
+    r.x &= vertex_mask(vbits);
+    r.z &= vertex_mask(vbits);
     key_col[i] = (int32_t)r.x;
-    const int64_t te = plan->wide ? t_in[r.y] : plan->tmin + (int64_t)r.w;
     other_col[i] = (int32_t)r.z;
     t_col[i] = te;
     eid_col[i] = (int32_t)r.y;
@@ -913,8 +1090,9 @@ __global__ __launch_bounds__(256) void k_emit(const uint4* __restrict__ in, int6
     }
   }
   if (off && i <= m) {
-    const int64_t prev = (i == 0) ? -1 : (int64_t)in[i - 1].x;
-    const int64_t cur = (i == m) ? (int64_t)n : (int64_t)in[i].x;
+    const uint32_t vm = vertex_mask(vbits);
+    const int64_t prev = (i == 0) ? -1 : (int64_t)(in[i - 1].x & vm);
+    const int64_t cur = (i == m) ? (int64_t)n : (int64_t)(in[i].x & vm);
     for (int64_t v = prev + 1; v <= cur; ++v) off[v] = (uint32_t)i;
   }
 }
@@ -951,21 +1129,13 @@ __global__ __launch_bounds__(256) void k_offsets(const int32_t* __restrict__ key
   }
 }
 
-// the validation word and the time range of the plan, for tc_graph
-__global__ void k_trange(const BuildPlan* __restrict__ plan, int64_t* __restrict__ tr) {
-  if (threadIdx.x == 0) {
-    tr[0] = plan->tmin;
-    tr[1] = plan->tmax;
-  }
-}
-
 // --------------------------------------------------------------- layout ----
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct GraphLayout {
   size_t out_off, in_off, out_src, out_dst, out_eid, out_t, in_src, in_eid, in_dst, in_t,
       pair_dst, out_rec, in_rec, pair_eid, pair_t, pair_hash, pair_skip, status, tminmax, trange,
-      plan, hist, part, part_elems, rr[4], total;
+      plan, low, hist, part, part_elems, rr[4], total;
 };
 
 static GraphLayout graph_layout(int32_t n, int64_t m) {
@@ -977,7 +1147,7 @@ static GraphLayout graph_layout(int32_t n, int64_t m) {
     return at;
   };
   const size_t M = (size_t)m;
-  const int64_t ntiles = (m + kRecTile - 1) / kRecTile;
+  const int64_t ntiles = sort_tiles(m);
   L.out_off = take(((size_t)n + 1) * 4);
   L.in_off = take(((size_t)n + 1) * 4);
   L.out_src = take(M * 4);
@@ -1002,9 +1172,10 @@ static GraphLayout graph_layout(int32_t n, int64_t m) {
   L.plan = take(sizeof(BuildPlan));
   // sort scratch: four 16-byte-record buffers
   for (int b = 0; b < 4; ++b) L.rr[b] = take((M + 1) * 16);
+  L.low = take((size_t)kMaxBins * ntiles * 4);
   L.hist = take((size_t)kMaxBins * ntiles * 4);
   // scan scratch of the histogram column scan
-  L.part_elems = col_scan_scratch_elems(ntiles, kMaxBins);
+  L.part_elems = col_scan_scratch_elems(ntiles);
   L.part = take(L.part_elems * 4);
   L.total = o;
   return L;
@@ -1050,20 +1221,21 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
   g->in_rec = (void*)(base + L.in_rec);
   uint64_t* tminmax = (uint64_t*)(base + L.tminmax);
   BuildPlan* plan = (BuildPlan*)(base + L.plan);
+  uint32_t* low = (uint32_t*)(base + L.low);
   uint32_t* hist = (uint32_t*)(base + L.hist);
   uint32_t* part = (uint32_t*)(base + L.part);
-  const size_t pe = L.part_elems;
 
+  const int vbits = bitlen((uint64_t)(n - 1));
   // validation and the sort plan, on the device
   hipLaunchKernelGGL(k_init_build, dim3(1), dim3(64), 0, st, g->status, tminmax);
   if (m > 0) {
-    const int64_t ntiles = (m + kRecTile - 1) / kRecTile;
-    hipLaunchKernelGGL(k_validate, dim3((unsigned)(ntiles < 1024 ? ntiles : 1024)),
-                       dim3(kSortBlock), 0, st, src, dst, t, m, n, g->status, tminmax, hist);
+    const int64_t ntiles = sort_tiles(m);
+    hipLaunchKernelGGL(large_tiles(m) ? k_validate<kItemsLarge> : k_validate<kItemsSmall>,
+                       dim3((unsigned)(ntiles < 1024 ? ntiles : 1024)), dim3(kSortBlock), 0, st,
+                       src, dst, t, m, n, g->status, tminmax, low);
   }
   hipLaunchKernelGGL(k_plan, dim3(1), dim3(64), 0, st, (const uint32_t*)g->status,
-                     (const uint64_t*)tminmax, m, plan);
-  hipLaunchKernelGGL(k_trange, dim3(1), dim3(64), 0, st, (const BuildPlan*)plan, g->t_range);
+                     (const uint64_t*)tminmax, m, vbits, plan, g->t_range);
   clear_pair_hash(g, st);
   if (m == 0) {
     hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for((int64_t)n + 1, 256)), dim3(256), 0, st,
@@ -1073,14 +1245,13 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
     if (hipGetLastError() != hipSuccess) return TC_E_HIP;
     return TC_OK;
   }
-  const int vbits = bitlen((uint64_t)(n - 1));
   const unsigned eb = blocks_for(m, 256);
   uint4* rr[4];
   for (int b = 0; b < 4; ++b) rr[b] = (uint4*)(base + L.rr[b]);
   // 1. time order, ending in rr[0] re-keyed as the out-CSR input
   const EdgeCols ec{src, dst, t};
-  if (!time_sort<kRecItems>(plan, ec, rr[0], rr[1], m, hist, part, pe, st, RX_OUT, nullptr,
-                            RX_NONE))
+  const SortScratch sc{hist, part, L.part_elems, vbits};
+  if (!time_sort(plan, ec, rr[0], rr[1], m, (const uint32_t*)low, sc, st, RX_OUT))
     return TC_E_WORKSPACE;
   // A vertex sort of rr[from] (spare rr[tmp]) whose last pass writes the
   // columns E; with no pass (n = 1) the records are emitted from rr[from].
@@ -1089,16 +1260,15 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
   // pass reads the in-list columns instead of rr[from].
   auto sort_emit = [&](int from, int tmp, const EmitCols& E, uint32_t* off, int extra = -1,
                        int xf2 = RX_NONE, int in0 = -1, int xf_in = RX_NONE,
-                       const InCols* ic = nullptr) -> bool {
-    const int w = radix_sort<kRecItems>(rr[from], rr[tmp], m, vbits, hist, part, pe, st,
-                                        RX_NONE, extra < 0 ? (uint4*)nullptr : rr[extra], xf2,
-                                        &E, in0 < 0 ? (const uint4*)nullptr : rr[in0], xf_in,
-                                        ic);
+                       const InCols* ic = nullptr, uint32_t* first = nullptr) -> bool {
+    const int w = radix_sort(rr[from], rr[tmp], m, vbits, sc, st,
+                             extra < 0 ? (uint4*)nullptr : rr[extra], xf2, E,
+                             in0 < 0 ? (const uint4*)nullptr : rr[in0], xf_in, ic, first);
     if (w < 0) return false;
-    if (w != 2)
+    if (w == 0)
       hipLaunchKernelGGL(k_emit, dim3(blocks_for(m + 1, 256)), dim3(256), 0, st,
-                         (const uint4*)rr[w ? tmp : from], m, (const BuildPlan*)plan, t, E.key,
-                         E.other, E.t, E.eid, E.rec, n, off, E.skip);
+                         (const uint4*)rr[from], m, (const BuildPlan*)plan, t, E.key,
+                         E.other, E.t, E.eid, E.rec, n, vbits, off, E.skip);
     else if (off)
       hipLaunchKernelGGL(k_offsets, dim3(blocks_for((m + kOffItems) / kOffItems, 256)),
                          dim3(256), 0, st, (const int32_t*)E.key, m, (const BuildPlan*)plan, n,
@@ -1110,15 +1280,23 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
   //    the in-list columns.  With a single vertex (no pass) a copy of the
   //    records re-keyed for the pair index goes to rr[3] instead.
   const bool one = vbits == 0;
+  if (!one) {
+    // the first histograms of the in-CSR sort (hist) and of the out-CSR sort
+    // (low, free now)
+    const int db = vertex_digit(vbits, digit_passes(vbits), 0);
+    hipLaunchKernelGGL(large_tiles(m) ? k_radix_hist2<kItemsLarge> : k_radix_hist2<kItemsSmall>,
+                       dim3((unsigned)sort_tiles(m)), dim3(kSortBlock), 0, st,
+                       (const uint4*)rr[0], (const BuildPlan*)plan, db, m, hist, low);
+  }
   if (!sort_emit(2, 1,
                  EmitCols{plan, t, g->in_dst, g->in_src, g->in_t, g->in_eid, (uint4*)g->in_rec,
                           nullptr},
-                 g->in_off, one ? 3 : -1, RX_PAIR, 0, RX_PAIR))
+                 g->in_off, one ? 3 : -1, RX_PAIR, 0, RX_PAIR, nullptr, one ? nullptr : hist))
     return TC_E_WORKSPACE;
   // 3. pair index: the in-order (dst, t, eid), read from the in-list
   //    columns, stably by src; the pair sources go to the free buffer rr[2]
   int32_t* psrc = (int32_t*)rr[2];
-  const InCols ic{(const uint4*)g->in_rec, g->in_dst, plan};
+  const InCols ic{(const uint4*)g->in_rec, g->in_dst, g->in_src};
   if (!sort_emit(3, 1,
                  EmitCols{plan, t, psrc, g->pair_dst, g->pair_t, g->pair_eid, nullptr,
                           g->pair_skip},
@@ -1131,7 +1309,7 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
   if (!sort_emit(0, 1,
                  EmitCols{plan, t, g->out_src, g->out_dst, g->out_t, g->out_eid,
                           (uint4*)g->out_rec, nullptr},
-                 g->out_off))
+                 g->out_off, -1, RX_NONE, -1, RX_NONE, nullptr, one ? nullptr : low))
     return TC_E_WORKSPACE;
   if (hipGetLastError() != hipSuccess) return TC_E_HIP;
   return TC_OK;

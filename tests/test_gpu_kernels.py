@@ -110,3 +110,41 @@ def test_features_long_runs_and_tiles(tcb, torch_mod, m, delta):
     got = (F.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
     want = og.features(og.weights(delta))
     assert np.all(np.abs(got - want) <= 2.0**-8 * np.abs(want) + 1e-6)
+
+
+@pytest.mark.parametrize("m", [2047, 2049, 131073, 2999999, 3000001])
+@pytest.mark.parametrize("n,t_bits", [(1, 40), (3, 33), (1 << 11, 22), (1 << 12, 36), (50000, 46), (50000, 55),
+                                      (1 << 26, 60)])
+def test_build_orders(tcb, torch_mod, m, n, t_bits):
+    """The three orders against torch sorts of the same keys: tile
+    remainders of both tile sizes, one and several digits per sort, and time
+    ranges below 32 bits, packed beside the vertex word and too wide for it."""
+    torch = torch_mod
+    gen = torch.Generator(device="cuda").manual_seed(m + n)
+    src = torch.randint(0, n, (m,), device="cuda", generator=gen).int()
+    dst = (torch.randint(0, n, (m,), device="cuda", generator=gen).int() // 2)
+    # repeated times, around zero, both ends of the range present
+    t = torch.randint(0, 1 << t_bits, (m,), device="cuda", generator=gen)
+    t[: m // 2] = t[m - m // 2:]
+    t[0], t[-1] = 0, (1 << t_bits) - 1
+    t -= 1 << (t_bits - 1)
+    g = tcb.tc_build_graph(n, src, dst, t, check=True).arrays()
+    by_t = torch.sort(t, stable=True)[1]
+
+    def order(*keys):  # stable, most significant key last
+        o = by_t
+        for k in keys:
+            o = o[torch.sort(k[o], stable=True)[1]]
+        return o
+
+    for name, o, key, other in (("out", order(src), src, dst), ("in", order(dst), dst, src)):
+        far = "dst" if name == "out" else "src"
+        near = "src" if name == "out" else "dst"
+        assert torch.equal(g[name + "_eid"].long(), o)
+        assert torch.equal(g[f"{name}_{near}"], key[o]) and torch.equal(g[f"{name}_{far}"], other[o])
+        assert torch.equal(g[name + "_t"], t[o])
+        off = torch.searchsorted(key[o].long(), torch.arange(n + 1, device="cuda"))
+        assert torch.equal(g[name + "_off"].long(), off)
+    o = order(dst, src)
+    assert torch.equal(g["pair_eid"].long(), o) and torch.equal(g["pair_dst"], dst[o])
+    assert torch.equal(g["pair_t"], t[o])
