@@ -47,12 +47,24 @@ static int64_t sort_tiles(int64_t m) {
   return (m + t - 1) / t;
 }
 
+// XCD-aware tile order: workgroups are dealt to the XCDs round robin (block b
+// to XCD b mod 8), and each XCD has its own L2.  Neighbouring tiles write
+// neighbouring pieces of every digit run, so each XCD takes a contiguous range
+// of the nb tiles: partial cache lines then meet in one L2 instead of being
+// written back piecewise from several.
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t block, uint32_t nb) {
+  const uint32_t xcd = block % kXcds, slot = block / kXcds;
+  const uint32_t q = nb / kXcds, rem = nb % kXcds;
+  return xcd * q + (xcd < rem ? xcd : rem) + slot;
+}
+
 static unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 // ------------------------------------------------------------ validation ---
-__global__ void k_init_build(uint32_t* status, uint64_t* tminmax) {
+__global__ void k_init_build(uint32_t* status, uint64_t* tminmax, uint32_t* spill_count) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     *status = 0;
+    *spill_count = 0;
     tminmax[0] = ~0ull;  // min of order-preserving keys
     tminmax[1] = 0ull;   // max
   }
@@ -624,8 +636,8 @@ __global__ __launch_bounds__(256) void k_col_apply(uint32_t* __restrict__ hist, 
 }
 
 // the totals row, then the chunk sums
-size_t col_scan_scratch_elems(int64_t ntiles) {
-  return (size_t)kMaxBins * ((ntiles + kColChunk - 1) / kColChunk + 1);
+size_t col_scan_scratch_elems(int64_t ntiles, int bins) {
+  return (size_t)bins * ((ntiles + kColChunk - 1) / kColChunk + 1);
 }
 
 static void col_scan(uint32_t* hist, int64_t ntiles, uint32_t* part, const PassBins& G,
@@ -637,7 +649,7 @@ static void col_scan(uint32_t* hist, int64_t ntiles, uint32_t* part, const PassB
     return;
   }
   const int64_t nchunks = (ntiles + kColChunk - 1) / kColChunk;
-  uint32_t* csum = part + kMaxBins;
+  uint32_t* csum = part + bins;
   hipLaunchKernelGGL(k_col_sum, dim3((unsigned)nchunks), dim3(256), 0, st,
                      (const uint32_t*)hist, ntiles, csum, G);
   hipLaunchKernelGGL(k_col_scan, dim3(bins), dim3(256), 0, st, csum, nchunks, part, G);
@@ -707,12 +719,7 @@ __global__ __launch_bounds__(kSortBlock, ITEMS > 5 ? 4 : 6) void k_radix_scatter
   uint4* const s_rec = reinterpret_cast<uint4*>(s_mem);
   const uint32_t nb = (uint32_t)((m + kTile - 1) / kTile);
   // One tile per block, or several when the grid is smaller (a multiple of 8
-  // blocks then, for the passes that are usually idle).  XCD-aware tile
-  // order: workgroups are dealt to the XCDs round robin (block b to XCD b mod
-  // 8), and each XCD has its own L2.  Neighbouring tiles write neighbouring
-  // pieces of every digit run, so each XCD takes a contiguous range of tiles:
-  // partial cache lines then meet in one L2 instead of being written back
-  // piecewise from several.
+  // blocks then, for the passes that are usually idle).
   for (uint32_t vt = blockIdx.x; vt < nb; vt += gridDim.x) {
     // a thread index the compiler cannot carry over from the last tile: it
     // would keep every address formed from it in registers across the loop
@@ -720,9 +727,7 @@ __global__ __launch_bounds__(kSortBlock, ITEMS > 5 ? 4 : 6) void k_radix_scatter
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = (int)uni(threadIdx.x >> 6);
     uint16_t* const my_pos = s_pos + wave * bins;
-    const uint32_t xcd = vt % kXcds, slot = vt / kXcds;
-    const uint32_t q = nb / kXcds, rem = nb % kXcds;
-    const uint32_t tile = xcd * q + (xcd < rem ? xcd : rem) + slot;
+    const uint32_t tile = xcd_tile(vt, nb);
     const int64_t start = (int64_t)tile * kTile;
     const int len = (int)((m - start) < kTile ? (m - start) : kTile);
 
@@ -908,7 +913,7 @@ static int radix_sort(uint4* k0, uint4* k1, int64_t m, int bits, const SortScrat
                       hipStream_t st, uint4* extra, int xf2, const EmitCols& E, const uint4* in0,
                       int xf_in, const InCols* ic, uint32_t* first) {
   const int64_t ntiles = sort_tiles(m);
-  if (sc.part_elems < col_scan_scratch_elems(ntiles)) return -1;
+  if (sc.part_elems < col_scan_scratch_elems(ntiles, kMaxBins)) return -1;
   const int npass = digit_passes(bits);
   if (npass == 0) {
     if (extra || in0)
@@ -951,7 +956,7 @@ static int radix_sort(uint4* k0, uint4* k1, int64_t m, int bits, const SortScrat
 static bool time_sort(const BuildPlan* plan, const EdgeCols& ec, uint4* b0, uint4* b1, int64_t m,
                       const uint32_t* low, const SortScratch& sc, hipStream_t st, int xf1) {
   const int64_t ntiles = sort_tiles(m);
-  if (sc.part_elems < col_scan_scratch_elems(ntiles)) return false;
+  if (sc.part_elems < col_scan_scratch_elems(ntiles, kMaxBins)) return false;
   hipLaunchKernelGGL(k_rec_init, dim3(blocks_for(m, 256) < 2048 ? blocks_for(m, 256) : 2048),
                      dim3(256), 0, st, ec, m, plan, b0, xf1);
   for (int p = 0; p < kTimePasses; ++p) {
@@ -1002,45 +1007,269 @@ __global__ __launch_bounds__(256) void k_hash_clear(PairSlot* __restrict__ tab, 
   }
 }
 
-// One thread per pair-index position.  The thread at the first position of
-// a (src, dst) run finds where the run ends -- galloping over the sorted
-// keys, then bisecting the last gap, so a run of length L costs O(log L)
-// probes and most runs (a single edge) one -- and inserts {key, start, end}:
-// a compare-and-swap claims the slot's key, one 8-byte store fills the run.
-__global__ __launch_bounds__(256) void k_hash_insert(const uint32_t* __restrict__ psrc,
-                                                     const int32_t* __restrict__ pdst, int64_t m,
-                                                     PairSlot* __restrict__ tab, int log2cap) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  auto key_at = [&](int64_t j) { return pair_key(psrc[j], (uint32_t)pdst[j]); };
-  const uint64_t key = key_at(i);
-  if (i > 0 && key_at(i - 1) == key) return;
-  int64_t lo = i, hi, step = 1;  // key_at(lo) == key
-  for (;;) {
-    hi = lo + step;
-    if (hi >= m || key_at(hi) != key) break;
-    lo = hi;
-    step <<= 1;
+// The pair index's sorted (src, dst) keys.
+struct PairKeys {
+  const uint32_t* src;
+  const int32_t* dst;
+  int64_t m;
+  __device__ __forceinline__ uint64_t at(int64_t j) const {
+    return pair_key(src[j], (uint32_t)dst[j]);
   }
-  if (hi > m) hi = m;  // hi == m, or key_at(hi) != key
-  while (hi - lo > 1) {
-    const int64_t mid = lo + ((hi - lo) >> 1);
-    if (key_at(mid) == key)
-      lo = mid;
-    else
-      hi = mid;
+  // whether position i, of key `key`, starts a run
+  __device__ __forceinline__ bool head(int64_t i, uint64_t key) const {
+    return i == 0 || at(i - 1) != key;
   }
+  // where the run starting at i ends: galloping over the sorted keys, then
+  // bisecting the last gap, so a run of length L costs O(log L) probes and
+  // most runs (a single edge) one
+  __device__ __forceinline__ int64_t run_end(int64_t i, uint64_t key) const {
+    int64_t lo = i, hi, step = 1;  // at(lo) == key
+    for (;;) {
+      hi = lo + step;
+      if (hi >= m || at(hi) != key) break;
+      lo = hi;
+      step <<= 1;
+    }
+    if (hi > m) hi = m;  // hi == m, or at(hi) != key
+    while (hi - lo > 1) {
+      const int64_t mid = lo + ((hi - lo) >> 1);
+      if (at(mid) == key)
+        lo = mid;
+      else
+        hi = mid;
+    }
+    return hi;
+  }
+};
+
+// Linear probing from slot h: a compare-and-swap claims the slot's key, one
+// 8-byte store fills the run.
+__device__ __forceinline__ void table_insert(PairSlot* __restrict__ tab, int log2cap, uint64_t h,
+                                             uint64_t key, uint32_t start, uint32_t end) {
   const uint64_t mask = (1ull << log2cap) - 1;
-  uint64_t h = pair_hash(key, log2cap);
   for (uint64_t probe = 0; probe <= mask; ++probe) {
     const unsigned long long prev =
         atomicCAS((unsigned long long*)&tab[h].key, (unsigned long long)kPairEmpty,
                   (unsigned long long)key);
     if (prev == kPairEmpty) {
-      *reinterpret_cast<uint2*>(&tab[h].start) = make_uint2((uint32_t)i, (uint32_t)hi);
+      *reinterpret_cast<uint2*>(&tab[h].start) = make_uint2(start, end);
       return;
     }
     h = (h + 1) & mask;
+  }
+}
+
+// One thread per pair-index position, the first of a run inserts it.
+__global__ __launch_bounds__(256) void k_hash_insert(PairKeys K, PairSlot* __restrict__ tab,
+                                                     int log2cap,
+                                                     const BuildPlan* __restrict__ plan) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= K.m || plan->bad) return;
+  const uint64_t key = K.at(i);
+  if (!K.head(i, key)) return;
+  table_insert(tab, log2cap, pair_hash(key, log2cap), key, (uint32_t)i,
+               (uint32_t)K.run_end(i, key));
+}
+
+// The table without random memory atomics.  A compare-and-swap on a random
+// line and the store into it run at 1.4*10^10 per second (1.42 ms for the
+// 2*10^7-edge graph, a third of its build); so the runs are first grouped by
+// the table segment that their home slot lies in (one radix pass over them,
+// in any order inside a group), then one block per segment places its runs
+// by linear probing in LDS and writes the whole segment, empty slots
+// included, as one stream.  A run that would probe past its segment's end is
+// put aside and inserted into the following segment afterwards, when every
+// slot from its home to the segment's end is taken, as a search expects.
+// Same graph: 0.58 ms (0.21 the grouping scatter, 0.29 the segments), and no
+// pass to clear the table.
+//
+// Segments have 2^14 slots (64 KB of LDS, two blocks per CU), or 2^15 where
+// the groups would be more than kMaxGroups; the groups' count rows then bound
+// the tables it serves (up to 2^27 slots: 10^8 edges).  Larger ones would
+// take a second grouping pass, which costs what the atomics do, and below
+// 2^21 slots (0.8*10^6 edges) the atomics' 25 us are less than three more
+// launches: both take k_hash_insert.
+constexpr int kSegLog2 = 14, kMaxSegLog2 = 15, kMaxGroupLog2 = 12, kGroupFromLog2 = 21;
+static_assert(1 << (kGroupFromLog2 - kSegLog2) >= kMinBins, "whole rows of the column scan");
+constexpr int kMaxGroups = 1 << kMaxGroupLog2;
+// 4,096 pair positions per grouping tile
+constexpr int kRunBlock = 1024, kRunItems = 4, kRunTile = kRunBlock * kRunItems;
+
+static int group_log2(int log2cap) {  // 0: not grouped
+  if (log2cap < kGroupFromLog2 || log2cap > kMaxSegLog2 + kMaxGroupLog2) return 0;
+  return log2cap - kSegLog2 < kMaxGroupLog2 ? log2cap - kSegLog2 : kMaxGroupLog2;
+}
+static int64_t run_tiles(int64_t m) { return (m + kRunTile - 1) / kRunTile; }
+
+// The runs of a grouping tile: thread tid's positions start + 1024 r + tid, the
+// key of each, and for the first of a run its group (else ~0)
+struct RunTile {
+  uint64_t key[kRunItems];
+  uint32_t group[kRunItems];
+  bool single[kRunItems];  // the next position has another key
+  __device__ __forceinline__ void load(const PairKeys& K, int64_t start, int tid, int glog2) {
+    uint64_t prev[kRunItems], next[kRunItems];
+#pragma unroll
+    for (int r = 0; r < kRunItems; ++r) {  // every load issued together
+      const int64_t i = start + (int64_t)r * kRunBlock + tid;
+      key[r] = i < K.m ? K.at(i) : 0;
+      prev[r] = i > 0 && i < K.m ? K.at(i - 1) : ~0ull;
+      next[r] = i + 1 < K.m ? K.at(i + 1) : ~0ull;  // no key (vertices are below 2^31)
+    }
+#pragma unroll
+    for (int r = 0; r < kRunItems; ++r) {
+      const bool head = start + (int64_t)r * kRunBlock + tid < K.m && prev[r] != key[r];
+      group[r] = head ? (uint32_t)pair_hash(key[r], glog2) : ~0u;
+      single[r] = next[r] != key[r];
+    }
+  }
+};
+
+// per-tile group counts
+__global__ __launch_bounds__(kRunBlock) void k_run_hist(PairKeys K, int glog2,
+                                                         uint32_t* __restrict__ hist,
+                                                         const BuildPlan* __restrict__ plan) {
+  if (plan->bad) return;
+  __shared__ uint32_t s_n[kMaxGroups];
+  const int groups = 1 << glog2, tid = threadIdx.x;
+  for (int g = tid; g < groups; g += kRunBlock) s_n[g] = 0;
+  __syncthreads();
+  const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
+  RunTile T;
+  T.load(K, (int64_t)tile * kRunTile, tid, glog2);
+#pragma unroll
+  for (int r = 0; r < kRunItems; ++r)
+    if (T.group[r] != ~0u) atomicAdd(&s_n[T.group[r]], 1u);
+  __syncthreads();
+  for (int g = tid; g < groups; g += kRunBlock) hist[(int64_t)tile * groups + g] = s_n[g];
+}
+
+// The runs {key, start, end} to their groups (hist: the group's runs in the
+// tiles before, tot: group totals), staged in LDS so that a tile's runs of a
+// group are written together.
+__global__ __launch_bounds__(kRunBlock) void k_run_scatter(PairKeys K, int glog2,
+                                                            const uint32_t* __restrict__ hist,
+                                                            const uint32_t* __restrict__ tot,
+                                                            uint4* __restrict__ list,
+                                                            const BuildPlan* __restrict__ plan) {
+  if (plan->bad) return;
+  extern __shared__ __align__(16) char s_raw[];
+  uint4* const s_rec = reinterpret_cast<uint4*>(s_raw);
+  const int groups = 1 << glog2, tid = threadIdx.x;
+  uint32_t* const s_off = reinterpret_cast<uint32_t*>(s_rec + kRunTile);  // counts, then starts
+  uint32_t* const s_base = s_off + groups;
+  __shared__ uint64_t s_w[kRunBlock / kWave];
+  __shared__ uint32_t s_total;
+  for (int g = tid; g < groups; g += kRunBlock) s_off[g] = 0;
+  __syncthreads();
+  const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int64_t start = (int64_t)tile * kRunTile;
+  RunTile T;
+  T.load(K, start, tid, glog2);
+  uint32_t rank[kRunItems];
+#pragma unroll
+  for (int r = 0; r < kRunItems; ++r)
+    rank[r] = T.group[r] != ~0u ? atomicAdd(&s_off[T.group[r]], 1u) : 0u;
+  __syncthreads();
+  // thread tid's consecutive groups: one scan gives their starts in the list
+  // (totals, above bit 16) and in the tile (counts, below)
+  constexpr int kOwn = kMaxGroups / kRunBlock;
+  const int own = (groups + kRunBlock - 1) / kRunBlock;  // at most kOwn
+  uint32_t cnt[kOwn], t[kOwn];
+  uint64_t sum = 0;
+#pragma unroll
+  for (int j = 0; j < kOwn; ++j) {
+    const int g = own * tid + j;
+    const bool in = j < own && g < groups;
+    cnt[j] = in ? s_off[g] : 0u;
+    t[j] = in ? tot[g] : 0u;
+    sum += ((uint64_t)t[j] << 16) + cnt[j];
+  }
+  const uint64_t inc = wave_inclusive_scan(sum);
+  if ((tid & 63) == 63) s_w[tid >> 6] = inc;
+  __syncthreads();
+  uint64_t run = inc - sum;
+#pragma unroll
+  for (int w = 0; w < kRunBlock / kWave; ++w) run += w < (tid >> 6) ? s_w[w] : 0ull;
+#pragma unroll
+  for (int j = 0; j < kOwn; ++j) {
+    const int g = own * tid + j;
+    if (j < own && g < groups) {
+      const uint32_t off = (uint32_t)run & 0xFFFFu;
+      s_off[g] = off;
+      s_base[g] = (uint32_t)(run >> 16) + hist[(int64_t)tile * groups + g] - off;
+    }
+    run += ((uint64_t)t[j] << 16) + cnt[j];
+  }
+  if (tid == kRunBlock - 1) s_total = (uint32_t)run & 0xFFFFu;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRunItems; ++r)
+    if (T.group[r] != ~0u) {
+      const int64_t i = start + (int64_t)r * kRunBlock + tid;
+      const int64_t end = T.single[r] ? i + 1 : K.run_end(i, T.key[r]);
+      s_rec[s_off[T.group[r]] + rank[r]] = make_uint4((uint32_t)T.key[r],
+                                                      (uint32_t)(T.key[r] >> 32), (uint32_t)i,
+                                                      (uint32_t)end);
+    }
+  __syncthreads();
+  for (uint32_t j = tid; j < s_total; j += kRunBlock) {
+    const uint4 r = s_rec[j];
+    list[s_base[pair_hash(((uint64_t)r.y << 32) | r.x, glog2)] + j] = r;
+  }
+}
+static size_t run_scatter_lds(int glog2) { return (size_t)kRunTile * 16 + ((size_t)8 << glog2); }
+
+constexpr int kSegBlock = 1024;
+__global__ __launch_bounds__(kSegBlock) void k_table_segment(const uint4* __restrict__ list,
+                                                             const uint32_t* __restrict__ tot,
+                                                             int log2cap, int glog2,
+                                                             uint4* __restrict__ tab,
+                                                             uint32_t* __restrict__ spill,
+                                                             uint32_t* __restrict__ spill_count,
+                                                             const BuildPlan* __restrict__ plan) {
+  extern __shared__ uint32_t s_slot[];  // per slot of the segment: its run, or ~0
+  __shared__ uint32_t s_w[kSegBlock / kWave];
+  const int tid = threadIdx.x, seg = blockIdx.x;
+  const uint32_t slots = 1u << (log2cap - glog2);
+  for (uint32_t q = tid; q < slots; q += kSegBlock) s_slot[q] = ~0u;
+  uint32_t before = 0;  // runs of the groups below
+  for (int g = tid; g < seg; g += kSegBlock) before += tot[g];
+  before = lane_u32(scan_dpp(before), kWave - 1);
+  if ((tid & 63) == 0) s_w[tid >> 6] = before;
+  __syncthreads();
+  uint32_t first = 0;
+  for (int w = 0; w < kSegBlock / kWave; ++w) first += s_w[w];
+  const bool bad = plan->bad != 0;  // a rejected input: an empty table
+  const uint32_t n = bad ? 0u : tot[seg];
+  for (uint32_t j = tid; j < n; j += kSegBlock) {
+    const uint4 r = list[first + j];
+    const uint64_t key = ((uint64_t)r.y << 32) | r.x;
+    uint32_t q = (uint32_t)pair_hash(key, log2cap) & (slots - 1);
+    while (q < slots && atomicCAS(&s_slot[q], ~0u, j) != ~0u) ++q;
+    if (q == slots) spill[atomicAdd(spill_count, 1u)] = first + j;
+  }
+  __syncthreads();
+  uint4* const out = tab + (uint64_t)seg * slots;
+  for (uint32_t q = tid; q < slots; q += kSegBlock) {
+    const uint32_t j = s_slot[q];
+    out[q] = j == ~0u ? make_uint4(~0u, ~0u, 0u, 0u) : list[first + j];
+  }
+}
+
+// the runs put aside, from the segment after their own
+__global__ __launch_bounds__(256) void k_table_spill(const uint4* __restrict__ list,
+                                                     const uint32_t* __restrict__ spill,
+                                                     const uint32_t* __restrict__ spill_count,
+                                                     int log2cap, int glog2,
+                                                     PairSlot* __restrict__ tab) {
+  const uint32_t n = *spill_count;
+  const int shift = log2cap - glog2;
+  for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+    const uint4 r = list[spill[i]];
+    const uint64_t key = ((uint64_t)r.y << 32) | r.x;
+    const uint64_t next = ((pair_hash(key, glog2) + 1) << shift) & ((1ull << log2cap) - 1);
+    table_insert(tab, log2cap, next, key, r.z, r.w);
   }
 }
 
@@ -1135,7 +1364,8 @@ static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct GraphLayout {
   size_t out_off, in_off, out_src, out_dst, out_eid, out_t, in_src, in_eid, in_dst, in_t,
       pair_dst, out_rec, in_rec, pair_eid, pair_t, pair_hash, pair_skip, status, tminmax, trange,
-      plan, low, hist, part, part_elems, rr[4], total;
+      plan, low, hist, part, part_elems, spill_count,
+      rr[4], total;
 };
 
 static GraphLayout graph_layout(int32_t n, int64_t m) {
@@ -1173,9 +1403,15 @@ static GraphLayout graph_layout(int32_t n, int64_t m) {
   // sort scratch: four 16-byte-record buffers
   for (int b = 0; b < 4; ++b) L.rr[b] = take((M + 1) * 16);
   L.low = take((size_t)kMaxBins * ntiles * 4);
-  L.hist = take((size_t)kMaxBins * ntiles * 4);
+  // (the grouping of the run table uses the same matrix and scan scratch)
+  const int64_t groups = (int64_t)1 << group_log2(pair_hash_log2(m));
+  const size_t rows = (size_t)kMaxBins * (size_t)ntiles, grows = (size_t)(groups * run_tiles(m));
+  L.hist = take((rows > grows ? rows : grows) * 4);
   // scan scratch of the histogram column scan
-  L.part_elems = col_scan_scratch_elems(ntiles);
+  L.part_elems = col_scan_scratch_elems(ntiles, kMaxBins);
+  const size_t gpart = col_scan_scratch_elems(run_tiles(m), (int)groups);
+  if (gpart > L.part_elems) L.part_elems = gpart;
+  L.spill_count = take(4);
   L.part = take(L.part_elems * 4);
   L.total = o;
   return L;
@@ -1224,10 +1460,12 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
   uint32_t* low = (uint32_t*)(base + L.low);
   uint32_t* hist = (uint32_t*)(base + L.hist);
   uint32_t* part = (uint32_t*)(base + L.part);
+  uint32_t* spill_count = (uint32_t*)(base + L.spill_count);
 
   const int vbits = bitlen((uint64_t)(n - 1));
   // validation and the sort plan, on the device
-  hipLaunchKernelGGL(k_init_build, dim3(1), dim3(64), 0, st, g->status, tminmax);
+  hipLaunchKernelGGL(k_init_build, dim3(1), dim3(64), 0, st, g->status, tminmax,
+                     spill_count);
   if (m > 0) {
     const int64_t ntiles = sort_tiles(m);
     hipLaunchKernelGGL(large_tiles(m) ? k_validate<kItemsLarge> : k_validate<kItemsSmall>,
@@ -1236,7 +1474,8 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
   }
   hipLaunchKernelGGL(k_plan, dim3(1), dim3(64), 0, st, (const uint32_t*)g->status,
                      (const uint64_t*)tminmax, m, vbits, plan, g->t_range);
-  clear_pair_hash(g, st);
+  const int lg = g->pair_hash_log2, glog2 = group_log2(lg);
+  if (m == 0 || glog2 == 0) clear_pair_hash(g, st);
   if (m == 0) {
     hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for((int64_t)n + 1, 256)), dim3(256), 0, st,
                        g->out_off, (int64_t)n + 1, 0u);
@@ -1245,7 +1484,6 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
     if (hipGetLastError() != hipSuccess) return TC_E_HIP;
     return TC_OK;
   }
-  const unsigned eb = blocks_for(m, 256);
   uint4* rr[4];
   for (int b = 0; b < 4; ++b) rr[b] = (uint4*)(base + L.rr[b]);
   // 1. time order, ending in rr[0] re-keyed as the out-CSR input
@@ -1302,9 +1540,39 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
                           g->pair_skip},
                  nullptr, -1, RX_NONE, -1, RX_NONE, one ? nullptr : &ic))
     return TC_E_WORKSPACE;
-  // 4. the run table (its clear was enqueued first)
-  hipLaunchKernelGGL(k_hash_insert, dim3(eb), dim3(256), 0, st, (const uint32_t*)psrc,
-                     (const int32_t*)g->pair_dst, m, (PairSlot*)g->pair_hash, g->pair_hash_log2);
+  // 4. the run table: grouped runs in rr[3] and the list of those put aside
+  //    in rr[1] (both free until the out-CSR sort), or inserted one by one
+  //    into the cleared table
+  const PairKeys pk{(const uint32_t*)psrc, (const int32_t*)g->pair_dst, m};
+  if (glog2 == 0) {
+    hipLaunchKernelGGL(k_hash_insert, dim3(blocks_for(m, 256)), dim3(256), 0, st, pk,
+                       (PairSlot*)g->pair_hash, lg, (const BuildPlan*)plan);
+  } else {
+    const int64_t rt = run_tiles(m);
+    const int segs = 1 << glog2;
+    const size_t lds = (size_t)4 << (lg - glog2);
+    hipLaunchKernelGGL(k_run_hist, dim3((unsigned)rt), dim3(kRunBlock), 0, st, pk, glog2, hist,
+                       (const BuildPlan*)plan);
+    col_scan(hist, rt, part, PassBins{plan, -1, segs}, st);
+    if (hipFuncSetAttribute((const void*)k_run_scatter,
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)run_scatter_lds(kMaxGroupLog2)) != hipSuccess)
+      return TC_E_HIP;
+    hipLaunchKernelGGL(k_run_scatter, dim3((unsigned)rt), dim3(kRunBlock),
+                       run_scatter_lds(glog2), st, pk, glog2, (const uint32_t*)hist,
+                       (const uint32_t*)part, rr[3], (const BuildPlan*)plan);
+    if (hipFuncSetAttribute((const void*)k_table_segment,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 4 << kMaxSegLog2) !=
+        hipSuccess)
+      return TC_E_HIP;
+    hipLaunchKernelGGL(k_table_segment, dim3((unsigned)segs), dim3(kSegBlock), lds, st,
+                       (const uint4*)rr[3], (const uint32_t*)part, lg, glog2,
+                       (uint4*)g->pair_hash, (uint32_t*)rr[1], spill_count,
+                       (const BuildPlan*)plan);
+    hipLaunchKernelGGL(k_table_spill, dim3(64), dim3(256), 0, st, (const uint4*)rr[3],
+                       (const uint32_t*)rr[1], (const uint32_t*)spill_count, lg, glog2,
+                       (PairSlot*)g->pair_hash);
+  }
   // 5. out-CSR: stable by src, from the time order in rr[0]
   if (!sort_emit(0, 1,
                  EmitCols{plan, t, g->out_src, g->out_dst, g->out_t, g->out_eid,

@@ -148,3 +148,43 @@ def test_build_orders(tcb, torch_mod, m, n, t_bits):
     o = order(dst, src)
     assert torch.equal(g["pair_eid"].long(), o) and torch.equal(g["pair_dst"], dst[o])
     assert torch.equal(g["pair_t"], t[o])
+
+
+@pytest.mark.parametrize("n,m", [(40, 900001), (5000, 1700000), (1 << 20, 13500000), (1 << 20, 14000003),
+                                 (1 << 22, 28000001)])
+def test_pair_table_finds_every_run(tcb, torch_mod, n, m):
+    """Every run of the pair index is found in the run table by linear
+    probing from its home slot, and no other key is in it: few and many runs
+    per segment, segments of both sizes, loads up to 0.8 (runs that do not
+    fit their segment)."""
+    torch = torch_mod
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    src = torch.randint(0, n, (m,), device="cuda", generator=gen).int()
+    dst = torch.randint(0, n, (m,), device="cuda", generator=gen).int()
+    t = torch.randint(0, 1000, (m,), device="cuda", generator=gen)
+    G = tcb.tc_build_graph(n, src, dst, t, check=True)
+    lg = G.c.pair_hash_log2
+    cap = 1 << lg
+    tab = G.view("pair_hash", torch.int64, 2 * cap).view(cap, 2)
+    run = tab[:, 1]
+    start, end = run & 0xFFFFFFFF, (run >> 32) & 0xFFFFFFFF
+    a = G.arrays()
+    ps = src[a["pair_eid"].long()].long()
+    key = (ps << 32) | a["pair_dst"].long()
+    want_start = torch.nonzero(torch.cat([torch.ones(1, dtype=torch.bool, device="cuda"),
+                                          key[1:] != key[:-1]])).flatten()
+    want_end = torch.cat([want_start[1:], torch.tensor([m], device="cuda")])
+    used = torch.nonzero(tab[:, 0] != -1).flatten()
+    assert used.numel() == want_start.numel()
+    o = torch.sort(start[used])[1]
+    used = used[o]
+    assert torch.equal(start[used], want_start) and torch.equal(end[used], want_end)
+    assert torch.equal(tab[used, 0], key[want_start])
+    # a search from the home slot reaches the run: no empty slot on the way
+    # (0x9E3779B97F4A7C15 as a signed word; the product wraps)
+    home = (key[want_start] * -7046029254386353131) >> (64 - lg)
+    home = home & (cap - 1)
+    empty = torch.cumsum(torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"),
+                                    (tab[:, 0] == -1).long()]), 0)
+    on_way = empty[used] - empty[home] + torch.where(used < home, empty[-1], 0)
+    assert int(on_way.abs().max()) == 0
