@@ -480,21 +480,29 @@ def new_result(n_motifs: int, k: int, device, per_sample: bool = False,
                moments: bool = False) -> Result:
     """Output buffers of one delta (per-sample arrays only with per_sample,
     the second moment only with moments)."""
-    nm = n_motifs
-    out = Result(torch.zeros(2 * nm, dtype=torch.int64, device=device),
-                 torch.zeros(nm, dtype=torch.int64, device=device),
-                 torch.zeros(nm, dtype=torch.float64, device=device),
-                 torch.zeros(1, dtype=torch.int32, device=device))
-    if per_sample:
-        out.e1 = torch.empty(k, dtype=torch.int32, device=device)
-        out.e2 = torch.empty(k, dtype=torch.int32, device=device)
-        out.e3 = torch.empty(k, dtype=torch.int32, device=device)
-        out.X = torch.empty((nm, k), dtype=torch.int64, device=device)
-        out.P = torch.empty(k, dtype=torch.int32, device=device)
-    if moments:
-        out.m2 = torch.zeros(nm, dtype=torch.float64, device=device)
-    out.xmax = torch.zeros(nm, dtype=torch.int64, device=device)
-    return out
+    return _results(1, n_motifs, k, device, per_sample, moments, torch.zeros)[0]
+
+
+def _results(n, nm, k, device, per_sample, moments, alloc=torch.empty):
+    """n Results whose per-motif outputs share one allocation (every call
+    overwrites them, so the calls' own are not cleared first)."""
+    per = 5 * nm + (nm if moments else 0) + 1
+    slab = alloc(n * per, dtype=torch.int64, device=device)
+    outs = []
+    for i in range(n):
+        w = slab[i * per:(i + 1) * per]
+        out = Result(w[:2 * nm], w[2 * nm:3 * nm], w[3 * nm:4 * nm].view(torch.float64),
+                     w[per - 1:].view(torch.int32)[:1], xmax=w[4 * nm:5 * nm])
+        if moments:
+            out.m2 = w[5 * nm:6 * nm].view(torch.float64)
+        if per_sample:
+            out.e1 = torch.empty(k, dtype=torch.int32, device=device)
+            out.e2 = torch.empty(k, dtype=torch.int32, device=device)
+            out.e3 = torch.empty(k, dtype=torch.int32, device=device)
+            out.X = torch.empty((nm, k), dtype=torch.int64, device=device)
+            out.P = torch.empty(k, dtype=torch.int32, device=device)
+        outs.append(out)
+    return outs
 
 
 def _c_result(out: Result) -> tc_result:
@@ -521,7 +529,7 @@ def tc_sample_estimate(graph: Graph, weights: Weights, motifs, k: int, seed: int
     nm, arr = _motif_array(motifs)
     dev = graph.ws.device
     if out is None:
-        out = new_result(nm, k, dev, per_sample, moments)
+        out = _results(1, nm, k, dev, per_sample, moments)[0]
         _on_stream(stream, out.cnt, out.hits, out.estimate, out.status, out.e1, out.e2, out.e3,
                    out.X, out.P, out.m2)
     r = _c_result(out)
@@ -545,7 +553,7 @@ def tc_exhaustive_count(graph: Graph, weights: Weights, motifs, r0: int = 0,
         count = max(1, weights.total() - r0)
     dev = graph.ws.device
     if out is None:
-        out = new_result(nm, count, dev, per_sample, moments=True)
+        out = _results(1, nm, count, dev, per_sample, True)[0]
         _on_stream(stream, out.cnt, out.hits, out.estimate, out.status, out.e1, out.e2, out.e3,
                    out.X, out.P, out.m2, out.xmax)
     r = _c_result(out)
@@ -563,7 +571,7 @@ def tc_sample_estimate_noalloc(graph: Graph, weights: Weights, motifs, k: int, s
     workspace is allocated for the call)."""
     nm, arr = _motif_array(motifs)
     if out is None:
-        out = new_result(nm, k, graph.ws.device, per_sample)
+        out = _results(1, nm, k, graph.ws.device, per_sample, False)[0]
         _on_stream(stream, out.cnt, out.hits, out.estimate, out.status, out.e1, out.e2, out.e3,
                    out.X, out.P)
     r = _c_result(out)
@@ -594,7 +602,7 @@ def tc_batch_estimate(graph: Graph, weights, motifs, k: int, seed: int, stream_i
     nm, arr = _motif_array(motifs)
     dev = graph.ws.device
     if outs is None:
-        outs = [new_result(nm, k, dev, per_sample) for _ in range(nd)]
+        outs = _results(nd, nm, k, dev, per_sample, False)
         for o in outs:
             _on_stream(stream, o.cnt, o.hits, o.estimate, o.status, o.e1, o.e2, o.e3, o.X, o.P)
     args = _BatchArgs(weights, outs)

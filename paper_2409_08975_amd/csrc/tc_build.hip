@@ -38,9 +38,11 @@ constexpr int kMaxDigit = 11;
 constexpr int kMaxBins = 1 << kMaxDigit;
 constexpr int kMinBins = 64;  // histogram rows are at least one 256-byte line
 // Records per thread: tiles of 4,096 records, or of 2,048 where the larger
-// ones would be too few to fill the CUs.
+// ones would be too few to fill the CUs (1,000,001 edges: the build 262 us
+// with small tiles, 280 with large; 2,000,001, where the small ones are past
+// the one-launch column scan, 490 and 368).
 constexpr int kItemsLarge = 8, kItemsSmall = 4;
-constexpr int64_t kLargeFrom = 3000000;
+constexpr int64_t kLargeFrom = (1 << 20) + 1;
 static bool large_tiles(int64_t m) { return m >= kLargeFrom; }
 static int64_t sort_tiles(int64_t m) {
   const int64_t t = (int64_t)kSortBlock * (large_tiles(m) ? kItemsLarge : kItemsSmall);
@@ -61,18 +63,16 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t block, uint32_t nb) {
 static unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 // ------------------------------------------------------------ validation ---
-__global__ void k_init_build(uint32_t* status, uint64_t* tminmax, uint32_t* spill_count) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    *status = 0;
-    *spill_count = 0;
-    tminmax[0] = ~0ull;  // min of order-preserving keys
-    tminmax[1] = 0ull;   // max
-  }
-}
+// What one block of the validation found; k_plan reduces them.
+struct Found {
+  uint64_t mn, mx;  // of order-preserving keys of the times
+  uint32_t bad;
+};
+constexpr int kMaxFound = 1024;
 
 // The validation, which also counts the low kMaxDigit bits of every time per
 // sort tile (tile-major rows of kMaxBins): the first pass of the time sort
-// takes its digit counts from these rows once t_min is known (k_fold_hist), so
+// takes its digit counts from these rows once t_min is known (k_start), so
 // it needs no histogram read of its own.  Each block walks tiles blockIdx.x,
 // blockIdx.x + gridDim.x, ...
 // t is mapped to an order-preserving unsigned key (flip the sign bit)
@@ -80,8 +80,7 @@ template <int ITEMS>
 __global__ __launch_bounds__(kSortBlock) void k_validate(const int32_t* __restrict__ src,
                                                          const int32_t* __restrict__ dst,
                                                          const int64_t* __restrict__ t, int64_t m,
-                                                         int32_t n, uint32_t* status,
-                                                         uint64_t* tminmax,
+                                                         int32_t n, Found* __restrict__ found,
                                                          uint32_t* __restrict__ hist) {
   const int64_t lim = (int64_t)1 << 62;
   uint64_t mn = ~0ull, mx = 0;
@@ -131,7 +130,6 @@ __global__ __launch_bounds__(kSortBlock) void k_validate(const int32_t* __restri
     mx = b > mx ? b : mx;
     bad |= __shfl_xor(bad, off, kWave);
   }
-  // one pair of atomics per block (not per wavefront): they all hit two words
   __shared__ uint64_t s_mn[kSortWaves], s_mx[kSortWaves];
   __shared__ uint32_t s_bad[kSortWaves];
   const int wave = threadIdx.x >> 6;
@@ -147,9 +145,7 @@ __global__ __launch_bounds__(kSortBlock) void k_validate(const int32_t* __restri
       mx = s_mx[w] > mx ? s_mx[w] : mx;
       bad |= s_bad[w];
     }
-    atomicMin((unsigned long long*)&tminmax[0], (unsigned long long)mn);
-    atomicMax((unsigned long long*)&tminmax[1], (unsigned long long)mx);
-    if (bad) atomicOr(status, TC_F_RANGE);
+    found[blockIdx.x] = Found{mn, mx, bad};
   }
 }
 
@@ -199,20 +195,48 @@ __host__ __device__ constexpr int hist_bins(int dbits) {
   return (1 << dbits) < kMinBins ? kMinBins : 1 << dbits;
 }
 
-__global__ void k_plan(const uint32_t* __restrict__ status, const uint64_t* __restrict__ tminmax,
-                       int64_t m, int vbits, BuildPlan* __restrict__ P,
-                       int64_t* __restrict__ t_range) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// one block of kMaxFound threads; also starts the counters of the build
+__global__ __launch_bounds__(kMaxFound) void k_plan(const Found* __restrict__ found, int nfound,
+                                                    int64_t m, int vbits,
+                                                    BuildPlan* __restrict__ P,
+                                                    uint32_t* __restrict__ status,
+                                                    int64_t* __restrict__ t_range,
+                                                    uint32_t* __restrict__ spill_count) {
+  const int tid = threadIdx.x;
+  uint64_t mn = ~0ull, mx = 0;
+  uint32_t any = 0;
+  if (tid < nfound) {
+    const Found f = found[tid];
+    mn = f.mn;
+    mx = f.mx;
+    any = f.bad;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const uint64_t a = __shfl_xor(mn, off, kWave), b = __shfl_xor(mx, off, kWave);
+    mn = a < mn ? a : mn;
+    mx = b > mx ? b : mx;
+    any |= __shfl_xor(any, off, kWave);
+  }
+  __shared__ Found s_f[kMaxFound / kWave];
+  if ((tid & 63) == 0) s_f[tid >> 6] = Found{mn, mx, any};
+  __syncthreads();
+  if (tid != 0) return;
+  for (int w = 1; w < kMaxFound / kWave; ++w) {
+    mn = s_f[w].mn < mn ? s_f[w].mn : mn;
+    mx = s_f[w].mx > mx ? s_f[w].mx : mx;
+    any |= s_f[w].bad;
+  }
   BuildPlan B;
-  B.bad = *status != 0 ? 1u : 0u;
+  B.bad = any;
   B.tmin = B.tmax = 0;
   B.wide = 0;
   B.npass = 0;
   B.high = kTimePasses;
   for (int p = 0; p < kTimePasses; ++p) B.shift[p] = B.dbits[p] = 0;
   if (!B.bad && m > 0) {
-    B.tmin = (int64_t)(tminmax[0] ^ (1ull << 63));
-    B.tmax = (int64_t)(tminmax[1] ^ (1ull << 63));
+    B.tmin = (int64_t)(mn ^ (1ull << 63));
+    B.tmax = (int64_t)(mx ^ (1ull << 63));
     const int tbits = bitlen_dev((uint64_t)(B.tmax - B.tmin));
     B.wide = tbits > 64 - vbits ? 1 : 0;
     const int lo = B.wide ? 32 : tbits, hi = tbits - lo;
@@ -223,34 +247,10 @@ __global__ void k_plan(const uint32_t* __restrict__ status, const uint64_t* __re
     if (B.wide) B.high = nlo;
   }
   *P = B;
+  *status = any ? TC_F_RANGE : 0u;
+  *spill_count = 0;
   t_range[0] = B.tmin;  // for tc_graph
   t_range[1] = B.tmax;
-}
-
-// The digit counts of the time sort's first pass from the validation's
-// counts of the low bits: its digit is the low w <= kMaxDigit bits of t - t_min
-// (shift 0), so digit d counts the low bits b with (b - t_min) mod 2^w = d.
-__global__ __launch_bounds__(kSortBlock) void k_fold_hist(const uint32_t* __restrict__ low,
-                                                          uint32_t* __restrict__ hist,
-                                                          int64_t ntiles,
-                                                          const BuildPlan* __restrict__ plan) {
-  if (plan->bad || plan->npass == 0) return;
-  __shared__ uint32_t s_r[kMaxBins];
-  const uint32_t W = 1u << plan->dbits[0], tm = (uint32_t)(uint64_t)plan->tmin;
-  const int bins = hist_bins(plan->dbits[0]);
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-#pragma unroll
-    for (int q = 0; q < kMaxBins / kSortBlock; ++q)
-      s_r[q * kSortBlock + threadIdx.x] = low[tile * kMaxBins + q * kSortBlock + threadIdx.x];
-    __syncthreads();
-    for (uint32_t d = threadIdx.x; d < (uint32_t)bins; d += kSortBlock) {
-      uint32_t v = 0;
-      if (d < W)
-        for (uint32_t b = (d + tm) & (W - 1); b < (uint32_t)kMaxBins; b += W) v += s_r[b];
-      hist[tile * bins + d] = v;
-    }
-    __syncthreads();  // the next row overwrites s_r
-  }
 }
 
 // ------------------------------------------------------------ radix pass ---
@@ -419,18 +419,44 @@ __device__ __forceinline__ uint32_t digit_of(const PassCfg& c, uint32_t mask, ui
   return (uint32_t)((((uint64_t)(w >> c.vbits) << 32) | x) >> c.shift) & mask;
 }
 
-// With no active time pass (every time equal): the records built from the
-// edge columns, re-keyed like the last pass of the time sort would leave them.
-__global__ __launch_bounds__(256) void k_rec_init(EdgeCols ec, int64_t m,
-                                                  const BuildPlan* __restrict__ plan,
-                                                  uint4* __restrict__ out, int xf1) {
-  if (plan->npass != 0 || plan->bad) return;
-  // grid-stride: the launch is small, since it is idle for all but inputs
-  // whose times are all equal
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const uint4 r = make_uint4(0u, (uint32_t)i, (uint32_t)ec.src[i], (uint32_t)ec.dst[i]);
-    out[i] = rec_xform(r, xf1);
+// What the sorts start from, in one launch: the digit counts of the time
+// sort's first pass from the validation's counts of the low bits (its digit is
+// the low w <= kMaxDigit bits of t - t_min, shift 0, so digit d counts the low
+// bits b with (b - t_min) mod 2^w = d); with no active time pass (every time
+// equal) the records built from the edge columns, re-keyed like the last pass
+// of the time sort would leave them; and the empty run table where runs are
+// inserted one by one (cap slots, else 0).
+__global__ __launch_bounds__(kSortBlock) void k_start(const uint32_t* __restrict__ low,
+                                                      uint32_t* __restrict__ hist,
+                                                      int64_t ntiles, EdgeCols ec, int64_t m,
+                                                      const BuildPlan* __restrict__ plan,
+                                                      uint4* __restrict__ out, int xf1,
+                                                      uint4* __restrict__ tab, int64_t cap) {
+  const int64_t first = (int64_t)blockIdx.x * kSortBlock + threadIdx.x;
+  const int64_t all = (int64_t)gridDim.x * kSortBlock;
+  for (int64_t i = first; i < cap; i += all) tab[i] = make_uint4(~0u, ~0u, 0u, 0u);
+  if (plan->bad) return;
+  if (plan->npass == 0) {
+    for (int64_t i = first; i < m; i += all)
+      out[i] = rec_xform(make_uint4(0u, (uint32_t)i, (uint32_t)ec.src[i], (uint32_t)ec.dst[i]),
+                         xf1);
+    return;
+  }
+  __shared__ uint32_t s_r[kMaxBins];
+  const uint32_t W = 1u << plan->dbits[0], tm = (uint32_t)(uint64_t)plan->tmin;
+  const int bins = hist_bins(plan->dbits[0]);
+  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+#pragma unroll
+    for (int q = 0; q < kMaxBins / kSortBlock; ++q)
+      s_r[q * kSortBlock + threadIdx.x] = low[tile * kMaxBins + q * kSortBlock + threadIdx.x];
+    __syncthreads();
+    for (uint32_t d = threadIdx.x; d < (uint32_t)bins; d += kSortBlock) {
+      uint32_t v = 0;
+      if (d < W)
+        for (uint32_t b = (d + tm) & (W - 1); b < (uint32_t)kMaxBins; b += W) v += s_r[b];
+      hist[tile * bins + d] = v;
+    }
+    __syncthreads();  // the next row overwrites s_r
   }
 }
 
@@ -513,14 +539,16 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_hist2(const uint4* __restr
 
 // Column scan of the tile-major histogram: hist[t][d] becomes the number of
 // keys of digit d in the tiles before t, and tot[d] the digit's total; the
-// scatter adds the keys of smaller digits.  Up to kOneScanTiles tiles it is
-// one kernel (32 digits per block, the tiles spread over its threads): at that
-// size a launch costs more than its work.  Above, three kernels: per-chunk
+// scatter adds the keys of smaller digits.  A launch costs 3 us, so up to
+// kSelfScanTiles tiles the scatter's blocks each add up the columns
+// themselves (20,001 edges: the build 120 -> 107 us; 60,001 edges in 30 tiles
+// 158 -> 165), and up to kOneScanTiles it is one kernel (32 digits per block,
+// the tiles spread over its threads).  Above, three kernels: per-chunk
 // column sums, an exclusive scan of each digit's chunk sums (which also
 // leaves the totals), and an in-place walk of every chunk.  Every access
 // reads or writes whole row pieces.  The row length follows the pass's digit;
 // a pass the plan leaves idle returns at once.
-constexpr int kOneScanTiles = 512;
+constexpr int kSelfScanTiles = 16, kOneScanTiles = 512;
 
 struct PassBins {
   const BuildPlan* plan;
@@ -741,8 +769,18 @@ __global__ __launch_bounds__(kSortBlock, ITEMS > 5 ? 4 : 6) void k_radix_scatter
     }
     uint4 gb{0, 0, 0, 0}, tt{0, 0, 0, 0};  // digits kOwn tid ..: prefix over tiles, totals
     if (kOwn * tid < bins) {
-      gb = *reinterpret_cast<const uint4*>(hist + (int64_t)tile * bins + kOwn * tid);
-      tt = *reinterpret_cast<const uint4*>(tot + kOwn * tid);
+      if (ITEMS == kItemsSmall && nb <= (uint32_t)kSelfScanTiles) {  // hist: plain counts
+#pragma unroll 8
+        for (uint32_t u = 0; u < nb; ++u) {
+          const uint4 v = *reinterpret_cast<const uint4*>(hist + (int64_t)u * bins + kOwn * tid);
+          tt.x += v.x, tt.y += v.y, tt.z += v.z, tt.w += v.w;
+          const uint32_t f = u < tile ? ~0u : 0u;
+          gb.x += v.x & f, gb.y += v.y & f, gb.z += v.z & f, gb.w += v.w & f;
+        }
+      } else {
+        gb = *reinterpret_cast<const uint4*>(hist + (int64_t)tile * bins + kOwn * tid);
+        tt = *reinterpret_cast<const uint4*>(tot + kOwn * tid);
+      }
     }
     for (int i = tid; i < kSortWaves * bins / 8; i += kSortBlock)
       reinterpret_cast<uint4*>(s_mem)[i] = uint4{0, 0, 0, 0};
@@ -869,8 +907,9 @@ void radix_pass(const RecPass& R, bool count, bool emit, int64_t m, unsigned gri
   if constexpr (KIND != RP_COLS)
     if (count)
     hipLaunchKernelGGL((k_radix_hist<ITEMS, KIND>), g, b, 0, st, R, m, sc.hist);
-  col_scan(sc.hist, ntiles, sc.part,
-           PassBins{R.plan, R.time, R.time < 0 ? hist_bins(R.dbits) : 0}, st);
+  if (ITEMS != kItemsSmall || ntiles > kSelfScanTiles)
+    col_scan(sc.hist, ntiles, sc.part,
+             PassBins{R.plan, R.time, R.time < 0 ? hist_bins(R.dbits) : 0}, st);
   TimedLaunch tl("k_radix_scatter", st);
   constexpr bool kVertex = KIND == RP_VERTEX || KIND == RP_INCOLS;
   if (kVertex && emit)
@@ -952,13 +991,15 @@ static int radix_sort(uint4* k0, uint4* k1, int64_t m, int bits, const SortScrat
 // The time sort: kTimePasses launched passes planned on the device (see
 // BuildPlan).  It reads the edge columns and leaves the time-ordered records
 // re-keyed by xf1 in b0.  Its first pass takes its digit counts from the
-// validation (k_fold_hist).
+// validation (k_start, which also clears `cap` slots of the run table).
 static bool time_sort(const BuildPlan* plan, const EdgeCols& ec, uint4* b0, uint4* b1, int64_t m,
-                      const uint32_t* low, const SortScratch& sc, hipStream_t st, int xf1) {
+                      const uint32_t* low, const SortScratch& sc, hipStream_t st, int xf1,
+                      uint4* tab, int64_t cap) {
   const int64_t ntiles = sort_tiles(m);
   if (sc.part_elems < col_scan_scratch_elems(ntiles, kMaxBins)) return false;
-  hipLaunchKernelGGL(k_rec_init, dim3(blocks_for(m, 256) < 2048 ? blocks_for(m, 256) : 2048),
-                     dim3(256), 0, st, ec, m, plan, b0, xf1);
+  const int64_t sb = cap > 0 && ntiles < 256 ? 256 : ntiles;
+  hipLaunchKernelGGL(k_start, dim3((unsigned)(sb < 2048 ? sb : 2048)), dim3(kSortBlock), 0, st,
+                     low, sc.hist, ntiles, ec, m, plan, b0, xf1, tab, cap);
   for (int p = 0; p < kTimePasses; ++p) {
     RecPass R{};
     R.plan = plan;
@@ -973,14 +1014,10 @@ static bool time_sort(const BuildPlan* plan, const EdgeCols& ec, uint4* b0, uint
     // microseconds
     const int64_t hb = ((ntiles + 63) / 64) * 8;
     const unsigned grid = (unsigned)(p >= 3 && hb < ntiles ? hb : ntiles);
-    // pass 0 takes its counts from the validation's (k_fold_hist)
-    if (p == 0) {
-      hipLaunchKernelGGL(k_fold_hist, dim3((unsigned)(ntiles < 2048 ? ntiles : 2048)),
-                         dim3(kSortBlock), 0, st, low, sc.hist, ntiles, plan);
+    if (p == 0)
       radix_pass<RP_COLS>(R, false, false, m, grid, sc, st);
-    } else {
+    else
       radix_pass<RP_TIME>(R, true, false, m, grid, sc, st);
-    }
   }
   return true;
 }
@@ -1326,15 +1363,21 @@ __global__ __launch_bounds__(256) void k_emit(const uint4* __restrict__ in, int6
   }
 }
 
-// CSR offsets from a sorted key column: off[v] = first position whose key is
-// at least v, for v in [0, n].  Each thread takes kOffItems consecutive
-// positions (two 16-byte loads where the column allows), so the launch has
-// an eighth of the blocks a thread per position would need.
+// CSR offsets of both orders from their sorted key columns (blockIdx.y):
+// off[v] = first position whose key is at least v, for v in [0, n].  Each
+// thread takes kOffItems consecutive positions (two 16-byte loads where the
+// column allows), so the launch has an eighth of the blocks a thread per
+// position would need.
 constexpr int kOffItems = 8;
-__global__ __launch_bounds__(256) void k_offsets(const int32_t* __restrict__ key, int64_t m,
-                                                 const BuildPlan* __restrict__ plan, int32_t n,
-                                                 uint32_t* __restrict__ off) {
+struct OffCols {
+  const int32_t* key[2];
+  uint32_t* off[2];
+};
+__global__ __launch_bounds__(256) void k_offsets(OffCols C, int64_t m,
+                                                 const BuildPlan* __restrict__ plan, int32_t n) {
   if (plan->bad) return;
+  const int32_t* __restrict__ key = C.key[blockIdx.y];
+  uint32_t* __restrict__ off = C.off[blockIdx.y];
   const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * kOffItems;
   if (i0 > m) return;
   int32_t k[kOffItems];
@@ -1363,7 +1406,7 @@ static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct GraphLayout {
   size_t out_off, in_off, out_src, out_dst, out_eid, out_t, in_src, in_eid, in_dst, in_t,
-      pair_dst, out_rec, in_rec, pair_eid, pair_t, pair_hash, pair_skip, status, tminmax, trange,
+      pair_dst, out_rec, in_rec, pair_eid, pair_t, pair_hash, pair_skip, status, found, trange,
       plan, low, hist, part, part_elems, spill_count,
       rr[4], total;
 };
@@ -1397,7 +1440,7 @@ static GraphLayout graph_layout(int32_t n, int64_t m) {
   L.pair_skip =
       take((size_t)(skip_level_len(m, 1) + skip_level_len(m, 2) + skip_level_len(m, 3)) * 8);
   L.status = take(16);
-  L.tminmax = take(16);
+  L.found = take(kMaxFound * sizeof(Found));
   L.trange = take(16);
   L.plan = take(sizeof(BuildPlan));
   // sort scratch: four 16-byte-record buffers
@@ -1420,13 +1463,6 @@ static GraphLayout graph_layout(int32_t n, int64_t m) {
 size_t graph_workspace_bytes(int32_t n, int64_t m) { return graph_layout(n, m).total; }
 
 static int bitlen(uint64_t x) { return x ? 64 - __builtin_clzll(x) : 0; }
-
-// The pair-run table from the pair index's sorted src keys.
-static void clear_pair_hash(const tc_graph* g, hipStream_t st) {
-  const int64_t cap = (int64_t)1 << g->pair_hash_log2;
-  hipLaunchKernelGGL(k_hash_clear, dim3(blocks_for(cap, 256)), dim3(256), 0, st,
-                     (PairSlot*)g->pair_hash, cap);
-}
 
 tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* dst,
                       const int64_t* t, void* ws, size_t ws_bytes, hipStream_t st, tc_graph* g) {
@@ -1455,7 +1491,7 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
   g->pair_skip = (int64_t*)(base + L.pair_skip);
   g->out_rec = (void*)(base + L.out_rec);
   g->in_rec = (void*)(base + L.in_rec);
-  uint64_t* tminmax = (uint64_t*)(base + L.tminmax);
+  Found* found = (Found*)(base + L.found);
   BuildPlan* plan = (BuildPlan*)(base + L.plan);
   uint32_t* low = (uint32_t*)(base + L.low);
   uint32_t* hist = (uint32_t*)(base + L.hist);
@@ -1464,19 +1500,19 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
 
   const int vbits = bitlen((uint64_t)(n - 1));
   // validation and the sort plan, on the device
-  hipLaunchKernelGGL(k_init_build, dim3(1), dim3(64), 0, st, g->status, tminmax,
-                     spill_count);
-  if (m > 0) {
-    const int64_t ntiles = sort_tiles(m);
+  const int64_t ntiles = sort_tiles(m);
+  const int nfound = (int)(ntiles < kMaxFound ? ntiles : kMaxFound);
+  if (m > 0)
     hipLaunchKernelGGL(large_tiles(m) ? k_validate<kItemsLarge> : k_validate<kItemsSmall>,
-                       dim3((unsigned)(ntiles < 1024 ? ntiles : 1024)), dim3(kSortBlock), 0, st,
-                       src, dst, t, m, n, g->status, tminmax, low);
-  }
-  hipLaunchKernelGGL(k_plan, dim3(1), dim3(64), 0, st, (const uint32_t*)g->status,
-                     (const uint64_t*)tminmax, m, vbits, plan, g->t_range);
+                       dim3((unsigned)nfound), dim3(kSortBlock), 0, st, src, dst, t, m, n, found,
+                       low);
+  hipLaunchKernelGGL(k_plan, dim3(1), dim3(kMaxFound), 0, st, (const Found*)found, nfound, m,
+                     vbits, plan, g->status, g->t_range, spill_count);
   const int lg = g->pair_hash_log2, glog2 = group_log2(lg);
-  if (m == 0 || glog2 == 0) clear_pair_hash(g, st);
+  const int64_t cap = (int64_t)1 << lg;
   if (m == 0) {
+    hipLaunchKernelGGL(k_hash_clear, dim3(blocks_for(cap, 256)), dim3(256), 0, st,
+                       (PairSlot*)g->pair_hash, cap);
     hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for((int64_t)n + 1, 256)), dim3(256), 0, st,
                        g->out_off, (int64_t)n + 1, 0u);
     hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for((int64_t)n + 1, 256)), dim3(256), 0, st,
@@ -1489,7 +1525,8 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
   // 1. time order, ending in rr[0] re-keyed as the out-CSR input
   const EdgeCols ec{src, dst, t};
   const SortScratch sc{hist, part, L.part_elems, vbits};
-  if (!time_sort(plan, ec, rr[0], rr[1], m, (const uint32_t*)low, sc, st, RX_OUT))
+  if (!time_sort(plan, ec, rr[0], rr[1], m, (const uint32_t*)low, sc, st, RX_OUT,
+                 (uint4*)g->pair_hash, glog2 == 0 ? cap : 0))
     return TC_E_WORKSPACE;
   // A vertex sort of rr[from] (spare rr[tmp]) whose last pass writes the
   // columns E; with no pass (n = 1) the records are emitted from rr[from].
@@ -1507,10 +1544,6 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
       hipLaunchKernelGGL(k_emit, dim3(blocks_for(m + 1, 256)), dim3(256), 0, st,
                          (const uint4*)rr[from], m, (const BuildPlan*)plan, t, E.key,
                          E.other, E.t, E.eid, E.rec, n, vbits, off, E.skip);
-    else if (off)
-      hipLaunchKernelGGL(k_offsets, dim3(blocks_for((m + kOffItems) / kOffItems, 256)),
-                         dim3(256), 0, st, (const int32_t*)E.key, m, (const BuildPlan*)plan, n,
-                         off);
     return true;
   };
   // 2. in-CSR: the time order read from rr[0] with src and dst swapped
@@ -1579,6 +1612,11 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
                           (uint4*)g->out_rec, nullptr},
                  g->out_off, -1, RX_NONE, -1, RX_NONE, nullptr, one ? nullptr : low))
     return TC_E_WORKSPACE;
+  if (!one)
+    hipLaunchKernelGGL(k_offsets, dim3(blocks_for((m + kOffItems) / kOffItems, 256), 2),
+                       dim3(256), 0, st,
+                       OffCols{{g->in_dst, g->out_src}, {g->in_off, g->out_off}}, m,
+                       (const BuildPlan*)plan, n);
   if (hipGetLastError() != hipSuccess) return TC_E_HIP;
   return TC_OK;
 }

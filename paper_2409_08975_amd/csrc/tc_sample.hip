@@ -80,6 +80,7 @@ struct DeltaArgs {
   uint32_t* P;
   double* m2;
   uint64_t* xmax;
+  double* est;
 };
 
 struct SampleArgs {
@@ -275,6 +276,7 @@ __device__ __forceinline__ double square_term(uint64_t X, uint32_t hp) {
 // serialise on the same few words in L2; k_finalize reduces the copies in
 // a fixed order.
 constexpr int kSpread = 64;
+constexpr int kCounters = 8;
 struct SpreadSums {
   uint64_t lo, hi, hits, xmax;
   double m2;
@@ -1551,7 +1553,8 @@ __global__ __launch_bounds__(kSBlock) void k_listcount_big(SampleArgs A) {
   sums_flush<kSWaves>(A);
 }
 
-__global__ void k_zero_result(SampleArgs A) {
+// the totals, the outputs and the first chunk's queue counters, in one launch
+__global__ void k_begin(SampleArgs A) {
   const int nm = A.plan.n_motifs;
   for (int i = threadIdx.x; i < kSpread * A.nd * nm; i += blockDim.x)
     A.spread[i] = SpreadSums{0, 0, 0, 0, 0.0};
@@ -1564,28 +1567,20 @@ __global__ void k_zero_result(SampleArgs A) {
     if (A.D[d].xmax) A.D[d].xmax[j] = 0;
   }
   if ((int)threadIdx.x < A.nd) *A.D[threadIdx.x].status = 0;
+  if (threadIdx.x < kCounters) A.item_count[threadIdx.x] = 0;
 }
 
-// estimate output pointers of the deltas, passed by value
-struct EstPtrs {
-  double* p[kMaxDeltas];
-};
-
-__global__ void k_store_ptrs(EstPtrs ep, double** dst) {
-  if (threadIdx.x < kMaxDeltas) dst[threadIdx.x] = ep.p[threadIdx.x];
-}
-
+// item_count, (spare), wide_count, wide_next, big_count, mid_count,
+// w128_count, w128_next
 __global__ void k_zero_counters(uint32_t* p) {
-  // item_count, (spare), wide_count, wide_next, big_count, mid_count,
-  // w128_count, w128_next
-  if (threadIdx.x < 8) p[threadIdx.x] = 0;
+  if (threadIdx.x < kCounters) p[threadIdx.x] = 0;
 }
 
 // C_hat = (cnt / k) * W, each integer rounded to nearest-even binary64; with
 // a proposal, C_hat = ((cnt * 2^-64) / k) * Q
 // One wavefront per (delta, motif): lane s holds copy s of the totals, and
 // fixed-order wavefront sums give cnt (128-bit, with overflow), hits and m2.
-__global__ __launch_bounds__(1024) void k_finalize(SampleArgs A, double* const* est) {
+__global__ __launch_bounds__(1024) void k_finalize(SampleArgs A) {
   const int nm = A.plan.n_motifs;
   const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
   static_assert(kSpread == kWave, "one lane per copy of the totals");
@@ -1615,7 +1610,7 @@ __global__ __launch_bounds__(1024) void k_finalize(SampleArgs A, double* const* 
       double c = u128_to_double(c128.lo, c128.hi);
       if (A.D[d].is) c = ldexp(c, -64);
       // exhaustive mode: the count itself
-      est[d][j] = A.exhaustive ? c
+      A.D[d].est[j] = A.exhaustive ? c
                                : ((W == 0) ? 0.0 : __dmul_rn(__ddiv_rn(c, (double)A.k), (double)W));
     }
   }
@@ -1656,7 +1651,7 @@ static int wide_blocks_for(const SampleTuning& t) {
 }
 
 struct SampleLayout {
-  size_t win_lo, win_len, code, mid, wide, big, w128, counters, fast_p, wide_p, est_ptrs, samp_h,
+  size_t win_lo, win_len, code, mid, wide, big, w128, counters, fast_p, wide_p, samp_h,
       spread, total;
   uint64_t chunk, cap;
   int fast_waves, wide_blocks;
@@ -1684,7 +1679,6 @@ static SampleLayout sample_layout(uint64_t k, int nd, int32_t n_motifs, const Sa
   L.counters = take(32);
   L.fast_p = take((size_t)L.fast_waves * 2 * (kKeyCap + 1) * 8);
   L.wide_p = take((size_t)L.wide_blocks * 2 * (kWideCap + 1) * 8);
-  L.est_ptrs = take(kMaxDeltas * sizeof(double*));
   L.samp_h = take((size_t)nd * L.chunk * 4);
   L.spread = take((size_t)kSpread * nd * n_motifs * sizeof(SpreadSums));
   L.total = o;
@@ -1734,7 +1728,6 @@ tc_status sample_batch(const tc_graph* g, const tc_weights* const* w, int nd,
     }
   }
   A.nd = nd;
-  double* est_host[kMaxDeltas] = {};
   for (int d = 0; d < kMaxDeltas; ++d) {
     DeltaArgs& D = A.D[d];
     D = DeltaArgs{};
@@ -1760,7 +1753,7 @@ tc_status sample_batch(const tc_graph* g, const tc_weights* const* w, int nd,
     D.P = out[d]->P;
     D.m2 = out[d]->m2;
     D.xmax = out[d]->xmax;
-    est_host[d] = out[d]->estimate;
+    D.est = out[d]->estimate;
   }
   A.k = k;
   A.seed = seed;
@@ -1789,13 +1782,10 @@ tc_status sample_batch(const tc_graph* g, const tc_weights* const* w, int nd,
   A.plan = plan;
   A.lds_cap = (uint32_t)(tune.lds_list_cap < kWave ? kWave
                          : (tune.lds_list_cap > kKeyCap ? kKeyCap : tune.lds_list_cap));
-  // the estimate pointers go to the device through a small kernel argument
-  // copy, so the call stays capturable (no host-to-device memcpy)
-  EstPtrs ep;
-  for (int d = 0; d < kMaxDeltas; ++d) ep.p[d] = est_host[d];
-  double** est_dev = (double**)(base + L.est_ptrs);
-  hipLaunchKernelGGL(k_store_ptrs, dim3(1), dim3(kMaxDeltas), 0, st, ep, est_dev);
-  hipLaunchKernelGGL(k_zero_result, dim3(1), dim3(1024), 0, st, A);
+  A.c0 = 0;
+  A.clen = 0;
+  A.tiles_per_delta = 0;
+  hipLaunchKernelGGL(k_begin, dim3(1), dim3(1024), 0, st, A);
   const int nm = plan.n_motifs;
   const unsigned reg_waves = (unsigned)(tune.reg_waves < 64 ? 64 : tune.reg_waves);
   for (uint64_t c0 = 0; c0 < k; c0 += L.chunk) {
@@ -1806,7 +1796,7 @@ tc_status sample_batch(const tc_graph* g, const tc_weights* const* w, int nd,
     const unsigned pblocks =
         (unsigned)((tune.path_blocks > 0 && (uint32_t)tune.path_blocks < units) ? tune.path_blocks
                                                                                 : units);
-    hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, st, A.item_count);
+    if (c0 > 0) hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, st, A.item_count);
     {
       TimedLaunch tl("k_paths", st);
       // the compile-time form needs the class <-,+,<,>>, anchor edges in path
@@ -1861,7 +1851,7 @@ tc_status sample_batch(const tc_graph* g, const tc_weights* const* w, int nd,
       }
     }
   }
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, st, A, (double* const*)est_dev);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, st, A);
   if (hipGetLastError() != hipSuccess) return TC_E_HIP;
   return TC_OK;
 }

@@ -64,9 +64,10 @@ __device__ __forceinline__ bool before(int32_t dv, int64_t dt, int32_t qv, int64
 // others bisect only between the splits of their two coarse neighbours (the
 // split grows with the diagonal), a window of at most kSplitStride tiles
 // whose probes stay in L2, where a full bisection reads a fresh line per
-// probe.
+// probe.  Up to kSplitDirect diagonals (2*10^6 edges, whose columns stay in
+// the last-level cache) the first launch takes every diagonal.
 constexpr int kMaxJobs = 2;
-constexpr int64_t kSplitStride = 32;
+constexpr int64_t kSplitStride = 32, kSplitDirect = 2048;
 struct SplitJob {
   KeyCols Q, D;
   uint32_t* split;
@@ -93,14 +94,14 @@ __device__ __forceinline__ uint32_t split_search(const SplitJob& S, int64_t d, i
   return (uint32_t)lo;
 }
 
-// coarse: thread c takes diagonal index c * kSplitStride (or the last one)
+// coarse: thread c takes diagonal index c * stride (or the last one)
 __global__ __launch_bounds__(256) void k_mp_split_coarse(SplitJobs J, int64_t nq, int64_t nd,
-                                                         int64_t nsplit) {
+                                                         int64_t nsplit, int64_t stride) {
   const SplitJob& S = J.j[blockIdx.y];
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t ncoarse = (nsplit - 1 + kSplitStride - 1) / kSplitStride + 1;
+  const int64_t ncoarse = (nsplit - 1 + stride - 1) / stride + 1;
   if (c >= ncoarse) return;
-  const int64_t b = c * kSplitStride < nsplit - 1 ? c * kSplitStride : nsplit - 1;
+  const int64_t b = c * stride < nsplit - 1 ? c * stride : nsplit - 1;
   const int64_t d = b * kMPTile < nq + nd ? b * kMPTile : nq + nd;
   const int64_t lo = d - nd > 0 ? d - nd : 0;
   const int64_t hi = d < nq ? d : nq;
@@ -654,6 +655,8 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(const uint64_t* __restrict_
 
 // the tile scans of every weights set of a call, one block each
 struct ScanSets {
+  const uint32_t* a[kMaxDeltas];
+  const uint32_t* b[kMaxDeltas];
   const uint64_t* tile_sums[kMaxDeltas];
   uint64_t* tile_off[kMaxDeltas];
   uint64_t* S[kMaxDeltas];
@@ -696,11 +699,11 @@ __global__ __launch_bounds__(kWBlock) void k_qtile_sums(const uint32_t* __restri
 // per tile: w = a * b (times h for the proposal), block-wide exclusive scan,
 // plus the tile offset -> S[p]
 template <bool H>
-__global__ __launch_bounds__(kWBlock) void k_scan_apply(const uint32_t* __restrict__ a,
-                                                      const uint32_t* __restrict__ b,
-                                                      const uint32_t* __restrict__ h, int64_t m,
-                                                      const uint64_t* __restrict__ tile_off,
-                                                      uint64_t* __restrict__ S, TreeOut T) {
+__device__ __forceinline__ void scan_apply(const uint32_t* __restrict__ a,
+                                           const uint32_t* __restrict__ b,
+                                           const uint32_t* __restrict__ h, int64_t m,
+                                           uint64_t tile_off, uint64_t* __restrict__ S,
+                                           const TreeOut& T) {
   __shared__ uint64_t s_w[kWBlock / kWave];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t p0 = (int64_t)blockIdx.x * kWTile + (int64_t)threadIdx.x * kWItems;
@@ -738,7 +741,7 @@ __global__ __launch_bounds__(kWBlock) void k_scan_apply(const uint32_t* __restri
   const uint64_t inc = wave_inclusive_scan(s);
   if (lane == 63) s_w[wave] = inc;
   __syncthreads();
-  uint64_t run = tile_off[blockIdx.x] + inc - s;
+  uint64_t run = tile_off + inc - s;
   for (int q = 0; q < wave; ++q) run += s_w[q];
   if (p0 + kWItems <= m) {
     uint64_t out[kWItems];
@@ -761,6 +764,167 @@ __global__ __launch_bounds__(kWBlock) void k_scan_apply(const uint32_t* __restri
       run += w[j];
     }
   }
+}
+
+template <bool H>
+__global__ __launch_bounds__(kWBlock) void k_scan_apply(const uint32_t* __restrict__ a,
+                                                      const uint32_t* __restrict__ b,
+                                                      const uint32_t* __restrict__ h, int64_t m,
+                                                      const uint64_t* __restrict__ tile_off,
+                                                      uint64_t* __restrict__ S, TreeOut T) {
+  scan_apply<H>(a, b, h, m, tile_off[blockIdx.x], S, T);
+}
+
+// the scans of every weights set of a call (blockIdx.y)
+__global__ __launch_bounds__(kWBlock) void k_scan_apply_sets(ScanSets J, int64_t m) {
+  const int i = blockIdx.y;
+  scan_apply<false>(J.a[i], J.b[i], nullptr, m, J.tile_off[i][blockIdx.x], J.S[i], J.T[i]);
+}
+
+// ---- small graphs ------------------------------------------------------------
+// Below kDirectEdges the merge passes above are launches of a few blocks whose
+// time is their chains of dependent reads, side 3 waits for side 1, and its
+// records for their gather.  One thread per scan position then searches its
+// own windows in the two vertices' lists, whose bounds the offset arrays give
+// (both sides and both ends side by side), and the scan's blocks add up the
+// tile sums before them instead of waiting for a scan of them: two launches
+// instead of seven.  One delta: 131,071 edges 48.8 -> 18.5 us, 262,143 63.6 ->
+// 26.9, 524,287 73.6 -> 49.6, but 1,000,001 94 -> 103 (every search then
+// leaves the XCD's L2), so the line lies between the last two; four deltas
+// cross at the same size (158 -> 111, 205 -> 246).
+constexpr int64_t kDirectEdges = 3 << 18;
+constexpr int kDirectBlock = 256;
+constexpr int kDirectPerTile = kWTile / kDirectBlock;
+constexpr int kDirectTiles = (int)(kDirectEdges / kDirectBlock);
+constexpr int kDirectSums = kDirectTiles / kWBlock;  // position sums per thread of the scan
+
+// the lists a side draws from: its CSR's offsets and times, and whose
+struct SideList {
+  const uint32_t* off;
+  const int64_t* t;
+  int32_t on;          // 0: no edge on this side
+  int32_t before, fu;  // window before the centre time; F counts "<="
+};
+struct DirectArgs {
+  const int32_t* src;
+  const int32_t* dst;
+  const int64_t* t;
+  SideList side[2];
+  int nd;
+  int64_t delta[kMaxDeltas];
+  uint32_t* lo[2][kMaxDeltas];
+  uint32_t* len[2][kMaxDeltas];
+  uint4* prec[kMaxDeltas];
+  uint64_t* sums[kMaxDeltas];  // 128-bit sums of a * b per kDirectBlock positions
+};
+
+// first position in [lo, hi) whose time is past the key: t > key when UP,
+// t >= key otherwise
+__device__ __forceinline__ uint32_t time_bound(const int64_t* __restrict__ t, uint32_t lo,
+                                               uint32_t hi, int64_t key, bool up) {
+  return up ? upper_bound<int64_t>(t, lo, hi, key) : lower_bound<int64_t>(t, lo, hi, key);
+}
+
+__global__ __launch_bounds__(kDirectBlock) void k_windows_direct(
+    DirectArgs A, int64_t m, const uint32_t* __restrict__ gstatus) {
+  if (*gstatus) return;  // a rejected graph: its arrays are not sorted
+  __shared__ U128 s_w[kDirectBlock / kWave];
+  const int64_t p = (int64_t)blockIdx.x * kDirectBlock + threadIdx.x;
+  const bool in = p < m;
+  int32_t u = 0, v = 0;
+  int64_t t = 0;
+  uint32_t l0[2] = {0, 0}, l1[2] = {0, 0}, F[2] = {0, 0};
+  if (in) {
+    u = A.src[p];
+    v = A.dst[p];
+    t = A.t[p];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (A.side[q].on) {
+        const int32_t w = q == 0 ? u : v;
+        l0[q] = A.side[q].off[w];
+        l1[q] = A.side[q].off[w + 1];
+      }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (A.side[q].on) F[q] = time_bound(A.side[q].t, l0[q], l1[q], t, A.side[q].fu != 0);
+  }
+  for (int k = 0; k < A.nd; ++k) {  // uniform
+    uint32_t lo[2] = {0, 0}, len[2] = {1, 1};
+    if (in) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (A.side[q].on) {
+          // before the centre time the window ends at F, after it begins there
+          const SideList& L = A.side[q];
+          const uint32_t R = L.before ? time_bound(L.t, l0[q], F[q], t - A.delta[k], false)
+                                      : time_bound(L.t, F[q], l1[q], t + A.delta[k], true);
+          lo[q] = L.before ? R : F[q];
+          len[q] = L.before ? F[q] - R : R - F[q];
+        }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        A.lo[q][k][p] = lo[q];
+        A.len[q][k][p] = len[q];
+      }
+      A.prec[k][2 * p] = make_uint4(lo[0], len[0], lo[1], len[1]);
+      A.prec[k][2 * p + 1] = make_uint4((uint32_t)u, (uint32_t)v, (uint32_t)t,
+                                        (uint32_t)(t >> 32));
+    }
+    const U128 s = wave_sum128(U128{in ? (uint64_t)len[0] * (uint64_t)len[1] : 0ull, 0});
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      U128 b{0, 0};
+      for (int w = 0; w < kDirectBlock / kWave; ++w) b = add128(b, s_w[w]);
+      A.sums[k][2 * blockIdx.x] = b.lo;
+      A.sums[k][2 * blockIdx.x + 1] = b.hi;
+    }
+    __syncthreads();  // the next delta reuses s_w
+  }
+}
+
+// Block (x, y): tile x of set y.  Its offset is the sum of the position sums
+// before its tile; the last block also has the total, and with it what
+// scan_tiles stores.
+__global__ __launch_bounds__(kWBlock) void k_scan_direct(ScanSets J, int64_t m,
+                                                         const uint32_t* __restrict__ upstream) {
+  static_assert(kDirectTiles % kWBlock == 0, "whole rounds of sums");
+  const int y = blockIdx.y, tid = threadIdx.x;
+  const int64_t nsum = (m + kDirectBlock - 1) / kDirectBlock;
+  const bool last = blockIdx.x + 1 == gridDim.x;
+  const bool bad = *upstream != 0;
+  __shared__ U128 s_b[kWBlock / kWave], s_a[kWBlock / kWave];
+  U128 b{0, 0}, a{0, 0};
+  const ulonglong2* sums = reinterpret_cast<const ulonglong2*>(J.tile_sums[y]);
+#pragma unroll
+  for (int r = 0; r < kDirectSums; ++r) {
+    const int i = r * kWBlock + tid;
+    if (!bad && i < nsum) {
+      const ulonglong2 v = sums[i];
+      a = add128(a, U128{v.x, v.y});
+      if (i < (int)blockIdx.x * kDirectPerTile) b = add128(b, U128{v.x, v.y});
+    }
+  }
+  b = wave_sum128(b);
+  a = wave_sum128(a);
+  if ((tid & 63) == 0) {
+    s_b[tid >> 6] = b;
+    s_a[tid >> 6] = a;
+  }
+  __syncthreads();
+  U128 off{0, 0}, W{0, 0};
+  for (int w = 0; w < kWBlock / kWave; ++w) {
+    off = add128(off, s_b[w]);
+    W = add128(W, s_a[w]);
+  }
+  if (last && tid == 0) {
+    J.S[y][m] = W.lo;  // 0 for a rejected graph
+    *J.status[y] = bad ? *upstream & (TC_F_RANGE | TC_F_OVERFLOW)
+                       : (W.hi != 0 ? TC_F_OVERFLOW : 0u);
+    if (J.T[y].tree) tree_tail(J.T[y], J.S[y], m, W.lo);
+  }
+  scan_apply<false>(J.a[y], J.b[y], nullptr, m, off.lo, J.S[y], J.T[y]);
 }
 
 // ---- 16-ary search tree over S ----------------------------------------------
@@ -824,7 +988,7 @@ static WeightsLayout weights_layout(int64_t m) {
   L.S = take((size_t)T.count[0] * 8);
   L.tree = take(T.total_words * 8);
   L.status = take(4);
-  L.tile_sums = take(ntiles * 16);
+  L.tile_sums = take((m <= kDirectEdges ? (size_t)kDirectTiles : ntiles) * 16);
   L.tile_off = take(ntiles * 8);
   L.prec = take(M * 32);
   L.total = o;
@@ -885,6 +1049,51 @@ tc_status path_weights_batch(const tc_graph* g, const int64_t* deltas, int nd,
   uint32_t* rec = (uint32_t*)((char*)ws + B.rec);
   uint32_t* split = (uint32_t*)((char*)ws + B.split);
   const uint32_t* gst = (const uint32_t*)g->status;
+  ScanSets SS{};
+  for (int i = 0; i < nd; ++i) {
+    SS.a[i] = w[i].a;
+    SS.b[i] = w[i].b;
+    SS.tile_sums[i] = tile_sums[i];
+    SS.tile_off[i] = tile_off[i];
+    SS.S[i] = w[i].S;
+    SS.status[i] = w[i].status;
+    SS.T[i] = tree_out(&w[i]);
+  }
+  if (m > 0 && m <= kDirectEdges) {
+    DirectArgs A{};
+    A.src = g->out_src;
+    A.dst = g->out_dst;
+    A.t = g->out_t;
+    A.nd = nd;
+    const int modes[2] = {cls.mode1, cls.mode3}, afters[2] = {cls.after1, cls.after3};
+    for (int q = 0; q < 2; ++q) {
+      SideList& L = A.side[q];
+      L.on = modes[q] != TC_SIDE_NONE;
+      L.off = modes[q] == TC_SIDE_IN ? g->in_off : g->out_off;
+      L.t = modes[q] == TC_SIDE_IN ? g->in_t : g->out_t;
+      L.before = (afters[q] & 1) == 0;
+      L.fu = (L.before != 0) != ((afters[q] & 2) != 0);
+    }
+    for (int i = 0; i < nd; ++i) {
+      A.delta[i] = deltas[i];
+      A.lo[0][i] = w[i].lo_in;
+      A.len[0][i] = w[i].a;
+      A.lo[1][i] = w[i].lo_out;
+      A.len[1][i] = w[i].b;
+      A.prec[i] = (uint4*)w[i].prec;
+      A.sums[i] = tile_sums[i];
+    }
+    {
+      TimedLaunch tl("k_windows", st);
+      hipLaunchKernelGGL(k_windows_direct,
+                         dim3((unsigned)((m + kDirectBlock - 1) / kDirectBlock)),
+                         dim3(kDirectBlock), 0, st, A, m, gst);
+    }
+    TimedLaunch tl("k_scan_apply", st);
+    hipLaunchKernelGGL(k_scan_direct, dim3((unsigned)ntiles, (unsigned)nd), dim3(kWBlock), 0, st,
+                       SS, m, gst);
+    return hipGetLastError() == hipSuccess ? TC_OK : TC_E_HIP;
+  }
   if (m > 0) {
     TimedLaunch tl("k_windows", st);
     const int64_t nsplit = B.nsplit;
@@ -921,10 +1130,12 @@ tc_status path_weights_batch(const tc_graph* g, const int64_t* deltas, int nd,
     if (s1) j1f = job(outk, d1, fu1);
     if (s3) j3f = job(ink, d3, fu3);
     if (nj > 0) {
-      const int64_t ncoarse = (nsplit - 1 + kSplitStride - 1) / kSplitStride + 1;
+      const int64_t stride = nsplit - 1 <= kSplitDirect ? 1 : kSplitStride;
+      const int64_t ncoarse = (nsplit - 1 + stride - 1) / stride + 1;
       hipLaunchKernelGGL(k_mp_split_coarse, dim3((unsigned)((ncoarse + 255) / 256), nj), dim3(256),
-                         0, st, J, m, m, nsplit);
-      hipLaunchKernelGGL(k_mp_split, dim3(sb, nj), dim3(256), 0, st, J, m, m, nsplit);
+                         0, st, J, m, m, nsplit, stride);
+      if (stride > 1)
+        hipLaunchKernelGGL(k_mp_split, dim3(sb, nj), dim3(256), 0, st, J, m, m, nsplit);
     }
     auto rank_mode = [&]() {
       RankMode M{};
@@ -984,23 +1195,11 @@ tc_status path_weights_batch(const tc_graph* g, const int64_t* deltas, int nd,
                        (const int32_t*)g->out_src, (const int32_t*)g->out_dst,
                        (const int64_t*)g->out_t, m, C, gst);
   }
-  ScanSets J{};
-  for (int i = 0; i < nd; ++i) {
-    J.tile_sums[i] = tile_sums[i];
-    J.tile_off[i] = tile_off[i];
-    J.S[i] = w[i].S;
-    J.status[i] = w[i].status;
-    J.T[i] = tree_out(&w[i]);
-  }
-  hipLaunchKernelGGL(k_scan_tiles_sets, dim3((unsigned)nd), dim3(1024), 0, st, J, ntiles, m, gst);
-  for (int i = 0; i < nd; ++i) {
-    const TreeOut& T = J.T[i];
-    if (ntiles > 0) {
-      TimedLaunch tl("k_scan_apply", st);
-      hipLaunchKernelGGL(k_scan_apply<false>, dim3((unsigned)ntiles), dim3(kWBlock), 0, st,
-                         (const uint32_t*)w[i].a, (const uint32_t*)w[i].b,
-                         (const uint32_t*)nullptr, m, (const uint64_t*)tile_off[i], w[i].S, T);
-    }
+  hipLaunchKernelGGL(k_scan_tiles_sets, dim3((unsigned)nd), dim3(1024), 0, st, SS, ntiles, m, gst);
+  if (ntiles > 0) {
+    TimedLaunch tl("k_scan_apply", st);
+    hipLaunchKernelGGL(k_scan_apply_sets, dim3((unsigned)ntiles, (unsigned)nd), dim3(kWBlock), 0,
+                       st, SS, m);
   }
   if (hipGetLastError() != hipSuccess) return TC_E_HIP;
   return TC_OK;

@@ -188,3 +188,42 @@ def test_pair_table_finds_every_run(tcb, torch_mod, n, m):
                                     (tab[:, 0] == -1).long()]), 0)
     on_way = empty[used] - empty[home] + torch.where(used < home, empty[-1], 0)
     assert int(on_way.abs().max()) == 0
+
+
+@pytest.mark.parametrize("m", [1, 255, 2049, 786432, 786433])
+@pytest.mark.parametrize("cls", [(1, 0, 2, 1), (2, 1, 1, 0), (0, 0, 1, 3), (2, 2, 0, 0), (1, 2, 2, 3)])
+def test_direct_windows_match_general_definition(tcb, torch_mod, m, cls):
+    """Windows, scan and total on both sides of the size where the per-edge
+    searches give way to the merge passes, for closed, open, before, after
+    and absent sides and two deltas, against ranks of composite keys."""
+    torch = torch_mod
+    n = 300
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    src = torch.randint(0, n, (m,), device="cuda", generator=gen).int()
+    dst = torch.randint(0, n, (m,), device="cuda", generator=gen).int()
+    t = torch.randint(0, max(2, m // 3), (m,), device="cuda", generator=gen)
+    G = tcb.tc_build_graph(n, src, dst, t, check=True)
+    a = {k: v.long() for k, v in G.arrays().items()}
+    T = 4 * m + 8
+    keys = {1: a["in_dst"] * T + a["in_t"] + m, 2: a["out_src"] * T + a["out_t"] + m}
+    deltas = [m // 7, 3]
+    for d, W in zip(deltas, tcb.tc_path_weights_batch(G, deltas, cls=cls)):
+        w = W.arrays()
+        prod = torch.ones(m, dtype=torch.int64, device="cuda")
+        for mode, after, v, lo, ln in ((cls[0], cls[1], a["out_src"], w["lo_in"], w["a"]),
+                                       (cls[2], cls[3], a["out_dst"], w["lo_out"], w["b"])):
+            if mode == 0:
+                assert int(lo.abs().max()) == 0 and bool((ln == 1).all())
+                continue
+            at = v * T + a["out_t"] + m
+            if after & 1:
+                first = torch.searchsorted(keys[mode], at, right=bool(after & 2))
+                end = torch.searchsorted(keys[mode], at + d, right=True)
+            else:
+                first = torch.searchsorted(keys[mode], at - d)
+                end = torch.searchsorted(keys[mode], at, right=not after & 2)
+            # an open window of delta 0 is empty: its first position is past the tie
+            assert torch.equal(lo.long(), first) and torch.equal(ln.long(), end - first)
+            prod *= ln.long()
+        S = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), torch.cumsum(prod, 0)])
+        assert torch.equal(w["S"], S) and W.status() == 0
