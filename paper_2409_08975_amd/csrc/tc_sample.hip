@@ -37,7 +37,9 @@
 //                    per-wavefront scratch.
 //   k_listcount_wide one 128-thread block per item, lists up to 65,536
 //                    entries: each level as a merge of L_{r-1} and L_r in
-//                    LDS tiles, prefix sums in per-block scratch.
+//                    LDS tiles, short lists' prefix sums in LDS and long
+//                    ones' in per-block scratch; a list longer than its
+//                    neighbours is not enumerated, theirs are placed in it.
 //   k_listcount_w128 items whose level total reached 2^64 in one of the
 //                    passes above: the merged pass in 128-bit arithmetic.
 //   k_listcount_big  lists longer than 65,536 entries: one thread per item,
@@ -46,6 +48,8 @@
 // block, so cnt is exact whatever the launch shape, the item order or the
 // tuning.
 #include <hip/hip_runtime.h>
+
+#include <limits>
 
 #include "tc_device.h"
 #include "tc_internal.h"
@@ -803,6 +807,46 @@ __device__ __forceinline__ void item_done(const SampleArgs& A, int d, int j, uin
            D.m2 ? square_term(X, hp) : 0.0, false, X);
 }
 
+// pos[e] = #{i < n : k[i] < key[e]} in a sorted LDS array, for N keys per
+// lane.  n is the same on every lane, so the halving runs on scalars and a
+// round takes three vector instructions and one LDS read per key, without a
+// divergent branch; the N reads of a round are in flight together.  k[-1] has
+// to exist (it is never read).
+template <typename K, int N>
+__device__ __forceinline__ void count_below(const K* k, uint32_t n, const K (&key)[N],
+                                            uint32_t (&pos)[N]) {
+  using Lds = const K __attribute__((address_space(3)))*;
+  const Lds k0 = (Lds)k - 1;
+  Lds p[N];  // the last entry known to be below the key
+#pragma unroll
+  for (int e = 0; e < N; ++e) p[e] = k0;
+  while (n > 0) {
+    const uint32_t half = (n + 1) >> 1;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      const Lds t = p[e] + half;
+      p[e] = *t < key[e] ? t : p[e];
+    }
+    n -= half;
+  }
+#pragma unroll
+  for (int e = 0; e < N; ++e) pos[e] = (uint32_t)(p[e] - k0);
+}
+__device__ __forceinline__ uint32_t count_below(const uint32_t* k, uint32_t n, uint32_t key) {
+  const uint32_t ky[1] = {key};
+  uint32_t pos[1];
+  count_below<uint32_t, 1>(k, n, ky, pos);
+  return pos[0];
+}
+
+// t[i] as a KEY: of a 32-bit key only the low word is read.
+template <typename KEY>
+__device__ __forceinline__ KEY raw_time(const int64_t* __restrict__ t, uint32_t i) {
+  KEY v;
+  __builtin_memcpy(&v, t + i, sizeof(KEY));
+  return v;
+}
+
 // Register-resident wavefront ListCount (64-thread blocks) for items whose
 // lists all have at most 64 * CH entries and whose window is shorter than
 // 2^32.  Keys are staged once in LDS as 32-bit offsets from the smallest
@@ -812,54 +856,99 @@ __device__ __forceinline__ void item_done(const SampleArgs& A, int d, int j, uin
 // carry across chunks gives P_r.
 // 1,024 keys (4 KB of LDS per one-wavefront block) keep the pass at the 7
 // wavefronts per SIMD its registers allow; 2,048 keys capped it at 5.
+// The pass waits on round trips: with the lists' keys loaded together (not
+// list by list), the next item's windows behind them and a level's chunks
+// searched side by side it takes 1.60 ms for 2.4e6 items of six motifs (was
+// 1.96), 0.54 for 5.4e5 (was 0.59).
 constexpr int kRegKeys = 1024;
+// lane r < n_lists: item `code`'s window of list r (else empty)
+__device__ __forceinline__ void reg_windows(const SampleArgs& A, uint32_t code, uint32_t* lo,
+                                            uint32_t* len) {
+  const int lane = threadIdx.x;
+  uint32_t li;
+  int j, d;
+  decode(code, &li, &j, &d);
+  *lo = 0;
+  *len = 0;
+  if (lane < A.plan.n_lists[j]) {
+    const uint64_t wi = win_index(A, d, A.plan.list_pair[j][lane], li);
+    *lo = A.win_lo[wi];
+    *len = A.win_len[wi];
+  }
+}
 template <int CH>
 __global__ __launch_bounds__(kWave) void k_listcount_reg(SampleArgs A) {
-  __shared__ uint32_t s_key[kRegKeys];
+  __shared__ uint32_t s_keys[1 + kRegKeys];
+  uint32_t* const s_key = s_keys + 1;
   const int lane = threadIdx.x;
   sums_clear<1>(A);
   FwdBuf fb{0u, 0u};  // items for the LDS-key pass
 
   const uint32_t n_items = *A.item_count;
-  for (uint32_t it = blockIdx.x; it < n_items; it += gridDim.x) {
-    const uint32_t code = A.item_code[it];
+  // An item's code is loaded one item ahead and its windows behind it, so
+  // that an item waits on two round trips (its first times, its keys) and not
+  // on a chain of four.
+  uint32_t code = 0, my_lo = 0, my_len = 0;
+  if (blockIdx.x < n_items) {
+    code = A.item_code[blockIdx.x];
+    reg_windows(A, code, &my_lo, &my_len);
+  }
+  uint32_t next_code = 0, next_lo = 0, next_len = 0;
+  for (uint32_t it = blockIdx.x; it < n_items;
+       it += gridDim.x, code = next_code, my_lo = next_lo, my_len = next_len) {
+    const bool more = n_items - it > gridDim.x;
+    if (more) next_code = A.item_code[it + gridDim.x];
     uint32_t li;
     int j, d;
     decode(code, &li, &j, &d);
     const int l = A.plan.n_lists[j];
-    uint32_t my_lo = 0, my_len = 0;
-    int64_t my_first = INT64_MAX;
-    if (lane < l) {
-      const uint64_t wi = win_index(A, d, A.plan.list_pair[j][lane], li);
-      my_lo = A.win_lo[wi];
-      my_len = A.win_len[wi];
-      if (my_len) my_first = A.pair_t[my_lo];
-    }
-    // longest list and smallest head time, read lane by lane as scalars
+    const int64_t my_first = my_len ? A.pair_t[my_lo] : INT64_MAX;
+    // longest list, read lane by lane as scalars
     uint32_t maxlen = 0;
-    int64_t base = INT64_MAX;
     for (int r = 0; r < l; ++r) {
       const uint32_t len_r = lane_u32(my_len, r);
-      const int64_t first_r = (int64_t)lane_u64((uint64_t)my_first, r);
       maxlen = len_r > maxlen ? len_r : maxlen;
-      base = first_r < base ? first_r : base;
     }
     // list r's keys start at my_off of lane r (exclusive prefix of the lengths)
     const uint32_t incl = scan_dpp(my_len);
     const uint32_t my_off = incl - my_len;
     const uint32_t total_keys = lane_u32(incl, kWave - 1);
+    if (more) reg_windows(A, next_code, &next_lo, &next_len);
     if (maxlen > (uint32_t)(kWave * CH) || total_keys > (uint32_t)kRegKeys ||
         A.D[d].delta >= ((int64_t)1 << 32)) {
       fwd_push(fb, code, A.mid_count, A.mid_code);
       continue;
     }
-    for (int r = 0; r < l; ++r) {
-      const uint32_t lo = lane_u32(my_lo, r), len = lane_u32(my_len, r);
-      const uint32_t off = lane_u32(my_off, r);
+    // The lists' keys one after the other: entry f of them is list entry
+    // f - off_r of the last list r with off_r <= f; 256 loads at a time are in
+    // flight.  The smallest head time is their base.
+    int64_t base = INT64_MAX;
+    for (uint32_t f0 = 0; f0 < total_keys; f0 += 4 * kWave) {
+      uint32_t at[4], raw[4];
 #pragma unroll
-      for (int h = 0; h < CH; ++h) {
-        const uint32_t i = h * kWave + lane;
-        if (i < len) s_key[off + i] = (uint32_t)(A.pair_t[lo + i] - base);
+      for (int e = 0; e < 4; ++e) at[e] = 0;
+      for (int r = 0; r < l; ++r) {
+        const uint32_t off = lane_u32(my_off, r), shift = lane_u32(my_lo, r) - off;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          at[e] = f0 + (uint32_t)(e * kWave + lane) >= off ? shift : at[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t f = f0 + (uint32_t)(e * kWave + lane);
+        raw[e] = 0;
+        if (f < total_keys) raw[e] = raw_time<uint32_t>(A.pair_t, at[e] + f);
+      }
+      if (f0 == 0) {
+        for (int r = 0; r < l; ++r) {
+          const int64_t first_r = (int64_t)lane_u64((uint64_t)my_first, r);
+          base = first_r < base ? first_r : base;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t f = f0 + (uint32_t)(e * kWave + lane);
+        if (f < total_keys) s_key[f] = raw[e] - (uint32_t)base;
       }
     }
     __threadfence_block();
@@ -881,6 +970,28 @@ __global__ __launch_bounds__(kWave) void k_listcount_reg(SampleArgs A) {
       uint64_t bound;
       const bool exact64 = !sat && !__builtin_mul_overflow((uint64_t)len, t_prev, &bound);
       uint64_t Pn[CH];
+      // the positions of all chunks, searched side by side
+      uint32_t pos[CH];
+      {
+        uint32_t key[CH];
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+          const uint32_t i = h * kWave + lane;
+          pos[h] = 0;
+          key[h] = i < len ? kcur[i] : 0u;
+        }
+        if (nch == 1)
+          pos[0] = count_below(kprev, prev_len, key[0]);
+        else if (nch == 2 && CH > 2) {
+          const uint32_t ky[2] = {key[0], key[1]};
+          uint32_t p2[2];
+          count_below<uint32_t, 2>(kprev, prev_len, ky, p2);
+          pos[0] = p2[0];
+          pos[1] = p2[1];
+        } else if (nch) {
+          count_below<uint32_t, CH>(kprev, prev_len, key, pos);
+        }
+      }
       if (exact64 && bound < (1ull << 32)) {
         // Every prefix of the previous level is at most T_{r-1} and every
         // prefix of this one at most |L_r| T_{r-1} < 2^32: the level runs in
@@ -892,9 +1003,7 @@ __global__ __launch_bounds__(kWave) void k_listcount_reg(SampleArgs A) {
           if ((uint32_t)h < nch) {  // uniform over the wavefront
             const uint32_t i = h * kWave + lane;
             const bool act = i < len;
-            uint32_t pos = 0;
-            if (act) pos = lower_bound<uint32_t>(kprev, 0u, prev_len, kcur[i]);
-            const uint32_t q = pos - 1;
+            const uint32_t q = pos[h] - 1;
             const int src = (int)(q & 63u);
             const uint32_t hsrc = q >> 6;
             uint32_t c = 0;
@@ -905,7 +1014,7 @@ __global__ __launch_bounds__(kWave) void k_listcount_reg(SampleArgs A) {
                 if (hsrc == (uint32_t)g) c = v32;
               }
             }
-            if (!act || pos == 0) c = 0;
+            if (!act || pos[h] == 0) c = 0;
             const uint32_t inc = scan_dpp(c);
             Pn[h] = (uint64_t)(carry32 + inc);
             carry32 += lane_u32(inc, kWave - 1);
@@ -924,9 +1033,7 @@ __global__ __launch_bounds__(kWave) void k_listcount_reg(SampleArgs A) {
         if ((uint32_t)h < nch) {  // uniform over the wavefront
           const uint32_t i = h * kWave + lane;
           const bool act = i < len;
-          uint32_t pos = 0;
-          if (act) pos = lower_bound<uint32_t>(kprev, 0u, prev_len, kcur[i]);
-          const uint32_t q = pos - 1;  // prefix entry pos - 1: lane q & 63 of chunk q >> 6
+          const uint32_t q = pos[h] - 1;  // prefix entry pos - 1: lane q & 63 of chunk q >> 6
           const int src = (int)(q & 63u);
           const uint32_t hsrc = q >> 6;
           uint64_t c = 0;
@@ -938,7 +1045,7 @@ __global__ __launch_bounds__(kWave) void k_listcount_reg(SampleArgs A) {
               if (hsrc == (uint32_t)g) c = ((uint64_t)hi32 << 32) | lo32;
             }
           }
-          if (!act || pos == 0) c = 0;
+          if (!act || pos[h] == 0) c = 0;
           const uint64_t inc = scan_dpp(c);
           Pn[h] = carry + inc;
           if (!exact64) total = add128(total, wave_sum128_dpp(c));
@@ -968,17 +1075,73 @@ __global__ __launch_bounds__(kWave) void k_listcount_reg(SampleArgs A) {
   sums_flush<1>(A);
 }
 
+// N chunks of 64 entries of a list from entry c0: their times (stored as the
+// level's keys), the positions in the previous keys, the prefixes there and
+// this level's.  The chunks' loads and searches run side by side: the pass
+// waits on the round trips of one chunk, not on their work.
+template <int N>
+__device__ __forceinline__ uint32_t lds_chunks(const int64_t* __restrict__ t, uint32_t c0,
+                                               uint32_t len, uint32_t kb, const uint32_t* kprev,
+                                               uint32_t* kcur, uint32_t prev_len, bool first_level,
+                                               bool prev32, bool cur32, bool exact64,
+                                               const uint64_t* Pprev, uint64_t* Pcur,
+                                               uint64_t* carry, U128* total) {
+  const int lane = threadIdx.x;
+  uint32_t key[N], pos[N];
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    const uint32_t i = c0 + (uint32_t)(e * kWave + lane);
+    key[e] = raw_time<uint32_t>(t, i < len ? i : len - 1);
+  }
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    const uint32_t i = c0 + (uint32_t)(e * kWave + lane);
+    key[e] -= kb;
+    if (i < len) kcur[i] = key[e];
+  }
+  count_below<uint32_t, N>(kprev, prev_len, key, pos);
+  uint64_t c[N];
+  if (first_level) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) c[e] = pos[e];
+  } else if (prev32) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) c[e] = reinterpret_cast<const uint32_t*>(Pprev)[pos[e]];
+  } else {
+#pragma unroll
+    for (int e = 0; e < N; ++e) c[e] = Pprev[pos[e]];
+  }
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    const uint32_t i = c0 + (uint32_t)(e * kWave + lane);
+    if (i >= len) c[e] = 0;
+    const uint64_t inc = cur32 ? (uint64_t)scan_dpp((uint32_t)c[e]) : scan_dpp(c[e]);
+    if (i < len) {
+      if (cur32)
+        reinterpret_cast<uint32_t*>(Pcur)[i + 1] = (uint32_t)(*carry + inc);
+      else
+        Pcur[i + 1] = *carry + inc;
+    }
+    if (!exact64) *total = add128(*total, wave_sum128_dpp(c[e]));
+    *carry += lane_u64(inc, kWave - 1);
+  }
+  return (uint32_t)(N * kWave);
+}
+
 // Wavefront-per-item ListCount (64-thread blocks) for lists up to kKeyCap
 // entries in a window shorter than 2^32: the keys of the previous and the
 // current list sit in LDS as 32-bit offsets from the smallest head, the
 // prefix sums in per-wavefront scratch.  Longer lists or wider windows go to
-// the merged block-per-item pass.
+// the merged block-per-item pass.  Four chunks of a list side by side, where it
+// has them, took 1.2e6 such items from 4.6 to 3.5 ms and 8.7e4 from 389 to
+// 302 us: the loads, the LDS searches and the prefix reads of a chunk are each
+// a round trip of some 2,000 cycles.
 // CAP (512 or 1,024, at least the lds_list_cap knob) sizes the key tiles:
 // at 512 a wavefront takes 4 KB of LDS and eight fit per SIMD, at 1,024
 // five.
 template <int CAP>
 __global__ __launch_bounds__(kWave) void k_listcount_lds(SampleArgs A, uint64_t* pscratch) {
-  __shared__ uint32_t s_key[2][CAP];
+  __shared__ uint32_t s_keys[1 + 2 * CAP];
   uint64_t* s_p[2] = {pscratch + (uint64_t)blockIdx.x * 2 * (kKeyCap + 1),
                       pscratch + ((uint64_t)blockIdx.x * 2 + 1) * (kKeyCap + 1)};
   const int lane = threadIdx.x;
@@ -1015,8 +1178,21 @@ __global__ __launch_bounds__(kWave) void k_listcount_lds(SampleArgs A, uint64_t*
     bool sat = false;  // a level total reached 2^64
     if (!fwd) {
       const uint32_t lo0 = lane_u32(my_lo, 0), len0 = lane_u32(my_len, 0);
-      for (uint32_t i = lane; i < len0; i += kWave)
-        s_key[0][i] = (uint32_t)(A.pair_t[lo0 + i] - base);
+      const uint32_t kb = (uint32_t)base;
+      for (uint32_t c0 = 0; c0 < len0; c0 += 4 * kWave) {
+        uint32_t raw[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t i = c0 + (uint32_t)(e * kWave + lane);
+          if (c0 + (uint32_t)(e * kWave) < len0)
+            raw[e] = raw_time<uint32_t>(A.pair_t + lo0, i < len0 ? i : len0 - 1);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t i = c0 + (uint32_t)(e * kWave + lane);
+          if (i < len0) s_keys[1 + i] = raw[e] - kb;
+        }
+      }
       __threadfence_block();
       int pb = 0;
       // Level totals: T_0 = |L_0| and T_r <= |L_r| T_{r-1}.  While that bound
@@ -1028,8 +1204,8 @@ __global__ __launch_bounds__(kWave) void k_listcount_lds(SampleArgs A, uint64_t*
         const uint32_t prev_len = lane_u32(my_len, r - 1);
         const uint32_t lo = lane_u32(my_lo, r);
         const uint32_t len = lane_u32(my_len, r);
-        const uint32_t* kprev = s_key[(r - 1) & 1];
-        uint32_t* kcur = s_key[r & 1];
+        const uint32_t* kprev = s_keys + 1 + ((r - 1) & 1) * CAP;
+        uint32_t* kcur = s_keys + 1 + (r & 1) * CAP;
         const uint64_t* Pprev = s_p[pb ^ 1];
         uint64_t* Pcur = s_p[pb];
         uint64_t bound;
@@ -1043,27 +1219,17 @@ __global__ __launch_bounds__(kWave) void k_listcount_lds(SampleArgs A, uint64_t*
           else
             Pcur[0] = 0;
         }
-        for (uint32_t c0 = 0; c0 < len; c0 += kWave) {
-          const uint32_t i = c0 + lane;
-          const bool act = i < len;
-          uint64_t c = 0;
-          if (act) {
-            const uint32_t key = (uint32_t)(A.pair_t[lo + i] - base);
-            kcur[i] = key;
-            const uint32_t pos = lower_bound<uint32_t>(kprev, 0u, prev_len, key);
-            c = (r == 1) ? (uint64_t)pos
-                         : (prev32 ? (uint64_t)reinterpret_cast<const uint32_t*>(Pprev)[pos]
-                                   : Pprev[pos]);
-          }
-          const uint64_t inc = scan_dpp(c);
-          if (act) {
-            if (cur32)
-              reinterpret_cast<uint32_t*>(Pcur)[i + 1] = (uint32_t)(carry + inc);
-            else
-              Pcur[i + 1] = carry + inc;
-          }
-          if (!exact64) total = add128(total, wave_sum128_dpp(c));
-          carry += lane_u64(inc, kWave - 1);
+        for (uint32_t c0 = 0; c0 < len;) {
+          const uint32_t left = len - c0;  // uniform
+          if (left > 2 * kWave)
+            c0 += lds_chunks<4>(A.pair_t + lo, c0, len, kb, kprev, kcur, prev_len, r == 1, prev32,
+                                cur32, exact64, Pprev, Pcur, &carry, &total);
+          else if (left > kWave)
+            c0 += lds_chunks<2>(A.pair_t + lo, c0, len, kb, kprev, kcur, prev_len, r == 1, prev32,
+                                cur32, exact64, Pprev, Pcur, &carry, &total);
+          else
+            c0 += lds_chunks<1>(A.pair_t + lo, c0, len, kb, kprev, kcur, prev_len, r == 1, prev32,
+                                cur32, exact64, Pprev, Pcur, &carry, &total);
         }
         if (exact64) {
           t_prev = carry;
@@ -1109,30 +1275,576 @@ constexpr int kWTile = kWBlock * kWPer;  // entries of B per step, of A per tile
 constexpr int kDefaultWideBlocks = 4096;
 constexpr int kMaxWideBlocks = 4096;
 
-// Seven wavefronts per SIMD (72 VGPRs): measured 7% faster than the
-// compiler's unbounded 105 VGPRs (4 per SIMD) on the batched workload.
-__global__ __launch_bounds__(kWBlock, 7) void k_listcount_wide(SampleArgs A, uint64_t* pscratch) {
-  __shared__ int64_t sA[kWTile];
-  __shared__ uint64_t sP[kWTile + 1];
-  __shared__ uint64_t s_wsum[kWWaves];
-  __shared__ uint64_t s_wlo[kWWaves], s_whi[kWWaves];
-  __shared__ uint32_t s_wset[kWWaves];
-  __shared__ uint32_t s_lo[kMaxLists], s_len[kMaxLists];
-  __shared__ uint32_t s_item, s_last_pos;
-  __shared__ int64_t s_key0;
+// The times of A staged at once: one fewer than a tile, so that their prefixes
+// (one more) are loaded four a thread too.
+constexpr uint32_t kWTileA = kWTile - 1;
+// Entries of a bridged list staged at once (32-bit keys).
+constexpr uint32_t kWBridge = 1024;
+constexpr int kWBPer = kWBridge / kWBlock;
+
+// LDS of one block: a tile of A's times (KEY offsets from the item's smallest
+// head, behind one unread entry) and of P_{r-1}.
+struct WideTile {
+  int64_t key[1 + kWTile];
+  uint64_t P[kWTile];
+  uint32_t bridge[1 + kWBridge];  // a bridged list's tile, then the weighted prefixes
+  uint64_t wsum[kWWaves], wlo[kWWaves], whi[kWWaves];
+  uint64_t bsum[2][kWWaves];
+  uint32_t wset[kWWaves];
+  uint32_t last_pos;
+  int64_t key0;
+};
+
+// How a level runs: while T_r <= |L_r| T_{r-1} stays below 2^64 the running
+// 64-bit carry is the exact level total (no 128-bit sums), and below 2^32 the
+// level's prefix sums are 32-bit words.  t: the previous level's total; sat:
+// a total reached 2^64 (the 128-bit pass takes the item).
+struct WideMode {
+  uint64_t t;
+  bool sat, exact64, cur32;
+  __device__ __forceinline__ void next(uint32_t len) {
+    uint64_t bound;
+    exact64 = !sat && !__builtin_mul_overflow((uint64_t)len, t, &bound);
+    cur32 = exact64 && bound < (1ull << 32);
+  }
+};
+
+// Entries of B a thread takes from a tile of nb: as few as cover it, so a
+// short list costs one search a thread, not four.
+__device__ __forceinline__ uint32_t wide_per(uint32_t nb) {
+  return nb <= (uint32_t)kWBlock ? 1u : nb <= 2u * kWBlock ? 2u : (uint32_t)kWPer;
+}
+// A thread's times of the tile t[0..nb), nb > 0 (lanes past it repeat the
+// last one): all loads are issued before any is waited for.
+template <typename KEY>
+__device__ __forceinline__ void wide_load(const int64_t* __restrict__ t, uint32_t nb,
+                                          KEY (&k)[kWPer]) {
+  const uint32_t per = wide_per(nb), first = threadIdx.x * per;
+#pragma unroll
+  for (int e = 0; e < kWPer; ++e)
+    if ((uint32_t)e < per) {  // uniform over the block
+      const uint32_t i = first + e;
+      k[e] = raw_time<KEY>(t, i < nb ? i : nb - 1);
+    }
+}
+
+// positions and prefix values of a thread's first N entries of B
+template <typename KEY, typename V, int N>
+__device__ __forceinline__ void wide_find(const KEY* sA, const V* sP, uint32_t na,
+                                          const KEY (&key)[kWPer], const bool (&set)[kWPer],
+                                          uint32_t (&pl)[kWPer], V (&c)[kWPer]) {
+  KEY ky[N];
+  uint32_t pos[N];
+#pragma unroll
+  for (int e = 0; e < N; ++e) ky[e] = key[e];
+  count_below<KEY, N>(sA, na, ky, pos);
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    pl[e] = pos[e];
+    c[e] = set[e] ? sP[pos[e]] : V(0);
+  }
+}
+
+// Leaves a list's times and prefixes (before + run) in LDS as the next level's
+// A; p32: as 32-bit words.  All reads of the tiles before have to be over.
+template <typename KEY, typename V>
+__device__ __forceinline__ void wide_keep(WideTile& T, bool p32, uint32_t first,
+                                          const bool (&set)[kWPer], const KEY (&key)[kWPer],
+                                          const V (&run)[kWPer], V before) {
+  KEY* const sA = reinterpret_cast<KEY*>(T.key) + 1;
+  uint32_t* const w32 = reinterpret_cast<uint32_t*>(T.P);
+#pragma unroll
+  for (int e = 0; e < kWPer; ++e)
+    if (set[e]) {
+      sA[first + e] = key[e];
+      if (p32)
+        w32[first + e + 1] = (uint32_t)(before + run[e]);
+      else
+        T.P[first + e + 1] = before + run[e];
+    }
+  if (threadIdx.x == 0) {
+    if (p32)
+      w32[0] = 0;
+    else
+      T.P[0] = 0;
+  }
+}
+
+// What one level leaves for the next.
+template <typename KEY>
+struct WideCarry {
+  KEY pk[kWPer];   // times of the next tile of B, already asked for
+  bool have;       // pk is that tile
+  bool resident;   // A's times and prefixes are in LDS
+  bool prev32;     // the prefixes (there or in scratch) are 32-bit words
+};
+
+// One level: P_r over B = L_r from P_{r-1} over A = L_{r-1}.  V is uint32_t
+// where M.cur32 holds (then every prefix and every P_{r-1} is below 2^32).
+// N is the next level's list (nN = 0: this level is the last).
+template <typename KEY, typename V>
+__device__ __forceinline__ void wide_level(WideTile& T, const int64_t* __restrict__ tA,
+                                           uint32_t nA, const int64_t* __restrict__ tB,
+                                           uint32_t nB, const int64_t* __restrict__ tN,
+                                           uint32_t nN, int64_t base, bool first_level,
+                                           const uint64_t* Pprev, uint64_t* Pcur, bool keep,
+                                           WideCarry<KEY>& C, WideMode& M) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const KEY kb = (KEY)base;
+  KEY* const sA = reinterpret_cast<KEY*>(T.key) + 1;
+  V* const sP = reinterpret_cast<V*>(T.P);
+  V* const out = reinterpret_cast<V*>(Pcur);
+  // a list of one tile stays in LDS for the whole level
+  const bool one = nA <= kWTileA;
+  bool staged = C.resident;
+  bool resident = false;  // this level's result stays in LDS
+  bool res32 = sizeof(V) == 4;
+  U128 total{0, 0};
+  uint64_t carry = 0;
+  uint32_t a0 = 0, b0 = 0;
+  while (b0 < nB) {
+    const uint32_t na = nA - a0 < kWTileA ? nA - a0 : kWTileA;
+    const uint32_t nb = nB - b0 < (uint32_t)kWTile ? nB - b0 : (uint32_t)kWTile;
+    const uint32_t per = wide_per(nb);
+    const uint32_t first = (uint32_t)tid * per;
+    if (!C.have) wide_load<KEY>(tB + b0, nb, C.pk);
+    if (!staged) {
+      KEY ra[kWPer];
+      V rp[kWPer];
+#pragma unroll
+      for (int e = 0; e < kWPer; ++e) {
+        const uint32_t i = (uint32_t)(e * kWBlock + tid);
+        if ((uint32_t)(e * kWBlock) < na) ra[e] = raw_time<KEY>(tA + a0, i < na ? i : na - 1);
+        if ((uint32_t)(e * kWBlock) <= na) {
+          const uint32_t ip = a0 + (i < na ? i : na);
+          if (first_level)
+            rp[e] = (V)ip;
+          else if (C.prev32)
+            rp[e] = (V) reinterpret_cast<const uint32_t*>(Pprev)[ip];
+          else
+            rp[e] = (V)Pprev[ip];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < kWPer; ++e) {
+        const uint32_t i = (uint32_t)(e * kWBlock + tid);
+        if (i < na) sA[i] = ra[e] - kb;
+        if (i <= na) sP[i] = rp[e];
+      }
+    }
+    KEY key[kWPer];
+#pragma unroll
+    for (int e = 0; e < kWPer; ++e)
+      key[e] = (uint32_t)e < per && first + e < nb ? (KEY)(C.pk[e] - kb)
+                                                   : std::numeric_limits<KEY>::max();
+    // the next tile of B, or the next list's first, is asked for now (64-bit
+    // keys have no registers to spare for it)
+    C.have = false;
+    staged = one;
+    if (one && sizeof(KEY) == 4) {
+      if (b0 + nb < nB) {
+        const uint32_t nx = nB - b0 - nb;
+        wide_load<KEY>(tB + b0 + nb, nx < (uint32_t)kWTile ? nx : (uint32_t)kWTile, C.pk);
+        C.have = true;
+      } else if (nN) {
+        wide_load<KEY>(tN, nN < (uint32_t)kWTile ? nN : (uint32_t)kWTile, C.pk);
+        C.have = true;
+      }
+    }
+    __syncthreads();
+    // settled entries: in the tile of B and at most A's last staged time
+    const bool a_ends = a0 + na == nA;
+    const KEY a_last = a_ends ? std::numeric_limits<KEY>::max() : sA[na - 1];
+    V c[kWPer] = {0, 0, 0, 0};
+    uint32_t pl[kWPer] = {0, 0, 0, 0};
+    bool set[kWPer];
+#pragma unroll
+    for (int e = 0; e < kWPer; ++e)
+      set[e] = (uint32_t)e < per && first + e < nb && key[e] <= a_last;
+    if (per == 1)
+      wide_find<KEY, V, 1>(sA, sP, na, key, set, pl, c);
+    else if (per == 2)
+      wide_find<KEY, V, 2>(sA, sP, na, key, set, pl, c);
+    else
+      wide_find<KEY, V, kWPer>(sA, sP, na, key, set, pl, c);
+    // inclusive prefix of this thread's counts, then across the block
+    const bool sum128 = sizeof(V) == 8 && !M.exact64;
+    U128 tsum{0, 0};
+    if (sum128) {
+#pragma unroll
+      for (int e = 0; e < kWPer; ++e) tsum = add128(tsum, U128{c[e], 0});
+    }
+    V(&run)[kWPer] = c;
+#pragma unroll
+    for (int e = 1; e < kWPer; ++e) run[e] += run[e - 1];
+    const V incl = scan_dpp(run[kWPer - 1]);
+    if (sum128) {
+      // tsum.hi <= 3 (four values below 2^64 each)
+      U128 wsum = wave_sum128_dpp(tsum.lo);
+      wsum.hi += lane_u32(scan_dpp((uint32_t)tsum.hi), kWave - 1);
+      if (lane == kWave - 1) {
+        T.wlo[wave] = wsum.lo;
+        T.whi[wave] = wsum.hi;
+      }
+    }
+    uint32_t wset = 0;
+    if (!a_ends) {
+#pragma unroll
+      for (int e = 0; e < kWPer; ++e) wset += (uint32_t)__popcll(__ballot(set[e]));
+    }
+    if (lane == kWave - 1) {
+      T.wsum[wave] = incl;
+      T.wset[wave] = wset;
+    }
+    __syncthreads();
+    V before = (V)carry + incl - run[kWPer - 1];
+    uint32_t nr = 0;
+    uint64_t blk = 0;
+#pragma unroll
+    for (int w = 0; w < kWWaves; ++w) {
+      if (w < wave) before += (V)T.wsum[w];
+      nr += T.wset[w];
+      blk += T.wsum[w];
+    }
+    nr = a_ends ? nb : uni(nr);
+    carry += uni64(blk);
+    if (sum128) {
+      U128 step{0, 0};
+#pragma unroll
+      for (int w = 0; w < kWWaves; ++w) step = add128(step, U128{T.wlo[w], T.whi[w]});
+      total = add128(total, U128{uni64(step.lo), uni64(step.hi)});
+    }
+    if (keep && one && nb == nB && nB <= kWTileA) {
+      // B was one tile and settled at once: it is the next level's A
+      resident = true;
+      WideMode N = M;
+      N.t = M.exact64 ? carry : total.hi ? ~0ull : total.lo;
+      N.sat = M.sat || (!M.exact64 && total.hi != 0);
+      N.next(nN);
+      res32 = N.cur32;
+      wide_keep<KEY, V>(T, N.cur32, first, set, key, run, before);
+      break;
+    }
+    if (keep) {
+#pragma unroll
+      for (int e = 0; e < kWPer; ++e)
+        if (set[e]) out[b0 + first + e + 1] = before + run[e];
+    }
+    b0 += nr;
+    if (one || b0 >= nB) continue;
+    // the next step's start in A: the position of the last settled entry, or
+    // past the tile and on to within one tile of the first unsettled time
+    const bool all = nr == nb;
+    const uint32_t at = all ? nb - 1 : nr;
+#pragma unroll
+    for (int e = 0; e < kWPer; ++e)
+      if ((uint32_t)e < per && first + e == at) {
+        T.last_pos = pl[e];
+        T.key0 = (int64_t)key[e];
+      }
+    __syncthreads();
+    if (all) {
+      a0 += uni(T.last_pos);
+    } else {
+      a0 += na;
+      const uint32_t rem = nA - a0;
+      if (rem > kWTileA) {
+        const KEY key0 = (KEY)uni64s(T.key0);
+        const uint32_t stride = (rem + kWBlock - 1) / kWBlock;
+        const uint64_t q = (uint64_t)a0 + (uint64_t)(tid + 1) * stride - 1;
+        const bool below = q < nA && (KEY)(raw_time<KEY>(tA, (uint32_t)q) - kb) < key0;
+        const uint32_t nb_below = (uint32_t)__syncthreads_count(below);
+        a0 += uni(nb_below) * stride;
+      }
+    }
+    __syncthreads();  // the tiles are rewritten by the next step
+  }
+  if (M.exact64) {
+    M.t = carry;
+  } else {
+    if (total.hi != 0) M.sat = true;
+    M.t = total.hi ? ~0ull : total.lo;
+  }
+  C.resident = resident;
+  C.prev32 = res32;
+  if (!resident) {
+    if (keep && tid == 0) out[0] = 0;
+    __threadfence_block();
+    __syncthreads();  // P_r complete before the next level reads it
+  }
+}
+
+// acc[e] += #{tile entries < key[e]} for a thread's first `per` keys
+__device__ __forceinline__ void bridge_count(const uint32_t* tile, uint32_t nb, uint32_t per,
+                                             const uint32_t (&key)[kWPer],
+                                             uint32_t (&acc)[kWPer]) {
+  if (per == 1) {
+    acc[0] += count_below(tile, nb, key[0]);
+  } else if (per == 2) {
+    const uint32_t ky[2] = {key[0], key[1]};
+    uint32_t pos[2];
+    count_below<uint32_t, 2>(tile, nb, ky, pos);
+    acc[0] += pos[0];
+    acc[1] += pos[1];
+  } else {
+    uint32_t pos[kWPer];
+    count_below<uint32_t, kWPer>(tile, nb, key, pos);
+#pragma unroll
+    for (int e = 0; e < kWPer; ++e) acc[e] += pos[e];
+  }
+}
+
+// A thread's exclusive prefix of v over the block, and the block's total (two
+// calls in a row use different slots).
+__device__ __forceinline__ uint64_t wide_scan(WideTile& T, int slot, uint64_t v, uint64_t* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t incl = scan_dpp(v);
+  if (lane == kWave - 1) T.bsum[slot][wave] = incl;
+  __syncthreads();
+  uint64_t before = incl - v, sum = 0;
+#pragma unroll
+  for (int w = 0; w < kWWaves; ++w) {
+    if (w < wave) before += T.bsum[slot][w];
+    sum += T.bsum[slot][w];
+  }
+  *total = uni64(sum);
+  return before;
+}
+
+// Two levels at once across a list B longer than its neighbours A (in LDS;
+// nA = 0: B is the first list) and D (nD = 0: B is the last list), both of at
+// most kWTileA entries: only their entries are placed in B, B's own are not
+// enumerated.  With v_j the chains ending at a_j, R_j = #{b <= a_j} and
+// rho(x) = #{b < x}, the chains ending in B before x are
+//   sum_{a_j < x} v_j (rho(x) - R_j) = P_A[k] rho(x) - H[k],
+// k = #{a_j < x} and H the prefix sums of v_j R_j; the terms are taken modulo
+// 2^64, and the caller has shown the results to be below.  A step is a tile of
+// B's times, loaded eight a thread while the tile before is searched.
+__device__ __forceinline__ void wide_bridge(WideTile& T, uint32_t nA,
+                                            const int64_t* __restrict__ tB, uint32_t nB,
+                                            const int64_t* __restrict__ tD, uint32_t nD,
+                                            int64_t base, uint32_t nN, bool keep,
+                                            WideCarry<uint32_t>& C, WideMode& M) {
+  const int tid = threadIdx.x;
+  const uint32_t kb = (uint32_t)base;
+  uint32_t* const sA = reinterpret_cast<uint32_t*>(T.key) + 1;
+  uint32_t* const sB = T.bridge + 1;
+  const uint32_t* const p32 = reinterpret_cast<const uint32_t*>(T.P);
+  const uint32_t perA = wide_per(nA), firstA = tid * perA;
+  const uint32_t perD = wide_per(nD), firstD = tid * perD;
+  if (nD) wide_load<uint32_t>(tD, nD, C.pk);
+  C.have = false;
+  uint32_t raw[kWBPer];
+#pragma unroll
+  for (int e = 0; e < kWBPer; ++e) {
+    const uint32_t i = (uint32_t)(e * kWBlock + tid);
+    if ((uint32_t)(e * kWBlock) < nB) raw[e] = raw_time<uint32_t>(tB, i < nB ? i : nB - 1);
+  }
+  __syncthreads();  // A is complete
+  uint32_t ka[kWPer], kd[kWPer], R[kWPer] = {0, 0, 0, 0}, rho[kWPer] = {0, 0, 0, 0};
+#pragma unroll
+  for (int e = 0; e < kWPer; ++e) {
+    // b <= a is b < a + 1 (offsets stay below 2^32 - 1); key 0 counts nothing
+    ka[e] = (uint32_t)e < perA && firstA + e < nA ? sA[firstA + e] + 1u : 0u;
+    kd[e] = (uint32_t)e < perD && firstD + e < nD ? C.pk[e] - kb : 0u;
+  }
+  for (uint32_t b0 = 0; b0 < nB; b0 += kWBridge) {
+    const uint32_t nb = nB - b0 < kWBridge ? nB - b0 : kWBridge;
+#pragma unroll
+    for (int e = 0; e < kWBPer; ++e) {
+      const uint32_t i = (uint32_t)(e * kWBlock + tid);
+      if (i < nb) sB[i] = raw[e] - kb;
+    }
+    const uint32_t b1 = b0 + nb;
+#pragma unroll
+    for (int e = 0; e < kWBPer; ++e) {
+      const uint32_t i = b1 + (uint32_t)(e * kWBlock + tid);
+      if (b1 + (uint32_t)(e * kWBlock) < nB) raw[e] = raw_time<uint32_t>(tB, i < nB ? i : nB - 1);
+    }
+    __syncthreads();
+    if (nA) bridge_count(sB, nb, perA, ka, R);
+    if (nD) bridge_count(sB, nb, perD, kd, rho);
+    __syncthreads();  // the tile is rewritten
+  }
+  uint64_t total = 0;
+  uint64_t x[kWPer] = {0, 0, 0, 0};
+  uint64_t* const sH = reinterpret_cast<uint64_t*>(T.bridge);
+  if (nA) {
+#pragma unroll
+    for (int e = 0; e < kWPer; ++e) {
+      const uint32_t i = firstA + e;
+      if ((uint32_t)e < perA && i < nA) {
+        const uint64_t v = C.prev32 ? (uint64_t)(p32[i + 1] - p32[i]) : T.P[i + 1] - T.P[i];
+        x[e] = v * (nD ? R[e] : nB - R[e]);
+      }
+      if (e) x[e] += x[e - 1];
+    }
+    const uint64_t before = wide_scan(T, 0, x[kWPer - 1], &total);
+    if (nD) {
+#pragma unroll
+      for (int e = 0; e < kWPer; ++e)
+        if ((uint32_t)e < perA && firstA + e < nA) sH[firstA + e + 1] = before + x[e];
+      if (tid == 0) sH[0] = 0;
+      __syncthreads();
+    }
+  }
+  C.resident = false;
+  if (nD) {
+    uint32_t k[kWPer] = {0, 0, 0, 0};
+    if (nA) bridge_count(sA, nA, perD, kd, k);
+    bool set[kWPer];
+#pragma unroll
+    for (int e = 0; e < kWPer; ++e) {
+      set[e] = (uint32_t)e < perD && firstD + e < nD;
+      x[e] = 0;
+      if (set[e])
+        x[e] = nA ? (C.prev32 ? (uint64_t)p32[k[e]] : T.P[k[e]]) * rho[e] - sH[k[e]]
+                  : (uint64_t)rho[e];
+      if (e) x[e] += x[e - 1];
+    }
+    const uint64_t before = wide_scan(T, 1, x[kWPer - 1], &total);
+    if (keep) {
+      WideMode N = M;
+      N.t = total;
+      N.next(nN);
+      C.resident = true;
+      C.prev32 = N.cur32;
+      wide_keep<uint32_t, uint64_t>(T, N.cur32, firstD, set, kd, x, before);
+    }
+  }
+  M.t = total;
+}
+
+// Whether list B goes by the bridge: longer than its neighbours together, so
+// that placing theirs costs less than enumerating it, and the totals of both
+// levels certain to stay below 2^64.
+__device__ __forceinline__ bool wide_bridges(const WideMode& M, uint32_t nA, uint32_t nB,
+                                             uint32_t nD) {
+  uint64_t t;
+  return nB > nA + nD && nA <= kWTileA && nD <= kWTileA && !M.sat &&
+         !__builtin_mul_overflow(M.t, (uint64_t)nB, &t) &&
+         !__builtin_mul_overflow(t, (uint64_t)(nD ? nD : 1u), &t);
+}
+
+// An item's levels; the last total is M.t unless M.sat.
+template <typename KEY>
+__device__ __forceinline__ void wide_item(WideTile& T, const int64_t* __restrict__ pair_t,
+                                          const uint32_t* s_lo, const uint32_t* s_len, int l,
+                                          int64_t base, uint64_t* P0, uint64_t* P1, WideMode& M) {
+  WideCarry<KEY> C{};
+  int r = 1;
+  uint32_t loA = uni(s_lo[0]), nA = uni(s_len[0]);
+  uint32_t loB = uni(s_lo[1]), nB = uni(s_len[1]);
+  if constexpr (sizeof(KEY) == 4) {
+    if (nB > 0 && nB <= kWTileA && nA > nB) {
+      // the first list is the longer one: list 1's entries are placed in it
+      const bool keep = l > 2;
+      M.t = 1;
+      wide_bridge(T, 0, pair_t + loA, nA, pair_t + loB, nB, base, keep ? uni(s_len[2]) : 0u, keep,
+                  C, M);
+      r = 2;
+    } else if (nA > 0 && nA <= kWTileA) {
+      // the first list into LDS with its prefixes 0, 1, 2, ...
+      M.next(nB);
+      uint32_t raw[kWPer];
+      wide_load<uint32_t>(pair_t + loA, nA, raw);
+      bool set[kWPer];
+      uint32_t key[kWPer], run[kWPer];
+      const uint32_t per = wide_per(nA), first = threadIdx.x * per;
+#pragma unroll
+      for (int e = 0; e < kWPer; ++e) {
+        set[e] = (uint32_t)e < per && first + e < nA;
+        key[e] = set[e] ? raw[e] - (uint32_t)base : 0u;
+        run[e] = (uint32_t)e + 1;
+      }
+      C.resident = true;
+      C.prev32 = M.cur32;
+      wide_keep<uint32_t, uint32_t>(T, M.cur32, first, set, key, run, first);
+    }
+  }
+  while (r < l) {
+    loA = uni(s_lo[r - 1]);
+    nA = uni(s_len[r - 1]);
+    loB = uni(s_lo[r]);
+    nB = uni(s_len[r]);
+    const bool keep = r + 1 < l;  // P_r is read by the next level
+    const uint32_t loN = keep ? uni(s_lo[r + 1]) : 0u, nN = keep ? uni(s_len[r + 1]) : 0u;
+    if constexpr (sizeof(KEY) == 4) {
+      if (C.resident && nA > 0 && (!keep || nN > 0) && wide_bridges(M, nA, nB, nN)) {
+        const bool keep2 = r + 2 < l;
+        wide_bridge(T, nA, pair_t + loB, nB, pair_t + loN, nN, base,
+                    keep2 ? uni(s_len[r + 2]) : 0u, keep2, C, M);
+        r += 2;
+        continue;
+      }
+    }
+    const uint64_t* Pprev = (r - 1) & 1 ? P1 : P0;
+    uint64_t* Pcur = r & 1 ? P1 : P0;
+    M.next(nB);
+    if (M.cur32)
+      wide_level<KEY, uint32_t>(T, pair_t + loA, nA, pair_t + loB, nB, pair_t + loN, nN, base,
+                                r == 1, Pprev, Pcur, keep, C, M);
+    else
+      wide_level<KEY, uint64_t>(T, pair_t + loA, nA, pair_t + loB, nB, pair_t + loN, nN, base,
+                                r == 1, Pprev, Pcur, keep, C, M);
+    ++r;
+  }
+}
+
+// Items are claimed by ticket: the first three quarters sixteen at a time, then
+// four and at the end one at a time.  The counter is one address for the whole
+// chip, which serves a claim in about 12 ns; one item a claim held the pass to
+// that, and the short end keeps the last blocks within one item of each other.
+struct WideDeal {
+  uint32_t n, t16, t4;  // items, tickets of 16, tickets of 4
+  __device__ __forceinline__ explicit WideDeal(uint32_t items) : n(items) {
+    t16 = n / 64 * 3;
+    t4 = (n - t16 * 16) / 16 * 3;
+  }
+  __device__ __forceinline__ void range(uint32_t t, uint32_t* lo, uint32_t* hi) const {
+    if (t < t16) {
+      *lo = t * 16;
+      *hi = *lo + 16;
+    } else if (t - t16 < t4) {
+      *lo = t16 * 16 + (t - t16) * 4;
+      *hi = *lo + 4;
+    } else {
+      const uint64_t i = (uint64_t)t16 * 16 + (uint64_t)t4 * 4 + (t - t16 - t4);
+      *lo = (uint32_t)(i < n ? i : n);
+      *hi = i < n ? *lo + 1 : n;
+    }
+  }
+};
+
+// 5.3e5 items of six motifs (mean 4,200 keys, lists to 7,200) take 8.3 ms
+// (12.6 with every list enumerated through 64-bit keys): 3,360 M vector
+// instructions fell to 2,690 M and the bytes read by half with the bridge; the
+// rest waits on LDS and memory round trips.  Five wavefronts per SIMD (96
+// VGPRs, no spill) measured 4% faster than six; blocks of 64 threads and
+// bridge tiles of 2,048 measured 10% slower.
+__global__ __launch_bounds__(kWBlock, 5) void k_listcount_wide(SampleArgs A, uint64_t* pscratch) {
+  __shared__ WideTile s_tile;
+  __shared__ uint32_t s_lo[kMaxLists], s_len[kMaxLists];
+  __shared__ int64_t s_first[kMaxLists];
+  __shared__ uint32_t s_item;
+  const int tid = threadIdx.x;
   uint64_t* Pbuf[2] = {pscratch + (uint64_t)blockIdx.x * 2 * (kWideCap + 1),
                        pscratch + ((uint64_t)blockIdx.x * 2 + 1) * (kWideCap + 1)};
   // Blocks past the item count leave at once (uniformly): the others keep
-  // claiming until the counter passes the count, so every item is taken,
-  // and an empty pass costs no contended claims.
+  // claiming until their ticket passes the last, so every item is taken, and
+  // an empty pass costs no contended claims.
   const uint32_t n_items = *A.wide_count;
   if (blockIdx.x >= n_items) return;
+  const WideDeal deal(n_items);
   sums_clear<1>(A);
-  if (tid == 0) s_item = atomicAdd(A.wide_next, 1u);
-  __syncthreads();
-  uint32_t it = uni(s_item);
-  while (it < n_items) {
+  uint32_t it = 0, it_end = 0;
+  for (;;) {
+    if (it == it_end) {
+      if (tid == 0) s_item = atomicAdd(A.wide_next, 1u);
+      __syncthreads();
+      deal.range(uni(s_item), &it, &it_end);
+      if (it == it_end) break;
+    }
     const uint32_t code = A.wide_code[it];
     uint32_t li;
     int j, d;
@@ -1140,172 +1852,38 @@ __global__ __launch_bounds__(kWBlock, 7) void k_listcount_wide(SampleArgs A, uin
     const int l = A.plan.n_lists[j];
     if (tid < l) {
       const uint64_t wi = win_index(A, d, A.plan.list_pair[j][tid], li);
-      s_lo[tid] = A.win_lo[wi];
-      s_len[tid] = A.win_len[wi];
+      const uint32_t lo = A.win_lo[wi], len = A.win_len[wi];
+      s_lo[tid] = lo;
+      s_len[tid] = len;
+      s_first[tid] = len ? A.pair_t[lo] : INT64_MAX;
     }
     __syncthreads();
     uint32_t maxlen = 0;
-    for (int r = 0; r < l; ++r) maxlen = s_len[r] > maxlen ? s_len[r] : maxlen;
+    int64_t base = INT64_MAX;
+    for (int r = 0; r < l; ++r) {
+      maxlen = s_len[r] > maxlen ? s_len[r] : maxlen;
+      base = s_first[r] < base ? s_first[r] : base;
+    }
     maxlen = uni(maxlen);
-    U128 total{0, 0};
-    bool sat = false;  // a level total reached 2^64
+    base = uni64s(base);
+    WideMode M{uni(s_len[0]), false, true, false};
     if (maxlen <= (uint32_t)kWideCap) {
-      // As in the one-wavefront pass: while T_r <= |L_r| T_{r-1} stays below
-      // 2^64 the running carry is the exact level total (no 128-bit sums),
-      // and below 2^32 the level's prefix sums are stored as 32-bit words.
-      uint64_t t_prev = uni(s_len[0]);
-      bool prev32 = false;
-      for (int r = 1; r < l; ++r) {
-        const uint32_t loA = uni(s_lo[r - 1]), nA = uni(s_len[r - 1]);
-        const uint32_t loB = uni(s_lo[r]), nB = uni(s_len[r]);
-        const uint64_t* Pprev = Pbuf[(r - 1) & 1];
-        uint64_t* Pcur = Pbuf[r & 1];
-        const uint32_t* Pprev32 = reinterpret_cast<const uint32_t*>(Pprev);
-        uint32_t* Pcur32 = reinterpret_cast<uint32_t*>(Pcur);
-        const bool keep = r + 1 < l;  // P_r is read by the next level
-        uint64_t bound;
-        const bool exact64 = !sat && !__builtin_mul_overflow((uint64_t)nB, t_prev, &bound);
-        const bool cur32 = exact64 && bound < (1ull << 32);
-        if (keep && tid == 0) {
-          if (cur32)
-            Pcur32[0] = 0u;
-          else
-            Pcur[0] = 0;
-        }
-        total = U128{0, 0};
-        uint64_t carry = 0;
-        uint32_t a0 = 0, b0 = 0;
-        while (b0 < nB) {
-          const uint32_t na = nA - a0 < (uint32_t)kWTile ? nA - a0 : (uint32_t)kWTile;
-          const uint32_t nb = nB - b0 < (uint32_t)kWTile ? nB - b0 : (uint32_t)kWTile;
-          for (uint32_t i = tid; i < na; i += kWBlock) sA[i] = A.pair_t[loA + a0 + i];
-          for (uint32_t i = tid; i <= na; i += kWBlock)
-            sP[i] = (r == 1) ? (uint64_t)(a0 + i)
-                             : (prev32 ? (uint64_t)Pprev32[a0 + i] : Pprev[a0 + i]);
-          int64_t key[kWPer];
-#pragma unroll
-          for (int e = 0; e < kWPer; ++e) {
-            const uint32_t bi = (uint32_t)(tid * kWPer + e);
-            key[e] = bi < nb ? A.pair_t[loB + b0 + bi] : INT64_MAX;
-          }
-          __syncthreads();
-          const bool a_ends = a0 + na == nA;
-          const int64_t a_last = na ? sA[na - 1] : INT64_MIN;
-          uint64_t c[kWPer];
-          uint32_t pl[kWPer];
-          uint32_t nset = 0;
-#pragma unroll
-          for (int e = 0; e < kWPer; ++e) {
-            const uint32_t bi = (uint32_t)(tid * kWPer + e);
-            const bool set = bi < nb && (a_ends || key[e] <= a_last);
-            pl[e] = set ? lower_bound<int64_t>(sA, 0u, na, key[e]) : 0u;
-            c[e] = set ? sP[pl[e]] : 0ull;
-            nset += set ? 1u : 0u;
-          }
-          // inclusive prefix of this thread's four counts, then across the block
-          uint64_t run[kWPer];
-#pragma unroll
-          for (int e = 0; e < kWPer; ++e) run[e] = (e ? run[e - 1] : 0ull) + c[e];
-          const uint64_t incl = scan_dpp(run[kWPer - 1]);
-          if (!exact64) {
-            U128 tsum{0, 0};
-#pragma unroll
-            for (int e = 0; e < kWPer; ++e) tsum = add128(tsum, U128{c[e], 0});
-            // tsum.hi <= 3 (four values below 2^64 each)
-            U128 wsum = wave_sum128_dpp(tsum.lo);
-            wsum.hi += lane_u32(scan_dpp((uint32_t)tsum.hi), kWave - 1);
-            if (lane == kWave - 1) {
-              s_wlo[wave] = wsum.lo;
-              s_whi[wave] = wsum.hi;
-            }
-          }
-          const uint32_t wset = lane_u32(scan_dpp(nset), kWave - 1);
-          if (lane == kWave - 1) {
-            s_wsum[wave] = incl;
-            s_wset[wave] = wset;
-          }
-          __syncthreads();
-          uint64_t before = carry + incl - run[kWPer - 1];
-          uint32_t nr = 0;
-#pragma unroll
-          for (int w = 0; w < kWWaves; ++w) {
-            if (w < wave) before += s_wsum[w];
-            nr += s_wset[w];
-          }
-          nr = uni(nr);
-          if (keep) {
-#pragma unroll
-            for (int e = 0; e < kWPer; ++e) {
-              const uint32_t bi = (uint32_t)(tid * kWPer + e);
-              if (bi < nr) {
-                if (cur32)
-                  Pcur32[b0 + bi + 1] = (uint32_t)(before + run[e]);
-                else
-                  Pcur[b0 + bi + 1] = before + run[e];
-              }
-            }
-          }
-          if (!exact64) {
-            U128 step{0, 0};
-#pragma unroll
-            for (int w = 0; w < kWWaves; ++w) step = add128(step, U128{s_wlo[w], s_whi[w]});
-            total = add128(total, U128{uni64(step.lo), uni64(step.hi)});
-          }
-          uint64_t blk = 0;
-#pragma unroll
-          for (int w = 0; w < kWWaves; ++w) blk += s_wsum[w];
-          carry += uni64(blk);
-          // the next step's start in A
-          if (nr == nb) {
-#pragma unroll
-            for (int e = 0; e < kWPer; ++e)
-              if ((uint32_t)(tid * kWPer + e) == nb - 1) s_last_pos = pl[e];
-          } else {
-#pragma unroll
-            for (int e = 0; e < kWPer; ++e)
-              if ((uint32_t)(tid * kWPer + e) == nr) s_key0 = key[e];
-          }
-          __syncthreads();
-          b0 += nr;
-          if (nr == nb) {
-            a0 += uni(s_last_pos);
-          } else {
-            a0 += na;
-            const uint32_t rem = nA - a0;
-            if (rem > (uint32_t)kWTile) {
-              const int64_t key0 = uni64s(s_key0);
-              const uint32_t stride = (rem + kWBlock - 1) / kWBlock;
-              const uint64_t q = (uint64_t)a0 + (uint64_t)(tid + 1) * stride - 1;
-              const bool below = q < nA && A.pair_t[loA + q] < key0;
-              const uint32_t nb_below = (uint32_t)__syncthreads_count(below);
-              a0 += uni(nb_below) * stride;
-            }
-          }
-          __syncthreads();  // the tiles are rewritten by the next step
-        }
-        if (exact64) {
-          t_prev = carry;
-        } else {
-          if (uni64(total.hi) != 0) sat = true;  // the 128-bit pass takes the item
-          t_prev = total.hi ? ~0ull : total.lo;
-        }
-        prev32 = cur32;
-        __threadfence_block();
-        __syncthreads();  // P_r complete before the next level reads it
-      }
-      total = U128{t_prev, 0};
+      // a window below 2^32 has 32-bit keys
+      if (A.D[d].delta < ((int64_t)1 << 32))
+        wide_item<uint32_t>(s_tile, A.pair_t, s_lo, s_len, l, base, Pbuf[0], Pbuf[1], M);
+      else
+        wide_item<int64_t>(s_tile, A.pair_t, s_lo, s_len, l, base, Pbuf[0], Pbuf[1], M);
     }
     if (tid == 0) {
       if (maxlen > (uint32_t)kWideCap)
         A.big_code[atomicAdd(A.big_count, 1u)] = code;
-      else if (sat)
+      else if (M.sat)
         A.w128_code[atomicAdd(A.w128_count, 1u)] = code;
       else
-        item_done(A, d, j, li, total.lo);
-      s_item = atomicAdd(A.wide_next, 1u);
+        item_done(A, d, j, li, M.t);
     }
+    ++it;
     __syncthreads();
-    it = uni(s_item);
   }
   __syncthreads();
   sums_flush<1>(A);

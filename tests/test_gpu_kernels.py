@@ -227,3 +227,35 @@ def test_direct_windows_match_general_definition(tcb, torch_mod, m, cls):
             prod *= ln.long()
         S = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), torch.cumsum(prod, 0)])
         assert torch.equal(w["S"], S) and W.status() == 0
+
+
+@pytest.mark.parametrize("n_ad,n_bd,tail,span", [
+    (511, 2000, 3, 4000),      # a bridged middle list between the longest LDS lists
+    (512, 2000, 3, 4000),      # one entry past them
+    (1024, 511, 4, 700),       # the first list is the longer one; ties
+    (1025, 64, 2, 3000),       # two lists: the first in the second's place
+    (3, 1100, 5, 50),          # many equal times, short neighbours
+    (129, 1025, 7, 10**6),     # seven lists: totals past 2^32, products past 2^64
+    (257, 2049, 2, 900),       # the last list is the longer one
+    (64, 1024, 5, 2000), (65, 128, 6, 300), (255, 256, 4, 5000),  # the shorter passes
+])
+@pytest.mark.parametrize("dplus", [0, 2**33])
+def test_chain_counts_by_list_shape(tcb, torch_mod, n_ad, n_bd, tail, span, dplus):
+    """Chain counts where the list lengths choose how a level runs: the
+    planted spine A->B->C->D, then `tail` lists alternating A->D and B->D.
+    Every sum and every per-sample count equals the oracle's, for windows with
+    32-bit keys and (dplus) with 64-bit ones."""
+    from test_gpu_parity import build_both, check_sample
+    rng = np.random.default_rng(n_ad * 7 + n_bd)
+    src = [0] * 8 + [1] + [2] * 8 + [0] * n_ad + [1] * n_bd
+    dst = [1] * 8 + [2] + [3] * 8 + [3] * (n_ad + n_bd)
+    t = list(range(1, 9)) + [10] + list(range(11, 19)) + (100 + rng.integers(0, span, size=n_ad + n_bd)).tolist()
+    g = sg.TemporalGraph(4, np.array(src, np.int32), np.array(dst, np.int32), np.array(t, np.int64))
+    G, og = build_both(tcb, torch_mod, g)
+    delta = 100 + span + dplus
+    Wt, ow = tcb.tc_path_weights(G, delta), og.weights(delta)
+    lists = [(0, 3) if r % 2 == 0 else (1, 3) for r in range(tail)]
+    spine = [(0, 1), (1, 2), (2, 3)]
+    R, E = check_sample(tcb, G, Wt, og, ow, [spine + lists, spine + lists[1:], spine + lists[:-1]], 300, seed=4,
+                        per_sample=True)
+    assert E.status == 0 and int(E.hits[0]) > 0
