@@ -259,3 +259,32 @@ def test_chain_counts_by_list_shape(tcb, torch_mod, n_ad, n_bd, tail, span, dplu
     R, E = check_sample(tcb, G, Wt, og, ow, [spine + lists, spine + lists[1:], spine + lists[:-1]], 300, seed=4,
                         per_sample=True)
     assert E.status == 0 and int(E.hits[0]) > 0
+
+
+@pytest.mark.parametrize("k", [786431, 786432, 786433, 1 << 20, 3145727, 3145728 + 77])
+@pytest.mark.parametrize("i0", [0, 2**32 - 5])
+def test_rank_ordered_samples_equal_small_chunks(tcb, torch_mod, k, i0):
+    """Chunks long enough to be put in rank order give every per-sample output
+    and every sum of 2^16-sample chunks, which are not; the sums of squares
+    agree to the rounding of k additions in another order."""
+    torch = torch_mod
+    g = sg.gen_tiny()
+    ut = torch.from_numpy
+    G = tcb.tc_build_graph(g.n, ut(g.src).cuda(), ut(g.dst).cuda(), ut(g.t).cuda())
+    Ws = tcb.tc_path_weights_batch(G, [3600, 40000])
+    motifs = [sg.MOTIFS["M4-0"], sg.MOTIFS["S5-paw"], sg.MOTIFS["M4-1"]]
+    a = tcb.tc_batch_estimate(G, Ws, motifs, k, 7, 2, i0, per_sample=True)
+    b = tcb.tc_batch_estimate(G, Ws, motifs, k, 7, 2, i0, per_sample=True,
+                              tuning=tcb.make_tuning(chunk_log2=16))
+    for x, y in zip(a, b):
+        for name in ("cnt", "hits", "estimate", "status", "e1", "e2", "e3", "X"):
+            u, v = getattr(x, name), getattr(y, name)
+            assert torch.equal(u.view(torch.uint8), v.view(torch.uint8)), name
+    h = torch.randint(1, 9, (g.m,), dtype=torch.int32, device="cuda")
+    q = tcb.tc_proposal_weights(G, Ws[1], h)
+    one = tcb.tc_sample_estimate(G, q, motifs, k, 7, 2, i0, moments=True)
+    parts = [tcb.tc_sample_estimate(G, q, motifs, min(1 << 19, k - c), 7, 2, i0 + c, moments=True)
+             for c in range(0, k, 1 << 19)]
+    assert one.counts() == [sum(c) for c in zip(*(p.counts() for p in parts))]
+    m2 = sum(p.m2.double() for p in parts)
+    assert torch.all((one.m2 - m2).abs() <= 2 * k * 2.0**-53 * m2)
