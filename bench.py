@@ -44,17 +44,21 @@ KERNEL_SRC = {"k_paths": "tc_sample.hip", "k_listcount_reg": "tc_sample.hip",
               "k_windows": "tc_weights.hip", "k_scan_apply": "tc_weights.hip",
               "k_radix_scatter": "tc_build.hip"}
 # the kernels each timed span covers, for counter-based traffic per span
-SPAN_KERNELS = {"k_windows": ["k_mp_split_coarse", "k_mp_split", "k_mp_rank", "k_combine"]}
+SPAN_KERNELS = {"k_windows": ["k_mp_split_coarse", "k_mp_split", "k_mp_rank", "k_combine",
+                              "k_windows_direct"],
+                "k_scan_apply": ["k_scan_apply_sets", "k_scan_direct"]}
 PMC_FILES = {"bitcoin": os.path.join(ROOT, "profiles", "pmc_traffic_bitcoin.txt"),
              "medium": os.path.join(ROOT, "profiles", "pmc_traffic_medium.txt")}
 # stages of a step -> kernels whose counter traffic makes up the stage
 STAGE_KERNELS = {
-    "build": ["k_init_build", "k_validate", "k_plan", "k_trange", "k_fold_hist", "k_hash_clear",
-              "k_rec_init", "k_radix_hist", "k_col_sum", "k_col_scan", "k_col_apply", "k_radix_scatter",
-              "k_rec_xform", "k_emit", "k_offsets", "k_hash_insert"],
+    "build": ["k_start", "k_validate", "k_plan", "k_hash_clear", "k_fill_u32", "k_radix_hist",
+              "k_radix_hist2", "k_col_one", "k_col_sum", "k_col_scan", "k_col_apply", "k_radix_scatter",
+              "k_rec_xform", "k_emit", "k_offsets", "k_hash_insert", "k_run_hist", "k_run_scatter",
+              "k_table_segment", "k_table_spill"],
     "weights": ["k_mp_split_coarse", "k_mp_split", "k_mp_rank", "k_combine", "k_scan_tiles",
-                "k_scan_tiles_sets", "k_scan_apply"],
-    "sample": ["k_zero_result", "k_store_ptrs", "k_zero_counters", "k_paths", "k_listcount_reg",
+                "k_scan_tiles_sets", "k_scan_apply", "k_scan_apply_sets", "k_windows_direct",
+                "k_scan_direct"],
+    "sample": ["k_begin", "k_zero_counters", "k_deal_count", "k_deal_place", "k_paths", "k_listcount_reg",
                "k_listcount_lds", "k_listcount_wide", "k_listcount_w128", "k_listcount_big", "k_finalize"],
 }
 
@@ -100,7 +104,8 @@ def kernel_alg_bytes(kernel, m, units, nd=1):
       k_windows        per edge of a call over nd deltas: read the (vertex,
                        time) keys of both CSRs once (24 B), and per delta write
                        lo_in, a, lo_out, b (16 B) and the 32-byte path record
-      k_scan_apply     per edge: read a, b (8 B), write S (8 B)
+      k_scan_apply     per edge of a call over nd deltas: per delta read a, b
+                       (8 B), write S (8 B)
       k_radix_scatter  per element and pass: read and write a 16-byte edge
                        record (32 B)"""
     if kernel == "k_paths":
@@ -108,7 +113,7 @@ def kernel_alg_bytes(kernel, m, units, nd=1):
     elif kernel == "k_windows":
         per = 24 + (16 + 32) * nd
     elif kernel == "k_scan_apply":
-        per = 16
+        per = 16 * nd
     elif kernel == "k_radix_scatter":
         per = 32
     else:
@@ -309,7 +314,7 @@ def kernel_table(ktime, m, k_total, steps, workload, nd=1):
         elif kname in ("k_windows", "k_scan_apply", "k_radix_scatter"):
             u = m
         if u is not None:
-            alg, per = kernel_alg_bytes(kname, m, u, nd if kname == "k_windows" else 1)
+            alg, per = kernel_alg_bytes(kname, m, u, nd if kname in ("k_windows", "k_scan_apply") else 1)
             gbs = alg / (per_launch_ms * 1e-3) / 1e9
             entry.update({"alg_bytes_per_unit": per, "alg_bytes_per_launch": alg,
                           "achieved_GBs": gbs, "frac_of_hbm_peak": gbs / HBM_PEAK_GBS})

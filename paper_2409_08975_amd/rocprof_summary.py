@@ -27,22 +27,22 @@ CALIB_BYTES = 1 << 30
 
 # kernel base name -> source file holding it
 KERNEL_SRC = {
-    "k_paths": "tc_sample.hip", "k_listcount_reg": "tc_sample.hip",
+    "k_validate": "tc_build.hip", "k_plan": "tc_build.hip", "k_start": "tc_build.hip",
+    "k_rec_xform": "tc_build.hip", "k_radix_hist": "tc_build.hip", "k_radix_hist2": "tc_build.hip",
+    "k_col_one": "tc_build.hip", "k_col_sum": "tc_build.hip", "k_col_scan": "tc_build.hip",
+    "k_col_apply": "tc_build.hip", "k_radix_scatter": "tc_build.hip", "k_fill_u32": "tc_build.hip",
+    "k_hash_clear": "tc_build.hip", "k_hash_insert": "tc_build.hip", "k_run_hist": "tc_build.hip",
+    "k_run_scatter": "tc_build.hip", "k_table_segment": "tc_build.hip", "k_table_spill": "tc_build.hip",
+    "k_emit": "tc_build.hip", "k_offsets": "tc_build.hip",
+    "k_windows": "tc_weights.hip", "k_mp_split_coarse": "tc_weights.hip", "k_mp_split": "tc_weights.hip",
+    "k_mp_rank": "tc_weights.hip", "k_combine": "tc_weights.hip", "k_scan_tiles": "tc_weights.hip",
+    "k_scan_tiles_sets": "tc_weights.hip", "k_scan_apply": "tc_weights.hip",
+    "k_scan_apply_sets": "tc_weights.hip", "k_windows_direct": "tc_weights.hip",
+    "k_scan_direct": "tc_weights.hip",
+    "k_begin": "tc_sample.hip", "k_zero_counters": "tc_sample.hip", "k_deal_count": "tc_sample.hip",
+    "k_deal_place": "tc_sample.hip", "k_paths": "tc_sample.hip", "k_listcount_reg": "tc_sample.hip",
     "k_listcount_lds": "tc_sample.hip", "k_listcount_wide": "tc_sample.hip",
-    "k_listcount_big": "tc_sample.hip", "k_listcount_w128": "tc_sample.hip",
-    "k_windows": "tc_weights.hip", "k_mp_rank": "tc_weights.hip", "k_combine": "tc_weights.hip",
-    "k_scan_tiles": "tc_weights.hip", "k_scan_tiles_sets": "tc_weights.hip", "k_scan_apply": "tc_weights.hip",
-    "k_radix_scatter": "tc_build.hip",
-    "k_radix_hist": "tc_build.hip", "k_hash_insert": "tc_build.hip", "k_emit": "tc_build.hip",
-    "k_offsets": "tc_build.hip",
-    "k_rec_xform": "tc_build.hip", "k_mp_split": "tc_weights.hip",
-    "k_mp_split_coarse": "tc_weights.hip", "k_rec_init": "tc_build.hip",
-    "k_col_sum": "tc_build.hip", "k_col_scan": "tc_build.hip", "k_col_apply": "tc_build.hip",
-    "k_hash_clear": "tc_build.hip", "k_validate": "tc_build.hip", "k_plan": "tc_build.hip",
-    "k_fold_hist": "tc_build.hip",
-    "k_init_build": "tc_build.hip", "k_trange": "tc_build.hip",
-    "k_zero_result": "tc_sample.hip", "k_store_ptrs": "tc_sample.hip",
-    "k_zero_counters": "tc_sample.hip", "k_finalize": "tc_sample.hip",
+    "k_listcount_w128": "tc_sample.hip", "k_listcount_big": "tc_sample.hip", "k_finalize": "tc_sample.hip",
 }
 IDLE_BYTES = 64 * 1024
 
