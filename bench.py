@@ -44,9 +44,9 @@ KERNEL_SRC = {"k_paths": "tc_sample.hip", "k_listcount_reg": "tc_sample.hip",
               "k_windows": "tc_weights.hip", "k_scan_apply": "tc_weights.hip",
               "k_radix_scatter": "tc_build.hip"}
 # the kernels each timed span covers, for counter-based traffic per span
-SPAN_KERNELS = {"k_windows": ["k_mp_split_coarse", "k_mp_split", "k_mp_rank", "k_combine",
-                              "k_windows_direct"],
-                "k_scan_apply": ["k_scan_apply_sets", "k_scan_direct"]}
+# (the stored profiles are of graphs past the direct form's size)
+SPAN_KERNELS = {"k_windows": ["k_mp_split_coarse", "k_mp_split", "k_mp_rank", "k_combine"],
+                "k_scan_apply": ["k_scan_apply_sets"]}
 PMC_FILES = {"bitcoin": os.path.join(ROOT, "profiles", "pmc_traffic_bitcoin.txt"),
              "medium": os.path.join(ROOT, "profiles", "pmc_traffic_medium.txt")}
 # stages of a step -> kernels whose counter traffic makes up the stage
