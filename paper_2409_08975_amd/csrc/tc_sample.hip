@@ -56,6 +56,7 @@
 
 #include "tc_device.h"
 #include "tc_internal.h"
+#include "tc_rules.h"
 
 namespace tc {
 
@@ -141,6 +142,7 @@ struct SampleArgs {
   uint64_t* fast_p;  // [fast waves][2][kKeyCap + 1]
   uint64_t* wide_p;  // [wide blocks][2][kWideCap + 1]
   uint32_t lds_cap;  // longest list of the LDS-key pass (at most kKeyCap)
+  uint32_t wide_shares;  // blocks the merged pass's tickets are shared among
   struct SpreadSums* spread;  // [kSpread][nd][n_motifs]
   MotifPlan plan;
 };
@@ -1890,31 +1892,6 @@ __device__ __forceinline__ void wide_item(WideTile& T, const int64_t* __restrict
   }
 }
 
-// Items are claimed by ticket: the first three quarters sixteen at a time, then
-// four and at the end one at a time.  The counter is one address for the whole
-// chip, which serves a claim in about 12 ns; one item a claim held the pass to
-// that, and the short end keeps the last blocks within one item of each other.
-struct WideDeal {
-  uint32_t n, t16, t4;  // items, tickets of 16, tickets of 4
-  __device__ __forceinline__ explicit WideDeal(uint32_t items) : n(items) {
-    t16 = n / 64 * 3;
-    t4 = (n - t16 * 16) / 16 * 3;
-  }
-  __device__ __forceinline__ void range(uint32_t t, uint32_t* lo, uint32_t* hi) const {
-    if (t < t16) {
-      *lo = t * 16;
-      *hi = *lo + 16;
-    } else if (t - t16 < t4) {
-      *lo = t16 * 16 + (t - t16) * 4;
-      *hi = *lo + 4;
-    } else {
-      const uint64_t i = (uint64_t)t16 * 16 + (uint64_t)t4 * 4 + (t - t16 - t4);
-      *lo = (uint32_t)(i < n ? i : n);
-      *hi = i < n ? *lo + 1 : n;
-    }
-  }
-};
-
 // 5.3e5 items of six motifs (mean 4,200 keys, lists to 7,200) take 8.3 ms
 // (12.6 with every list enumerated through 64-bit keys): 3,360 M vector
 // instructions fell to 2,690 M and the bytes read by half with the bridge; the
@@ -1934,7 +1911,7 @@ __global__ __launch_bounds__(kWBlock, 5) void k_listcount_wide(SampleArgs A, uin
   // an empty pass costs no contended claims.
   const uint32_t n_items = *A.wide_count;
   if (blockIdx.x >= n_items) return;
-  const WideDeal deal(n_items);
+  const WideDeal deal(n_items, A.wide_shares);
   sums_clear<1>(A);
   uint32_t it = 0, it_end = 0;
   for (;;) {
@@ -2475,6 +2452,9 @@ tc_status sample_batch(const tc_graph* g, const tc_weights* const* w, int nd,
   A.plan = plan;
   A.lds_cap = (uint32_t)(tune.lds_list_cap < kWave ? kWave
                          : (tune.lds_list_cap > kKeyCap ? kKeyCap : tune.lds_list_cap));
+  bool any_length = false;  // the shorter passes leave windows past 2^32 to the merged one
+  for (int d = 0; d < nd; ++d) any_length = any_length || w[d]->delta >= ((int64_t)1 << 32);
+  A.wide_shares = wide_shares((uint32_t)L.wide_blocks, any_length);
   A.c0 = 0;
   A.clen = 0;
   A.tiles_per_delta = 0;

@@ -1,0 +1,52 @@
+"""GPU tests of calls on either side of a rule that chooses how they run: the
+same results whichever way they go."""
+import numpy as np
+import pytest
+
+import synthgraph as sg
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tcb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_08975_amd as tcb
+    tcb.lib()
+    return tcb
+
+
+@pytest.fixture(scope="module")
+def torch_mod():
+    import torch
+    return torch
+
+
+def _same(torch, a, b, names=("cnt", "hits", "estimate", "status", "xmax", "e1", "e2", "e3", "X", "P")):
+    for name in names:
+        u, v = getattr(a, name), getattr(b, name)
+        assert (u is None) == (v is None)
+        assert u is None or torch.equal(u.view(torch.uint8), v.view(torch.uint8)), name
+
+
+@pytest.mark.parametrize("k", [40, 700, 3000])
+@pytest.mark.parametrize("dplus", [0, 2**33])
+def test_long_list_queue_by_blocks(tcb, torch_mod, k, dplus):
+    """Queues of items with lists past 1,024 entries: one item a claim, and
+    with 16 blocks tickets of sixteen, four and one."""
+    rng = np.random.default_rng(3)
+    src = [0] * 8 + [1] + [2] * 8 + [0] * 700 + [1] * 1100
+    dst = [1] * 8 + [2] + [3] * 8 + [3] * 1800
+    t = list(range(1, 9)) + [10] + list(range(11, 19)) + (100 + rng.integers(0, 4000, size=1800)).tolist()
+    ut = torch_mod.from_numpy
+    G = tcb.tc_build_graph(4, ut(np.array(src, np.int32)).cuda(), ut(np.array(dst, np.int32)).cuda(),
+                           ut(np.array(t, np.int64)).cuda(), check=True)
+    W = tcb.tc_path_weights(G, 5000 + dplus)
+    spine, lists = [(0, 1), (1, 2), (2, 3)], [(0, 3), (1, 3), (0, 3)]
+    motifs = [spine + lists, spine + lists[1:], spine + lists[:-1]]
+    a = tcb.tc_sample_estimate(G, W, motifs, k, 5, per_sample=True)
+    b = tcb.tc_batch_estimate(G, [W], motifs, k, 5, per_sample=True, tuning=tcb.make_tuning(wide_blocks=16))[0]
+    _same(torch_mod, a, b)
+    assert int(a.status) == 0 and int(a.hits[0]) > 0

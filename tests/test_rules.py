@@ -1,0 +1,80 @@
+"""CPU tests of the rules that decide how a call runs (csrc/tc_rules.h, plain
+constant expressions), compiled into a small program with g++."""
+import heapq
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2409_08975_amd", "csrc")
+
+DRIVER = r"""
+#include <cstdio>
+#include <cstring>
+#include "tc_rules.h"
+int main() {
+  char what[32];
+  long long a, b, c;
+  while (std::scanf("%31s %lld %lld %lld", what, &a, &b, &c) == 4) {
+    if (!std::strcmp(what, "shares")) {
+      std::printf("%u\n", tc::wide_shares((uint32_t)a, b != 0));
+    } else if (!std::strcmp(what, "tickets")) {
+      const tc::WideDeal d((uint32_t)a, (uint32_t)b);
+      for (uint32_t t = 0;; ++t) {
+        uint32_t lo, hi;
+        d.range(t, &lo, &hi);
+        if (lo == hi) break;
+        std::printf("%u:%u ", lo, hi);
+      }
+      uint32_t lo, hi;
+      d.range(0xFFFFFFFFu, &lo, &hi);
+      std::printf("%u:%u\n", lo, hi);
+    }
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, exe = d / "rules.cpp", d / "rules"
+    src.write_text(DRIVER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)],
+                   check=True)
+
+    def ask(*queries):
+        text = "".join("%s %d %d %d\n" % (q + (0,) * (4 - len(q))) for q in queries)
+        return subprocess.run([str(exe)], input=text, capture_output=True, text=True,
+                              check=True).stdout.splitlines()
+    return ask
+
+
+def _tickets(line):
+    return [tuple(map(int, x.split(":"))) for x in line.split()]
+
+
+@pytest.mark.parametrize("blocks", [1, 16, 32, 2560, 4096])
+@pytest.mark.parametrize("any_length", [False, True])
+def test_merged_pass_tickets(rules, blocks, any_length):
+    """Tickets hand out every item once, and no block is left with a row of
+    them while others idle: with items of one cost, claimed in order by
+    `blocks` blocks, the last block ends within two items of the queue's
+    share of a block (with tickets for half the blocks, once the queue is past
+    two items a block, within eight more)."""
+    shares = int(rules(("shares", blocks, any_length))[0])
+    live = min(blocks, 2560)
+    assert shares == (live + 1) // 2 if any_length else shares == live
+    sizes = [1, 2, 15, 16, 17, 63, 64, 65, 1000, 1001, 4 * shares, 4 * shares + 1, 8000, 16 * shares + 1, 40000,
+             40001, 16 * shares + 17, 200003]
+    for n, line in zip(sizes, rules(*(("tickets", n, shares) for n in sizes))):
+        *tickets, past = _tickets(line)
+        assert past == (n, n)
+        assert [lo for lo, _ in tickets] == [0] + [hi for _, hi in tickets[:-1]] and tickets[-1][1] == n
+        assert {hi - lo for lo, hi in tickets} <= {1, 4, 16}
+        ends = [0] * live
+        for lo, hi in tickets:
+            heapq.heapreplace(ends, ends[0] + hi - lo)
+        slack = 8 if any_length and n > 2 * live else 0
+        assert max(ends) <= n / live + 2 + slack, n
