@@ -7,6 +7,28 @@
 
 namespace tc {
 
+// ---- order of a chunk's samples ------------------------------------------------
+// Whether a chunk's samples are put in rank order before the path kernel.  That
+// costs two launches and 4 bytes a sample, and makes neighbouring slots share
+// lines of the graph.  One delta, not ordered and ordered, graphs of 1e5, 1e6
+// and 2e7 edges: 2.6e5 samples 66, 67, 81 and 72, 72, 86 us; 5.2e5 87, 94, 118
+// and 89, 92, 118; 7.9e5 105, 110, 147 and 103, 108, 143; 1e7 681 to 1,170 and
+// 558 to 924.  One ordering serves every delta of the call: 2.6e5 samples of
+// two 70, 82, 121 and 75, 76, 112, of four 130, 145, 213 and 119, 124, 190;
+// 7.9e5 of two 100, 128, 233 and 104, 110, 192, of four 211, 257, 439 and 179,
+// 199, 354.
+// A per-sample output array is then written far apart by neighbouring slots, a
+// partial line each.  One array (4 or 8 bytes a sample) costs less than the
+// order gains; from two arrays on the order is the slower way.  Not ordered and
+// ordered, 8e6 samples over 3e5, 3e6 and 2e7 edges: P alone 528, 773, 937 and
+// 419, 723, 920 us; P and one motif's X 534, 792, 954 and 466, 933, 1,088; e1..e3
+// and X 610, 913, 1,095 and 872, 1,372, 1,463; every output of six motifs 1,144,
+// 2,276, 3,165 and 2,465, 3,552, 4,419.
+constexpr uint32_t kOrderFrom = 3u << 18;
+constexpr bool orders_samples(uint32_t samples, uint32_t arrays) {
+  return samples >= kOrderFrom && arrays <= 1u;
+}
+
 // ---- merged ListCount pass: items per claim ------------------------------------
 // Its blocks claim tickets from one counter, which serves a claim in about
 // 12 ns.  An item claimed alone holds a pass of short items to that; sixteen

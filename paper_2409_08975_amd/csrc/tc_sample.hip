@@ -2308,12 +2308,6 @@ static int wide_blocks_for(const SampleTuning& t) {
                             : (t.wide_blocks > kMaxWideBlocks ? kMaxWideBlocks : t.wide_blocks);
 }
 
-// Whether a chunk's samples are put in rank order first.  Measured with one
-// delta, ordered against not, over graphs of 1e5, 1e6 and 2e7 edges: 2.6e5
-// samples take 79 to 94 us against 62 to 80, 5.2e5 are even, 1e6 take 117 to
-// 167 against 117 to 170, 1e7 take 558 to 924 against 681 to 1,170.
-static bool deals(uint32_t clen) { return clen >= (3u << 18); }
-
 struct SampleLayout {
   size_t win_lo, win_len, code, mid, wide, big, w128, counters, fast_p, wide_p, samp_h, deal, order,
       spread, total;
@@ -2344,7 +2338,7 @@ static SampleLayout sample_layout(uint64_t k, int nd, int32_t n_motifs, const Sa
   L.fast_p = take((size_t)L.fast_waves * 2 * (kKeyCap + 1) * 8);
   L.wide_p = take((size_t)L.wide_blocks * 2 * (kWideCap + 1) * 8);
   L.samp_h = take((size_t)nd * L.chunk * 4);
-  const bool ordered = deals((uint32_t)L.chunk);
+  const bool ordered = orders_samples((uint32_t)L.chunk, 0);
   L.deal = take(ordered ? (size_t)2 * kDealBuckets * 4 : 0);
   L.order = take(ordered ? (size_t)L.chunk * 4 : 0);
   L.spread = take((size_t)kSpread * nd * n_motifs * sizeof(SpreadSums));
@@ -2444,7 +2438,14 @@ tc_status sample_batch(const tc_graph* g, const tc_weights* const* w, int nd,
   A.w128_next = A.item_count + 7;
   A.fast_p = (uint64_t*)(base + L.fast_p);
   A.samp_h = (uint32_t*)(base + L.samp_h);
-  A.deal = deals((uint32_t)L.chunk) ? (uint32_t*)(base + L.deal) : nullptr;
+  uint32_t arrays = 0;  // per-sample output arrays of a delta
+  for (int d = 0; d < nd; ++d) {
+    const uint32_t a = (out[d]->e1 ? 3u : 0u) + (out[d]->P ? 1u : 0u) +
+                       (out[d]->X ? (uint32_t)plan.n_motifs : 0u);
+    arrays = a > arrays ? a : arrays;
+  }
+  const bool ordered = !exhaustive && orders_samples((uint32_t)L.chunk, arrays);
+  A.deal = ordered ? (uint32_t*)(base + L.deal) : nullptr;
   uint32_t* const order = (uint32_t*)(base + L.order);
   A.order = nullptr;
   A.wide_p = (uint64_t*)(base + L.wide_p);
@@ -2472,7 +2473,7 @@ tc_status sample_batch(const tc_graph* g, const tc_weights* const* w, int nd,
     if (c0 > 0)
       hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(1024), 0, st, A.item_count, A.deal);
     A.order = nullptr;
-    if (!exhaustive && deals(A.clen)) {
+    if (ordered && orders_samples(A.clen, arrays)) {
       TimedLaunch tl("k_deal", st);
       const bool large = A.clen >= kDealLarge;
       const unsigned tile = kDealBlock * (large ? 16u : 4u);

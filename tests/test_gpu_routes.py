@@ -50,3 +50,27 @@ def test_long_list_queue_by_blocks(tcb, torch_mod, k, dplus):
     b = tcb.tc_batch_estimate(G, [W], motifs, k, 5, per_sample=True, tuning=tcb.make_tuning(wide_blocks=16))[0]
     _same(torch_mod, a, b)
     assert int(a.status) == 0 and int(a.hits[0]) > 0
+
+
+@pytest.mark.parametrize("k", [786431, 786432, 2 * 786432 + 5])
+def test_sample_order_by_outputs(tcb, torch_mod, k):
+    """The same sums and per-sample outputs whichever of them are asked for:
+    none or one array (long chunks in rank order), or several (not), and in
+    chunks of 2^16."""
+    torch, g = torch_mod, sg.gen_tiny()
+    ut = torch.from_numpy
+    G = tcb.tc_build_graph(g.n, ut(g.src).cuda(), ut(g.dst).cuda(), ut(g.t).cuda())
+    Ws = tcb.tc_path_weights_batch(G, [3600, 40000])
+    h = torch.randint(1, 9, (g.m,), dtype=torch.int32, device="cuda")
+    sets = Ws + [tcb.tc_proposal_weights(G, Ws[1], h)]
+    for names in (["M4-0"], ["S5-paw", "M4-1"]):
+        motifs = [sg.MOTIFS[x] for x in names]
+        want = tcb.tc_batch_estimate(G, sets, motifs, k, 11, per_sample=True, tuning=tcb.make_tuning(chunk_log2=16))
+        for keep in ((), ("P",), ("X",), ("e1", "e2", "e3"), ("P", "X"), ("e1", "e2", "e3", "X", "P")):
+            outs = [tcb.new_result(len(motifs), k, "cuda", per_sample=True) for _ in sets]
+            for o in outs:
+                for x in ("e1", "e2", "e3", "X", "P"):
+                    if x not in keep:
+                        setattr(o, x, None)
+            for a, b in zip(tcb.tc_batch_estimate(G, sets, motifs, k, 11, outs=outs), want):
+                _same(torch, a, b, ("cnt", "hits", "estimate", "status", "xmax") + keep)

@@ -19,6 +19,8 @@ int main() {
   while (std::scanf("%31s %lld %lld %lld", what, &a, &b, &c) == 4) {
     if (!std::strcmp(what, "shares")) {
       std::printf("%u\n", tc::wide_shares((uint32_t)a, b != 0));
+    } else if (!std::strcmp(what, "order")) {
+      std::printf("%d\n", tc::orders_samples((uint32_t)a, (uint32_t)b));
     } else if (!std::strcmp(what, "tickets")) {
       const tc::WideDeal d((uint32_t)a, (uint32_t)b);
       for (uint32_t t = 0;; ++t) {
@@ -78,3 +80,12 @@ def test_merged_pass_tickets(rules, blocks, any_length):
             heapq.heapreplace(ends, ends[0] + hi - lo)
         slack = 8 if any_length and n > 2 * live else 0
         assert max(ends) <= n / live + 2 + slack, n
+
+
+def test_sample_order_and_outputs(rules):
+    """Long chunks are put in rank order, which scatters the per-sample
+    outputs, only for at most one output array a sample."""
+    sizes = [1, 1 << 16, (3 << 18) - 1, 3 << 18, 10**6, 1 << 25]
+    for arrays in (0, 1, 2, 3, 5, 20):
+        got = [int(x) for x in rules(*(("order", n, arrays) for n in sizes))]
+        assert got == [int(n >= 3 << 18 and arrays <= 1) for n in sizes]
