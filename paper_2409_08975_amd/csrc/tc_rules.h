@@ -7,6 +7,37 @@
 
 namespace tc {
 
+// ---- windows of small graphs ---------------------------------------------------
+// Whether every edge's windows are searched by its own thread in the lists of
+// its end vertices (two launches) instead of by merge passes (seven).  Searches
+// in the source's lists share lines with their neighbours in scan order; those
+// in the destination's lists do not, and leave the XCD's L2 as the graph grows,
+// the sooner the longer the lists.  Every delta adds a search to the first way
+// and little to the second.  The lines, in 65,536 edges, lie below the first
+// size at which the searches were the slower way on any of twenty graphs: degree
+// exponents of 1.8 to 2.4 with 2 to 20 edges a vertex, and (long lists, 128
+// edges a vertex and more) uniform and skewed ones of 20 to 2,000 vertices.
+// Merge passes and searches, us, exponent 1.8, 20 edges a vertex:
+//   both sides, one delta    786,432 edges 113 and 113
+//   both sides, two          589,824 131 and 123, 655,360 131 and 140
+//   both sides, four         589,824 205 and 195, 655,360 204 and 223
+//   destination only, one    524,288 75 and 63, 589,824 84 and 87
+//   destination only, four   458,752 130 and 114, 524,288 131 and 140
+//   source only, one, eight  786,432 76 and 44, 263 and 138
+// 300 vertices:
+//   both sides, one, four    524,288 92 and 71, 150 and 157; 458,752 143 and 136
+//   destination, one, eight  524,288 73 and 64; 393,216 147 and 168
+constexpr int64_t kDirectEdges = (int64_t)12 << 16;  // the most any call searches
+constexpr bool direct_windows(int64_t n, int64_t m, int deltas, bool source, bool destination) {
+  // one, two, three or four, five to eight deltas
+  constexpr uint8_t both[2][4] = {{12, 9, 9, 9}, {8, 8, 7, 6}};
+  constexpr uint8_t dest[2][4] = {{8, 8, 7, 7}, {8, 7, 6, 5}};
+  const int lists = m >= 128 * n ? 1 : 0;
+  const int d = deltas <= 2 ? deltas - 1 : (deltas <= 4 ? 2 : 3);
+  const int64_t line = !destination ? 12 : (source ? both[lists][d] : dest[lists][d]);
+  return m > 0 && m <= line << 16;
+}
+
 // ---- order of a chunk's samples ------------------------------------------------
 // Whether a chunk's samples are put in rank order before the path kernel.  That
 // costs two launches and 4 bytes a sample, and makes neighbouring slots share

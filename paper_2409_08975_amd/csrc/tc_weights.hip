@@ -33,6 +33,7 @@
 
 #include "tc_device.h"
 #include "tc_internal.h"
+#include "tc_rules.h"
 
 namespace tc {
 
@@ -782,17 +783,14 @@ __global__ __launch_bounds__(kWBlock) void k_scan_apply_sets(ScanSets J, int64_t
 }
 
 // ---- small graphs ------------------------------------------------------------
-// Below kDirectEdges the merge passes above are launches of a few blocks whose
-// time is their chains of dependent reads, side 3 waits for side 1, and its
-// records for their gather.  One thread per scan position then searches its
-// own windows in the two vertices' lists, whose bounds the offset arrays give
-// (both sides and both ends side by side), and the scan's blocks add up the
-// tile sums before them instead of waiting for a scan of them: two launches
-// instead of seven.  One delta: 131,071 edges 48.8 -> 18.5 us, 262,143 63.6 ->
-// 26.9, 524,287 73.6 -> 49.6, but 1,000,001 94 -> 103 (every search then
-// leaves the XCD's L2), so the line lies between the last two; four deltas
-// cross at the same size (158 -> 111, 205 -> 246).
-constexpr int64_t kDirectEdges = 3 << 18;
+// On small graphs (direct_windows) the merge passes above are launches of a few
+// blocks whose time is their chains of dependent reads, side 3 waits for side
+// 1, and its records for their gather.  One thread per scan position then
+// searches its own windows in the two vertices' lists, whose bounds the offset
+// arrays give (both sides and both ends side by side), and the scan's blocks
+// add up the tile sums before them instead of waiting for a scan of them: two
+// launches instead of seven.  One delta: 131,071 edges 48.8 -> 18.5 us, 262,143
+// 63.6 -> 26.9, 524,287 73.6 -> 49.6.
 constexpr int kDirectBlock = 256;
 constexpr int kDirectPerTile = kWTile / kDirectBlock;
 constexpr int kDirectTiles = (int)(kDirectEdges / kDirectBlock);
@@ -1059,7 +1057,7 @@ tc_status path_weights_batch(const tc_graph* g, const int64_t* deltas, int nd,
     SS.status[i] = w[i].status;
     SS.T[i] = tree_out(&w[i]);
   }
-  if (m > 0 && m <= kDirectEdges) {
+  if (direct_windows(g->n, m, nd, cls.mode1 != TC_SIDE_NONE, cls.mode3 != TC_SIDE_NONE)) {
     DirectArgs A{};
     A.src = g->out_src;
     A.dst = g->out_dst;

@@ -74,3 +74,25 @@ def test_sample_order_by_outputs(tcb, torch_mod, k):
                         setattr(o, x, None)
             for a, b in zip(tcb.tc_batch_estimate(G, sets, motifs, k, 11, outs=outs), want):
                 _same(torch, a, b, ("cnt", "hits", "estimate", "status", "xmax") + keep)
+
+
+@pytest.mark.parametrize("m", [5 << 16, (6 << 16) + 1, (7 << 16) + 1, (1 << 19) + 1, 9 << 16, (9 << 16) + 1])
+@pytest.mark.parametrize("cls", [(1, 0, 2, 1), (0, 0, 1, 3), (2, 1, 0, 0)])
+def test_windows_by_class_and_count(tcb, torch_mod, m, cls):
+    """One to three deltas of a class give the same words whether the edges
+    are searched one by one or the merge passes run: each set of a call of
+    three equals its own call, and the columns equal ranks of composite keys."""
+    from test_gpu_kernels import test_direct_windows_match_general_definition as against_ranks
+    torch = torch_mod
+    against_ranks(tcb, torch, m, cls)
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    src, dst = (torch.randint(0, 5000, (m,), device="cuda", generator=gen).int() for _ in "ab")
+    t = torch.randint(0, 10**6, (m,), device="cuda", generator=gen)
+    G = tcb.tc_build_graph(5000, src, dst, t, check=True)
+    deltas = [4000, 7, 90000]
+    assert tcb.tc_path_weights_batch(G, deltas * 2, cls=cls)[5].total() == tcb.tc_path_weights(G, 90000, cls=cls).total()
+    for d, w in zip(deltas, tcb.tc_path_weights_batch(G, deltas, cls=cls)):
+        one = tcb.tc_path_weights(G, d, cls=cls)
+        for name, x in w.arrays().items():
+            assert torch.equal(x, one.arrays()[name]), name
+        assert torch.equal(w.view("prec", torch.int64, 4 * m), one.view("prec", torch.int64, 4 * m))

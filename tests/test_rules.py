@@ -21,6 +21,8 @@ int main() {
       std::printf("%u\n", tc::wide_shares((uint32_t)a, b != 0));
     } else if (!std::strcmp(what, "order")) {
       std::printf("%d\n", tc::orders_samples((uint32_t)a, (uint32_t)b));
+    } else if (!std::strcmp(what, "direct")) {  // c: source, destination, vertices
+      std::printf("%d\n", tc::direct_windows(c >> 2, a, (int)b, (c & 1) != 0, (c & 2) != 0));
     } else if (!std::strcmp(what, "tickets")) {
       const tc::WideDeal d((uint32_t)a, (uint32_t)b);
       for (uint32_t t = 0;; ++t) {
@@ -89,3 +91,22 @@ def test_sample_order_and_outputs(rules):
     for arrays in (0, 1, 2, 3, 5, 20):
         got = [int(x) for x in rules(*(("order", n, arrays) for n in sizes))]
         assert got == [int(n >= 3 << 18 and arrays <= 1) for n in sizes]
+
+
+# Sizes (in 65,536 edges) up to which searching every edge's windows was
+# measured faster than the merge passes, and the first at which it was slower
+# on some graph: with fewer than 128 edges a vertex, and with more.
+@pytest.mark.parametrize("sides,deltas,faster,slower,long_faster,long_slower", [
+    (3, 1, 12, None, 8, 9), (3, 2, 9, 10, 8, 9), (3, 4, 9, 10, 7, 8), (3, 8, 9, 11, 6, 7), (2, 1, 8, 9, 8, 9),
+    (2, 2, 8, 9, 7, 8), (2, 4, 7, 8, 6, 7), (2, 8, 7, 8, 5, 6), (1, 1, 12, None, 12, None), (1, 8, 12, None, 12, None)])
+def test_windows_of_small_graphs(rules, sides, deltas, faster, slower, long_faster, long_slower):
+    """Windows are searched edge by edge only at sizes where that was not
+    measured slower on any of the graphs, and at all of them up to 5 * 2^16."""
+    line = [m for m in range(1, 14 << 16, 4096)] + [k << 16 for k in range(1, 15)]
+    for n, top, bad in ((1 << 16, faster, slower), (300, long_faster, long_slower)):
+        ask = [("direct", m, deltas, sides | n << 2) for m in line]
+        got = dict(zip(line, map(int, rules(*ask))))
+        assert all(got[m] for m in line if m <= 5 << 16)
+        assert not any(got[m] for m in line if m > top << 16)
+        assert bad is None or not got[bad << 16]
+    assert rules(("direct", 0, deltas, sides | 4)) == ["0"]
