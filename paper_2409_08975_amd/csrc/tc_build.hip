@@ -27,6 +27,7 @@
 
 #include "tc_device.h"
 #include "tc_internal.h"
+#include "tc_rules.h"
 
 namespace tc {
 
@@ -1132,7 +1133,7 @@ __global__ __launch_bounds__(256) void k_hash_insert(PairKeys K, PairSlot* __res
 // the tables it serves (up to 2^27 slots: 10^8 edges).  Larger ones would
 // take a second grouping pass, which costs what the atomics do, and below
 // 2^21 slots (0.8*10^6 edges) the atomics' 25 us are less than three more
-// launches: both take k_hash_insert.
+// launches: both take k_hash_insert, as graphs of few vertices do (few_pairs).
 constexpr int kSegLog2 = 14, kMaxSegLog2 = 15, kMaxGroupLog2 = 12, kGroupFromLog2 = 21;
 static_assert(1 << (kGroupFromLog2 - kSegLog2) >= kMinBins, "whole rows of the column scan");
 constexpr int kMaxGroups = 1 << kMaxGroupLog2;
@@ -1515,7 +1516,7 @@ tc_status build_graph(int32_t n, int64_t m, const int32_t* src, const int32_t* d
                        low);
   hipLaunchKernelGGL(k_plan, dim3(1), dim3(kMaxFound), 0, st, (const Found*)found, nfound, m,
                      vbits, plan, g->status, g->t_range, spill_count);
-  const int lg = g->pair_hash_log2, glog2 = group_log2(lg);
+  const int lg = g->pair_hash_log2, glog2 = few_pairs(n, m) ? 0 : group_log2(lg);
   const int64_t cap = (int64_t)1 << lg;
   if (m == 0) {
     hipLaunchKernelGGL(k_hash_clear, dim3(blocks_for(cap, 256)), dim3(256), 0, st,

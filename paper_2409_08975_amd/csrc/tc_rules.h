@@ -7,6 +7,16 @@
 
 namespace tc {
 
+// ---- run table of the build ----------------------------------------------------
+// Whether the graph's runs are few for its edges: n vertices have at most n^2
+// pairs.  Grouping the runs by table segment costs per edge, inserting them one
+// by one per run, and few runs are long ones, whose ends both ways search for.
+// The whole build, grouped and inserted, us: 3e6 edges of 40, 1,000 and 1,700
+// vertices 429, 510, 588 and 388, 499, 624; 2e7 of 40, 1,000 and 3,000 1,750,
+// 2,355, 2,509 and 1,632, 2,312, 2,772; 6e7 of 40, 1,700 and 5,500 5,180, 8,310,
+// 7,578 and 4,710, 8,107, 8,682.
+constexpr bool few_pairs(int64_t n, int64_t m) { return n * n < m / 8; }
+
 // ---- windows of small graphs ---------------------------------------------------
 // Whether every edge's windows are searched by its own thread in the lists of
 // its end vertices (two launches) instead of by merge passes (seven).  Searches

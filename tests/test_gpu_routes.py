@@ -96,3 +96,11 @@ def test_windows_by_class_and_count(tcb, torch_mod, m, cls):
         for name, x in w.arrays().items():
             assert torch.equal(x, one.arrays()[name]), name
         assert torch.equal(w.view("prec", torch.int64, 4 * m), one.view("prec", torch.int64, 4 * m))
+
+
+@pytest.mark.parametrize("n,m", [(1, 1700001), (2, 1700001), (460, 1700001), (461, 1700001), (612, 3000001)])
+def test_run_table_by_vertices(tcb, torch_mod, n, m):
+    """Graphs of few vertices, whose runs are inserted one by one, and the
+    first that are grouped: every run is found and no other key is there."""
+    from test_gpu_kernels import test_pair_table_finds_every_run as finds_every_run
+    finds_every_run(tcb, torch_mod, n, m)

@@ -23,6 +23,8 @@ int main() {
       std::printf("%d\n", tc::orders_samples((uint32_t)a, (uint32_t)b));
     } else if (!std::strcmp(what, "direct")) {  // c: source, destination, vertices
       std::printf("%d\n", tc::direct_windows(c >> 2, a, (int)b, (c & 1) != 0, (c & 2) != 0));
+    } else if (!std::strcmp(what, "few")) {
+      std::printf("%d\n", tc::few_pairs(a, b));
     } else if (!std::strcmp(what, "tickets")) {
       const tc::WideDeal d((uint32_t)a, (uint32_t)b);
       for (uint32_t t = 0;; ++t) {
@@ -110,3 +112,14 @@ def test_windows_of_small_graphs(rules, sides, deltas, faster, slower, long_fast
         assert not any(got[m] for m in line if m > top << 16)
         assert bad is None or not got[bad << 16]
     assert rules(("direct", 0, deltas, sides | 4)) == ["0"]
+
+
+@pytest.mark.parametrize("m,inserted,grouped", [
+    (1700000, 400, 1000), (3 * 10**6, 400, 1700), (5 * 10**6, 700, 1700), (10**7, 700, 1700), (2 * 10**7, 1000, 3000),
+    (6 * 10**7, 1700, 5500)])
+def test_run_table_of_few_vertices(rules, m, inserted, grouped):
+    """Vertex counts at which inserting the runs one by one was measured the
+    faster build, and at which grouping them was; the largest counts do not
+    overflow."""
+    ask = [1, 2, 40, inserted, grouped, 30000, 2**31 - 1]
+    assert rules(*(("few", n, m) for n in ask)) == ["1"] * 4 + ["0"] * 3
