@@ -1428,7 +1428,10 @@ static GraphLayout graph_layout(int32_t n, int64_t m) {
     return at;
   };
   const size_t M = (size_t)m;
-  const int64_t ntiles = sort_tiles(m);
+  // rows of the count matrices: never fewer than a smaller graph's, whose
+  // smaller tiles can be more, so that a workspace serves every smaller graph
+  const int64_t most = sort_tiles(kLargeFrom - 1);
+  const int64_t ntiles = large_tiles(m) && sort_tiles(m) < most ? most : sort_tiles(m);
   L.out_off = take(((size_t)n + 1) * 4);
   L.in_off = take(((size_t)n + 1) * 4);
   L.out_src = take(M * 4);

@@ -2340,7 +2340,9 @@ static SampleLayout sample_layout(uint64_t k, int nd, int32_t n_motifs, const Sa
   L.samp_h = take((size_t)nd * L.chunk * 4);
   const bool ordered = orders_samples((uint32_t)L.chunk, 0);
   L.deal = take(ordered ? (size_t)2 * kDealBuckets * 4 : 0);
-  L.order = take(ordered ? (size_t)L.chunk * 4 : 0);
+  // (for every delta, though one order serves them all: a chunk of fewer
+  // deltas is longer, and a workspace for more deltas has to hold it)
+  L.order = take(ordered ? (size_t)nd * L.chunk * 4 : 0);
   L.spread = take((size_t)kSpread * nd * n_motifs * sizeof(SpreadSums));
   L.total = o;
   return L;

@@ -986,7 +986,9 @@ static WeightsLayout weights_layout(int64_t m) {
   L.S = take((size_t)T.count[0] * 8);
   L.tree = take(T.total_words * 8);
   L.status = take(4);
-  L.tile_sums = take((m <= kDirectEdges ? (size_t)kDirectTiles : ntiles) * 16);
+  // the sums of k_windows_direct's blocks or of tiles; no fewer for a larger
+  // graph, so that a workspace serves every smaller one
+  L.tile_sums = take((ntiles < (size_t)kDirectTiles ? (size_t)kDirectTiles : ntiles) * 16);
   L.tile_off = take(ntiles * 8);
   L.prec = take(M * 32);
   L.total = o;
