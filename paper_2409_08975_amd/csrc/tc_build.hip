@@ -1017,11 +1017,8 @@ static bool time_sort(const BuildPlan* plan, const EdgeCols& ec, uint4* b0, uint
     R.buf[1] = b1;
     R.xf1 = xf1;
     R.ec = ec;
-    // the passes past 33 bits work only for ranges that wide: their launches
-    // take up to eight tiles per block, so that idle ones cost a few
-    // microseconds
-    const int64_t hb = ((ntiles + 63) / 64) * 8;
-    const unsigned grid = (unsigned)(p >= 3 && hb < ntiles ? hb : ntiles);
+    // the passes past 33 bits work only for ranges that wide
+    const unsigned grid = (unsigned)(p >= 3 ? late_pass_blocks(ntiles) : ntiles);
     if (p == 0)
       radix_pass<RP_COLS>(R, false, false, m, grid, sc, st);
     else

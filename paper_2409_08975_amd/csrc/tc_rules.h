@@ -7,6 +7,21 @@
 
 namespace tc {
 
+// ---- late passes of the time sort ----------------------------------------------
+// Blocks of the passes that only time ranges past 33 bits use (milliseconds over
+// a year have 35).  Others leave them idle, and an idle block costs its launch:
+// an eighth of the tiles, but as many as the CUs hold at once, which an active
+// pass needs.  A multiple of 8 where it is not every tile (tiles go to the XCDs
+// by their index mod 8).  The build with an eighth of the tiles and with these:
+// 36-bit times, 5e5 edges 307 and 270 us, 2e6 468 and 410, 5e6 1,051 and 1,012;
+// 60-bit times, 5e5 462 and 307, 2e6 838 and 609; 22-bit times (the passes idle)
+// 249 and 246, 369 and 372, 946 and 949.
+constexpr int64_t late_pass_blocks(int64_t ntiles) {
+  const int64_t eighth = (ntiles + 63) / 64 * 8, resident = 2 * 256;
+  const int64_t b = eighth > resident ? eighth : resident;
+  return b < ntiles ? b : ntiles;
+}
+
 // ---- run table of the build ----------------------------------------------------
 // Whether the graph's runs are few for its edges: n vertices have at most n^2
 // pairs.  Grouping the runs by table segment costs per edge, inserting them one

@@ -25,6 +25,8 @@ int main() {
       std::printf("%d\n", tc::direct_windows(c >> 2, a, (int)b, (c & 1) != 0, (c & 2) != 0));
     } else if (!std::strcmp(what, "few")) {
       std::printf("%d\n", tc::few_pairs(a, b));
+    } else if (!std::strcmp(what, "late")) {
+      std::printf("%lld\n", (long long)tc::late_pass_blocks(a));
     } else if (!std::strcmp(what, "tickets")) {
       const tc::WideDeal d((uint32_t)a, (uint32_t)b);
       for (uint32_t t = 0;; ++t) {
@@ -123,3 +125,11 @@ def test_run_table_of_few_vertices(rules, m, inserted, grouped):
     overflow."""
     ask = [1, 2, 40, inserted, grouped, 30000, 2**31 - 1]
     assert rules(*(("few", n, m) for n in ask)) == ["1"] * 4 + ["0"] * 3
+
+
+def test_late_time_passes_fill_the_chip(rules):
+    """Passes of wide time ranges get a block per tile up to the 512 blocks
+    the CUs hold, then at least those and an eighth of the tiles."""
+    tiles = [1, 7, 8, 160, 489, 511, 512, 513, 1221, 4095, 4096, 4883, 73243]
+    for n, b in zip(tiles, map(int, rules(*(("late", n) for n in tiles)))):
+        assert b == n if n <= 512 else 512 <= b <= max(512, n // 8 + 8) and b % 8 == 0
