@@ -1323,8 +1323,9 @@ int pair_hash_log2(int64_t m) {
 
 // sorted records (key, eid, other, t - t_min) -> columns of one order, for a
 // graph of a single vertex (its vertex sorts have no pass whose last one
-// would write the columns).  The time is t_min + the record's time word, or,
-// when the range is wider than 32 bits, read back from the input by edge id.
+// would write the columns).  The time is t_min + the record's time word and the
+// bits above it in a vertex word (rec_time): with no vertex bits there is room
+// for every range, so none is read back from the input.
 // With `off` (n + 1 entries), also the CSR offsets of the sorted keys:
 // off[v] = first position whose key is >= v, written by the thread of the
 // position where the key passes v (grid of m + 1 threads).  With `skip`

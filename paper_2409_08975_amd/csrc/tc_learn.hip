@@ -584,11 +584,12 @@ __device__ __forceinline__ Label load_label(const BatchMap& bm, const uint16_t* 
 
 // Sum over the 32 lanes of each half of 64 values per lane, spread out: at
 // step OFF a lane keeps half of its values and adds the copies of them that
-// lane i ^ OFF holds, so the 64 sums cost 62 additions instead of 320, each
-// formed by the same tree as a butterfly over the lanes.  Lane i is left
-// with the sums of values 2 i and 2 i + 1 in val[0] and val[1].  Inside a row
-// of 16 lanes the other lane's value is a DPP operand (rotations by 8, by
-// 12 or 4, quad permutations); rows are exchanged by a bpermute.
+// lane i ^ OFF holds, so the 64 sums cost 92 additions and 94 selects instead of
+// 320 additions (a DPP step adds both candidates and selects afterwards), each
+// formed by the same tree as a butterfly over the lanes.  Lane i is left with
+// the sums of values 2 i and 2 i + 1 in val[0] and val[1].  Inside a row of 16
+// lanes the other lane's value is a DPP operand (rotations by 8, by 12 or 4,
+// quad permutations); rows are exchanged by a bpermute.
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v) {
   return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(

@@ -375,14 +375,6 @@ __device__ __forceinline__ void key_window(const SampleArgs& A, const PathRec& P
   *hi = sg + 1 < A.plan.n_anchor ? P.T[sg + 1] - 1 : P.T[0] + delta;
 }
 
-// Seven wavefronts per SIMD (72 VGPRs, a few spilled): the kernel waits on
-// round trips, and with the samples in rank order most of them end in L2.
-// 1e7 samples, 2e7 edges: 2,185 us against 2,471 with five (no spills) and
-// 2,332 with eight; the general form 1,158 us a launch against 1,350.
-// GENERAL = false is the form for the <-,+,<,>> class with the anchor ranks
-// in path order (e1, centre, e3) and random draws, with those choices fixed
-// at compile time (fewer live registers); GENERAL = true reads them from the
-// plan (any class, wedges, the exhaustive mode).
 // An edge of a side's window: a uniform position among its `len`, or with
 // window factors (prefix sums `ps` over the side's CSR) position j with
 // probability (ps[lo+j+1] - ps[lo+j]) / (ps[lo+len] - ps[lo]): a uniform
@@ -517,6 +509,14 @@ __global__ __launch_bounds__(kDealBlock) void k_deal_place(SampleArgs A, const u
   for (uint32_t p = tid; p < n; p += kDealBlock) order[s_shift[s_b[p]] + p] = s_si[p];
 }
 
+// Seven wavefronts per SIMD (72 VGPRs, a few spilled): the kernel waits on
+// round trips, and with the samples in rank order most of them end in L2.
+// 1e7 samples, 2e7 edges: 2,185 us against 2,471 with five (no spills) and
+// 2,332 with eight; the general form 1,158 us a launch against 1,350.
+// GENERAL = false is the form for the <-,+,<,>> class with the anchor ranks
+// in path order (e1, centre, e3) and random draws, with those choices fixed
+// at compile time (fewer live registers); GENERAL = true reads them from the
+// plan (any class, wedges, the exhaustive mode).
 template <bool GENERAL>
 __global__ __launch_bounds__(kSBlock, 7) void k_paths(SampleArgs A) {
   __shared__ PathRec s_path[kSBlock];
