@@ -24,9 +24,11 @@
  *     least the size reported by the *_workspace_bytes queries, 256-byte
  *     aligned (as hipMalloc and torch allocations are: the 64-bit atomics
  *     and 16-byte records inside them need it); a null or misaligned
- *     workspace gives TC_E_ARG, a short one TC_E_WORKSPACE.  tc_graph and
- *     tc_weights then hold pointers into those workspaces (borrowed: keep the
- *     workspace alive while the struct is used).  There is no free call.
+ *     workspace gives TC_E_ARG, a short one TC_E_WORKSPACE.  No query falls
+ *     as one of its sizes grows: a workspace for the largest call a program
+ *     makes serves the smaller ones.  tc_graph and tc_weights then hold
+ *     pointers into those workspaces (borrowed: keep the workspace alive
+ *     while the struct is used).  There is no free call.
  *   - Host-checkable argument errors are returned synchronously and nothing
  *     is enqueued.  Data-dependent errors are recorded as bits of a device
  *     status word (TC_F_*); results guarded by a non-zero status word are
